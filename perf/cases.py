@@ -20,7 +20,7 @@ MB = 1 << 20
 STATUS_CODES = {name: code for code, name in rei.STATUS.items()}
 
 
-def _case(family, entry, count=1, costs="1,1,1,1,1", max_cost=0, cache_mb=1024, le=0, p=10,
+def _case(family, entry, count=1, costs="1,1,1,1,1", max_cost=12, cache_mb=1024, le=0, p=10,
           max_errors=0, on_the_fly=False):
     return {"family": family, "entry": entry, "count": count, "costs": costs, "max_cost": max_cost,
             "cache_mb": cache_mb, "le": le, "p": p, "max_errors": max_errors, "on_the_fly": on_the_fly}
@@ -29,7 +29,7 @@ def _case(family, entry, count=1, costs="1,1,1,1,1", max_cost=0, cache_mb=1024, 
 def listed():
     return [
         # one small question asked once: staged, solved, printed, given back
-        dict(_case("plain", "one_shot", cache_mb=64), name="plain one-shot"),
+        dict(_case("plain", "one_shot", max_cost=12, cache_mb=64), name="plain one-shot"),
         # one mid-sized staged specification (2-4 words per language), an easy or a deep one
         dict(_case("single", "solve", count=8, max_cost=18), name="single solves"),
         # the benchmark's flagship: a few large ternary specifications at once (8-16 words)
@@ -119,7 +119,7 @@ def _specs(case, seed):
         else:
             gen = I.type1_instance if kind == "type1" else I.type2_instance
             it = gen(sub, case["p"], case["p"], case["le"], costs=costs, max_cost=cap)
-        out.append((it, min(it.max_cost, cap) if cap else it.max_cost, cache))
+        out.append((it, min(it.max_cost, cap), cache))
     return out
 
 
@@ -146,23 +146,31 @@ def prepare(case, seed):
     return state
 
 
-LEVELS, CHARS = 272, 512  # levels and expression bytes that the outputs have room for
-
-
-def _outputs(results):
-    """Everything a search returns, as arrays over the specifications."""
+def _outputs(results, max_cost):
+    """Everything a search returns, as arrays over the specifications.  No
+    search goes beyond level max_cost, and no expression of that cost takes
+    more than four bytes per unit of it."""
+    levels, chars = max_cost + 1, 4 * max_cost
     n = len(results)
-    head = np.zeros((n, 6), dtype=np.int64)
-    regex = np.zeros((n, CHARS), dtype=np.uint8)
-    unique = np.zeros((n, LEVELS), dtype=np.int64)
-    candidates = np.zeros((n, LEVELS), dtype=np.int64)
-    for k, r in enumerate(results):
-        text = r.regex.encode()
-        head[k] = (STATUS_CODES[r.status], r.cost, r.first_level, r.total_unique, r.ic_size, r.cs_words)
-        regex[k, :len(text)] = np.frombuffer(text, dtype=np.uint8)
-        unique[k, :len(r.unique)] = r.unique
-        candidates[k, :len(r.candidates)] = r.candidates
-    return {"head": head, "regex": regex, "unique": unique, "candidates": candidates}
+    head = np.array([(STATUS_CODES[r.status], r.cost, r.first_level, r.total_unique, r.ic_size, r.cs_words)
+                     for r in results], dtype=np.int64)
+    text = [r.regex.encode() for r in results]
+    return {"head": head, "regex": _padded(b"".join(text), [len(t) for t in text], n, chars, np.uint8),
+            "unique": _padded([u for r in results for u in r.unique], [len(r.unique) for r in results], n,
+                              levels, np.int64),
+            "candidates": _padded([u for r in results for u in r.candidates],
+                                  [len(r.candidates) for r in results], n, levels, np.int64)}
+
+
+def _padded(values, lengths, n, width, dtype):
+    """n rows of `width` values, row k holding the next lengths[k] of `values`."""
+    flat = np.frombuffer(values, dtype=dtype) if isinstance(values, bytes) else np.array(values, dtype=dtype)
+    lengths = np.array(lengths, dtype=np.int64)
+    if lengths.max() > width:
+        raise ValueError(f"a result has more than {width} values")
+    out = np.zeros((n, width), dtype=dtype)
+    out[np.arange(width) < lengths[:, None]] = flat
+    return out
 
 
 def _solve_all(state):
@@ -181,7 +189,7 @@ def _solve_all(state):
 
 
 def run(state):
-    return _outputs(_solve_all(state))
+    return _outputs(_solve_all(state), state["case"]["max_cost"])
 
 
 _work_memo = {}
