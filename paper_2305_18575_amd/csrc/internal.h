@@ -254,8 +254,9 @@ struct ConcatPart {
   uint64_t e0, e1;                  // block-local candidate range
   uint64_t i_lo, i_hi;              // left rows of the range (set by the launcher)
   uint32_t rel0;                    // chunk-relative index of candidate e0
-  uint32_t yt, xi, gx;              // right tiles and left rows per workgroup, tile groups (launcher)
-  uint32_t wg0, pad;                // first workgroup of this part (launcher)
+  uint32_t yt, xi, gx;              // tiles and uniform rows per workgroup, tile groups (launcher)
+  uint32_t wg0;                     // first workgroup of this part (launcher)
+  uint32_t left;                    // left rows across the lanes, else right rows (launcher)
 };
 struct ConcatSet {
   uint32_t n, pad;

@@ -105,62 +105,61 @@ __global__ __launch_bounds__(256) void gen_star(GenArgs a) {
   }
 }
 
-// x.y, bit-sliced over 64 right operands.  A workgroup owns YT tiles of 64
-// rows of the right level (transposed into LDS: Yt[tile][w], bit t = row t
-// contains word w) and a group of left rows.  For a left row x, lane l of a
-// wave owns word w = 64k + l of output word k; the cuts (u, v) of w with u in
-// x select which Yt[v] are or-ed:  out_t(w) = OR_{(u,v) cut of w, x(u)=1} y_t(v)
+// x.y, bit-sliced over 64 values of one operand.  A workgroup owns up to YT
+// tiles of 64 rows of the operand across the lanes (transposed into LDS:
+// Yt[tile][w], bit t = row t contains word w) and a group of rows of the
+// other, uniform, operand.  Right rows across the lanes (kLeft = false): for
+// a left row x, lane l of a wave owns word w = 64k + l of output word k; the
+// cuts (u, v) of w with u in x select which Yt[v] are or-ed:
+//   out_t(w) = OR_{(u,v) cut of w, x(u)=1} y_t(v)
 // (Algorithm 2, the fold over the guide table, done for 64 candidates at once).
-// A wave transpose then gives lane t the W words of candidate (x, y_t).
+// Left rows across the lanes (kLeft = true): the mirror image, the uniform
+// right row y selects by v and Yt[u] are or-ed.
+// A wave transpose then gives lane t the W words of its candidate.
+// Half of a level's blocks pair a huge left level with a right level of 2, 4,
+// 5, ... rows: with right rows across the lanes only, those filled 2 to 24 of
+// 64 lanes and took most of the launch.  With the left form for them, searches
+// of 0.5-3.5 G candidates went 175.6 -> 99.6 ms (one word per language, 58
+// infixes), 88.7 -> 31.3 ms (two words, 95), 22.1 -> 9.2 ms (four words, 130).
 constexpr int kConcatYT = 8;
 
 // kShort: every word has at most 32 cuts (length <= 31), so the cuts whose
-// prefix is in x fit one 32-bit mask per output word; otherwise the prefix
-// bit is tested inside the fold.
+// factor is in the uniform row fit one 32-bit mask per output word; otherwise
+// that bit is tested inside the fold.
 // kGtLds: the guide table is staged in LDS.  The choice is made at compile
 // time so that every access has a fixed address space: reading LDS through a
 // generic pointer (chosen at run time between LDS and global memory) gave
 // wrong prefix bits now and then on gfx950.
-template <int W, bool kShort, bool kInl, bool kGtLds>
-__global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
-  extern __shared__ uint64_t lds[];
-  if (a.st->stop) return;
-  // this workgroup's part (block) and its place in the part's grid
-  uint32_t part = 0;
-  while (part + 1 < cs.n && cs.p[part + 1].wg0 <= blockIdx.x) ++part;
-  const ConcatPart& cp = cs.p[part];
-  a.lstart = cp.lstart;
-  a.rstart = cp.rstart;
-  a.rcount = cp.rcount;
-  a.e0 = cp.e0;
-  a.e1 = cp.e1;
-  a.rel0 = cp.rel0;
-  const uint32_t yt_per_wg = cp.yt, xi_per_wg = cp.xi, n_tile_groups = cp.gx;
-  const uint64_t i_lo = cp.i_lo, i_hi = cp.i_hi;
-  const uint32_t bid = blockIdx.x - cp.wg0;
+template <int W, bool kShort, bool kInl, bool kGtLds, bool kLeft>
+__device__ __forceinline__ void concat_part(const GenArgs& a, const ConcatPart& cp, uint32_t bid, uint64_t* lds) {
+  const uint32_t yt_per_wg = cp.yt, xi_per_wg = cp.xi;
   uint64_t* Yt = lds;                                        // [yt_per_wg][64W]
   uint64_t* Xs = Yt + (size_t)yt_per_wg * 64 * W;            // [xi_per_wg][W]
   uint32_t* G = (uint32_t*)(Xs + (size_t)xi_per_wg * W);     // guide pairs (if gt_lds)
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t nR = a.rcount;
-  const uint64_t nT = (nR + 63) / 64;
-  // flat grid: workgroup -> (group of right tiles, group of left rows)
-  const uint64_t t0 = (uint64_t)(bid % n_tile_groups) * yt_per_wg;
+  const uint64_t nR = cp.rcount;
+  // rows [l0, l1) of the lane operand, [u0, u1) of the uniform one
+  const uint64_t l0 = kLeft ? cp.i_lo : 0, l1 = kLeft ? cp.i_hi + 1 : nR;
+  const uint64_t u0 = kLeft ? 0 : cp.i_lo, u1 = kLeft ? nR : cp.i_hi + 1;
+  const uint64_t lane_start = kLeft ? cp.lstart : cp.rstart, uni_start = kLeft ? cp.rstart : cp.lstart;
+  const uint64_t nT = (l1 - l0 + 63) / 64;
+  // flat grid: workgroup -> (group of tiles, group of uniform rows)
+  const uint64_t t0 = (uint64_t)(bid % cp.gx) * yt_per_wg;
   const uint32_t nt = (uint32_t)min<uint64_t>(yt_per_wg, nT - t0);
-  const uint64_t x0 = i_lo + (uint64_t)(bid / n_tile_groups) * xi_per_wg;
-  const uint32_t nx = (uint32_t)min<uint64_t>(xi_per_wg, i_hi + 1 - x0);
+  const uint64_t x0 = u0 + (uint64_t)(bid / cp.gx) * xi_per_wg;
+  const uint32_t nx = (uint32_t)min<uint64_t>(xi_per_wg, u1 - x0);
 
-  // stage right tiles (transposed), left rows and guide table; every load
-  // of a thread is issued before the first is used
+  // stage tiles (transposed), uniform rows and guide table; every load of a
+  // thread is issued before the first is used
   for (uint32_t tq = wave; tq < nt; tq += 4) {
-    const uint64_t j = (t0 + tq) * 64 + lane;
+    const uint64_t r = l0 + (t0 + tq) * 64 + lane;
     uint64_t v[W];
-    load_row<W>(a.rows, a.rstart + j, j < nR, v);
+    load_row<W>(a.rows, lane_start + r, r < l1, v);
 #pragma unroll
     for (int k = 0; k < W; ++k) Yt[(size_t)tq * 64 * W + 64 * k + lane] = transpose64(v[k]);
   }
   {
-    const uint64_t* src = a.rows + (a.lstart + x0) * W;
+    const uint64_t* src = a.rows + (uni_start + x0) * W;
     const uint32_t total = nx * W;
     uint32_t q = threadIdx.x;
     for (; q + 3 * 256 < total; q += 4 * 256) {
@@ -179,6 +178,9 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
     gp = G;
   else
     gp = a.gt_pair;
+  // a cut's factor in the uniform row, and the one in the tile
+  auto uni_of = [](uint32_t p) -> uint32_t { return kLeft ? (p & 0xFFFFu) : (p >> 16); };
+  auto tile_of = [](uint32_t p) -> uint32_t { return kLeft ? (p >> 16) : (p & 0xFFFFu); };
 
   // cut ranges of this lane's words
   uint32_t off[W], cnt[W];
@@ -189,10 +191,12 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
     cnt[k] = (w < a.n) ? a.gt_off[w + 1] - off[k] : 0u;
   }
 
-  for (uint32_t xi = wave; xi < nx; xi += 4) {
-    const uint64_t i = x0 + xi;
+  // a wave takes whole uniform rows, or every 2nd or 4th tile of one when
+  // there are only two rows or one
+  const uint32_t per_row = nx >= 3 ? 1u : 4u / nx;
+  for (uint32_t xi = wave / per_row; xi < nx; xi += 4 / per_row) {
     const uint64_t* xr = Xs + (size_t)xi * W;
-    // bit q of m[k]: x contains the prefix of cut q of word 64k+lane
+    // bit q of m[k]: the uniform row contains its factor of cut q of word 64k+lane
     uint32_t m[W];
     if constexpr (kShort) {
 #pragma unroll
@@ -202,7 +206,7 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
           // four cuts at a time: their reads overlap
           uint32_t u[4];
 #pragma unroll
-          for (int t = 0; t < 4; ++t) u[t] = (q0 + t < cnt[k]) ? gp[off[k] + q0 + t] >> 16 : 0u;
+          for (int t = 0; t < 4; ++t) u[t] = (q0 + t < cnt[k]) ? uni_of(gp[off[k] + q0 + t]) : 0u;
 #pragma unroll
           for (int t = 0; t < 4; ++t)
             if (q0 + t < cnt[k]) mm |= (uint32_t)((xr[u[t] >> 6] >> (u[t] & 63)) & 1ull) << (q0 + t);
@@ -210,7 +214,7 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
         m[k] = mm;
       }
     }
-    for (uint32_t tq = 0; tq < nt; ++tq) {
+    for (uint32_t tq = wave % per_row; tq < nt; tq += per_row) {
       const uint64_t* Y = Yt + (size_t)tq * 64 * W;
       uint64_t key[W];
 #pragma unroll
@@ -219,23 +223,37 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
         if constexpr (kShort) {
           for (uint32_t mm = m[k]; mm; mm &= mm - 1) {
             const uint32_t q = __ffs(mm) - 1;
-            acc |= Y[gp[off[k] + q] & 0xFFFFu];
+            acc |= Y[tile_of(gp[off[k] + q])];
           }
         } else {
           for (uint32_t q = 0; q < cnt[k]; ++q) {
             const uint32_t p = gp[off[k] + q];
-            const uint32_t u = p >> 16;
-            if ((xr[u >> 6] >> (u & 63)) & 1ull) acc |= Y[p & 0xFFFFu];
+            const uint32_t u = uni_of(p);
+            if ((xr[u >> 6] >> (u & 63)) & 1ull) acc |= Y[tile_of(p)];
           }
         }
         key[k] = transpose64(acc);
       }
-      const uint64_t j = (t0 + tq) * 64 + lane;
-      const uint64_t e = i * nR + j;
-      const bool valid = (j < nR) && (e >= a.e0) && (e < a.e1);
-      filter_emit<W, kInl>(a, valid, false, key, (uint32_t)(e - a.e0) + a.rel0);
+      const uint64_t r = l0 + (t0 + tq) * 64 + lane;  // this lane's row
+      const uint64_t e = kLeft ? r * nR + (x0 + xi) : (x0 + xi) * nR + r;
+      const bool valid = r < l1 && e >= cp.e0 && e < cp.e1;
+      filter_emit<W, kInl>(a, valid, false, key, (uint32_t)(e - cp.e0) + cp.rel0);
     }
   }
+}
+
+template <int W, bool kShort, bool kInl, bool kGtLds>
+__global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
+  extern __shared__ uint64_t lds[];
+  if (a.st->stop) return;
+  // this workgroup's part (block) and its place in the part's grid
+  uint32_t part = 0;
+  while (part + 1 < cs.n && cs.p[part + 1].wg0 <= blockIdx.x) ++part;
+  const ConcatPart& cp = cs.p[part];
+  if (cp.left)
+    concat_part<W, kShort, kInl, kGtLds, true>(a, cp, blockIdx.x - cp.wg0, lds);
+  else
+    concat_part<W, kShort, kInl, kGtLds, false>(a, cp, blockIdx.x - cp.wg0, lds);
 }
 
 // One thread per candidate x + y; several union blocks of a chunk share a
@@ -956,11 +974,11 @@ inline uint32_t grid_for(uint64_t n, uint32_t block, uint32_t cap = 0x7fffffffu)
 template <int W, bool kInl>
 hipError_t launch_concat_w(const GenArgs& a, ConcatSet cs, hipStream_t s) {
   if (cs.n == 0 || cs.n > (uint32_t)kMaxConcatParts) return hipErrorInvalidValue;
-  // right tiles in LDS: at most 32 KB
+  // tiles in LDS: at most 32 KB
   const uint32_t yt_cap = (uint32_t)std::max(1, std::min(kConcatYT, 32768 / (512 * W)));
-  // per part: left rows per workgroup at most concat_xi (16 by default),
-  // fewer (down to 4), then fewer right tiles, while its grid has under
-  // concat_wg workgroups (2048 by default)
+  // per part: uniform rows per workgroup at most concat_xi (16 by default),
+  // fewer (down to 4), then fewer tiles, while its grid has under concat_wg
+  // workgroups (2048 by default)
   const uint64_t target = a.concat_wg ? a.concat_wg : 2048;
   const uint32_t xi_max = a.concat_xi ? std::min<uint32_t>(a.concat_xi, 64) : 16;
   size_t lds = 0;
@@ -972,14 +990,17 @@ hipError_t launch_concat_w(const GenArgs& a, ConcatSet cs, hipStream_t s) {
     p.i_lo = p.e0 / nR;
     p.i_hi = (p.e1 - 1) / nR;
     const uint64_t rowsx = p.i_hi - p.i_lo + 1;
-    const uint64_t nT = (nR + 63) / 64;
+    // the operand across the lanes: the one whose tiles of 64 fill better
+    // (fewer wave iterations; left rows when the right level is small)
+    p.left = ((rowsx + 63) / 64) * nR < rowsx * ((nR + 63) / 64) ? 1u : 0u;
+    const uint64_t nT = ((p.left ? rowsx : nR) + 63) / 64, nU = p.left ? nR : rowsx;
     uint32_t yt = (uint32_t)std::min<uint64_t>(yt_cap, nT);
     uint32_t xi = xi_max;
-    auto wgs = [&](uint32_t y, uint32_t x) { return ((nT + y - 1) / y) * ((rowsx + x - 1) / x); };
-    while (xi > 4 && wgs(yt, xi) < target) xi /= 2;
+    auto wgs = [&](uint32_t y, uint32_t x) { return ((nT + y - 1) / y) * ((nU + x - 1) / x); };
+    while (xi > 4 && (wgs(yt, xi) < target || xi >= 2 * nU)) xi /= 2;
     while (yt > 1 && wgs(yt, xi) < target) yt /= 2;
     lds = std::max(lds, (size_t)yt * 64 * W * 8 + (size_t)xi * W * 8);
-    const uint64_t gx = (nT + yt - 1) / yt, gy = (rowsx + xi - 1) / xi;
+    const uint64_t gx = (nT + yt - 1) / yt, gy = (nU + xi - 1) / xi;
     p.yt = yt;
     p.xi = xi;
     p.gx = (uint32_t)gx;
