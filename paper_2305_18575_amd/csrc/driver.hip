@@ -44,6 +44,20 @@ struct Block {
   bool same;         // union of a level with itself (pairs x before y)
 };
 
+// The launches of one chunk, as planned (kept between chunks for its storage).
+struct ChunkLaunches {
+  std::vector<std::pair<int, GenArgs>> singles;  // constructor, arguments
+  std::vector<PieceArgs> pieces;
+  std::vector<ConcatSet> concats;
+  std::vector<UnionSet> unions;
+  void clear() {
+    singles.clear();
+    pieces.clear();
+    concats.clear();
+    unions.clear();
+  }
+};
+
 // Device memory of an instance: hipMalloc / hipFree, or the caller's pair
 // (rei_set_allocator) captured when the instance is created.
 struct DevAlloc {
@@ -111,6 +125,8 @@ struct rei_instance {
   uint32_t* d_se = nullptr;
   uint64_t* d_spos = nullptr;
   uint64_t surv_cap = 0;
+  uint2* d_reg = nullptr;      // the large generators' survivor ranges
+  uint64_t reg_cap = 0;
   uint32_t* d_bitmap = nullptr;
   uint32_t* d_prefix = nullptr;
   uint32_t* d_bsums = nullptr;
@@ -141,6 +157,7 @@ struct rei_instance {
   uint32_t otf_level = 0;
   bool otf_blocked = false;
   uint64_t pending = 0;
+  ChunkLaunches launches;   // of the chunk being enqueued
   uint32_t chunks_enq = 0;  // chunks enqueued on the per-chunk path since the state was reset
 
   // levels, indexed by cost
@@ -342,22 +359,32 @@ rei_status ensure_table(rei_instance* in, uint64_t entries, hipStream_t s, bool 
   return REI_OK;
 }
 
-rei_status ensure_chunk_buffers(rei_instance* in, uint64_t len) {
+// slots: survivor slots; len: candidates (bitmap bits); regions: survivor ranges.
+rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, uint64_t regions) {
   const int W = in->st.W;
-  if (len > in->surv_cap) {
+  if (slots > in->surv_cap) {
     dfree(in, in->d_skey);
     dfree(in, in->d_se);
     dfree(in, in->d_spos);
-    HIP_OK(in, dev_alloc(in, &in->d_skey, len * W * 8));
-    HIP_OK(in, dev_alloc(in, &in->d_se, len * 4));
-    HIP_OK(in, dev_alloc(in, &in->d_spos, len * 8));
-    in->surv_cap = len;
+    in->surv_cap = 0;
+    HIP_OK(in, dev_alloc(in, &in->d_skey, slots * W * 8));
+    HIP_OK(in, dev_alloc(in, &in->d_se, slots * 4));
+    HIP_OK(in, dev_alloc(in, &in->d_spos, slots * 8));
+    in->surv_cap = slots;
+  }
+  if (regions > in->reg_cap) {
+    dfree(in, in->d_reg);
+    in->reg_cap = 0;
+    const uint64_t cap = std::max<uint64_t>(4096, pow2_at_least(regions));
+    HIP_OK(in, dev_alloc(in, &in->d_reg, cap * sizeof(uint2)));
+    in->reg_cap = cap;
   }
   const uint64_t words = (len + 31) / 32;
   if (words > in->bitmap_cap) {
     dfree(in, in->d_bitmap);
     dfree(in, in->d_prefix);
     dfree(in, in->d_bsums);
+    in->bitmap_cap = 0;
     HIP_OK(in, dev_alloc(in, &in->d_bitmap, words * 4));
     HIP_OK(in, dev_alloc(in, &in->d_prefix, words * 4));
     HIP_OK(in, dev_alloc(in, &in->d_bsums, ((words + 1023) / 1024 + 1) * 4));
@@ -497,86 +524,36 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   rei_status r;
   auto worst_rows = [&] { return std::min(in->row_cap, in->known_rows + in->pending + len); };
   auto worst_entries = [&] { return in->known_rows + in->pending + len; };
-  // a level enumerated in OnTheFly mode stores nothing: no buffer grows
-  const bool otf_level = in->otf_level != 0;
-  if (!otf_level && (worst_rows() > in->rows_alloc || 2 * worst_entries() > in->slots_cap ||
-                     len > in->surv_cap || words > in->bitmap_cap)) {
-    if ((r = sync_state(in, s, true)) != REI_OK) return r;
-    if (in->h_state->stop) {
-      *stopped = true;
-      return REI_OK;
-    }
-    if ((r = ensure_chunk_buffers(in, len)) != REI_OK) return r;
-    if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + len), s)) != REI_OK) return r;
-    if ((r = ensure_table(in, in->known_rows + len, s, false)) != REI_OK) return r;
-  }
-
+  // The chunk's launches.  Small pieces (W <= kPiecesMaxW) share gen_pieces
+  // launches of up to kMaxPieces pieces; large concatenation and union blocks
+  // share launches of up to kMaxConcatParts and kMaxUnionParts blocks; other
+  // large blocks get their constructor's kernel.
   GenArgs g{};
-  g.rows = in->d_rows;
-  g.slots = in->d_slots;
-  g.slot_mask = in->slots_cap - 1;
-  g.skey = in->d_skey;
-  g.se = in->d_se;
-  g.spos = in->d_spos;
-  g.ctrl = in->d_ctrl;
-  g.pmask = in->d_pmask;
-  g.nmask = in->d_nmask;
   g.max_err = in->max_err;
-  g.gt_off = in->d_gt_off;
-  g.gt_pair = in->d_gt_pair;
-  g.len_off = in->d_len_off;
   g.max_len = in->st.max_len;
   g.n = in->st.n;
   g.n_pairs = (uint32_t)in->st.gt_pair.size();
-  g.st = in->d_state;
   g.inl = in->inl ? 1u : 0u;
   {
     const GridTune gt = grid_params(in);
     g.concat_wg = gt.concat_wg;
     g.concat_xi = gt.concat_xi;
   }
-  // small pieces (W <= kPiecesMaxW) share gen_pieces launches of up to
-  // kMaxPieces pieces; larger ones get their constructor's kernel
-  PieceArgs pa{};
-  // large concatenation blocks share gen_concat launches of up to
-  // kMaxConcatParts blocks
-  ConcatSet cset{};
-  uint64_t cset_cand = 0;
-  auto flush_concat = [&]() -> rei_status {
-    if (!cset.n) return REI_OK;
-    LAUNCH(in, s, REI_K_GEN_CONCAT, cset_cand, launch_concat_set(W, g, cset, s));
-    cset = ConcatSet{};
-    cset_cand = 0;
-    return REI_OK;
-  };
-  // large union blocks share gen_union launches likewise
-  UnionSet uset{};
-  uint64_t uset_cand = 0;
-  auto flush_union = [&]() -> rei_status {
-    if (!uset.n) return REI_OK;
-    LAUNCH(in, s, REI_K_GEN_UNION, uset_cand, launch_union_set(W, g, uset, s));
-    uset = UnionSet{};
-    uset_cand = 0;
-    return REI_OK;
-  };
-  auto flush_pieces = [&]() -> rei_status {
-    if (!pa.n) return REI_OK;
-    GenArgs gp = g;  // pieces carry their own ranges; characters index from the table's start
-    gp.char_index = in->d_char_index;
-    LAUNCH(in, s, REI_K_GEN_MIXED, pa.items_cand, launch_gen_pieces(W, gp, pa, s));
-    pa = PieceArgs{};
-    return REI_OK;
-  };
+  ChunkLaunches& cl = in->launches;
+  cl.clear();
+  SlotPlan sp{0, 0};
   for (const Piece& p : pieces) {
     const Block& b = p.b;
+    const uint32_t rel0 = (uint32_t)(p.e_base + p.e0 - chunk_e0);
     if (W <= kPiecesMaxW && p.e1 - p.e0 <= kSmallPiece) {
-      PieceD& d = pa.p[pa.n];
-      d = PieceD{};
+      if (cl.pieces.empty() || cl.pieces.back().n == (uint32_t)kMaxPieces) cl.pieces.push_back(PieceArgs{});
+      PieceArgs& pa = cl.pieces.back();
+      PieceD& d = pa.p[pa.n++];
       d.op = (uint32_t)b.op;
       d.same = b.same ? 1u : 0u;
       d.e0 = p.e0;
       d.e1 = p.e1;
-      d.rel0 = (uint32_t)(p.e_base + p.e0 - chunk_e0);
+      d.rel0 = rel0;
       if (b.op == OP_CHAR) {
         uint32_t first = 0, count = 0;
         chars_at(in, c, &first, &count);
@@ -609,52 +586,106 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       }
       pa.items += items;
       pa.items_cand += p.e1 - p.e0;
-      if (++pa.n == kMaxPieces && (r = flush_pieces()) != REI_OK) return r;
-      continue;
-    }
-    if (b.op == OP_CONCAT) {
-      ConcatPart& cp = cset.p[cset.n];
-      cp = ConcatPart{};
+      sp.slots += p.e1 - p.e0;  // appended with one counter, from slot 0
+    } else if (b.op == OP_CONCAT) {
+      if (cl.concats.empty() || cl.concats.back().n == (uint32_t)kMaxConcatParts) cl.concats.push_back(ConcatSet{});
+      ConcatSet& cset = cl.concats.back();
+      ConcatPart& cp = cset.p[cset.n++];
       cp.lstart = in->lstart[b.L];
       cp.rstart = in->lstart[b.R];
       cp.rcount = in->lcount[b.R];
       cp.e0 = p.e0;
       cp.e1 = p.e1;
-      cp.rel0 = (uint32_t)(p.e_base + p.e0 - chunk_e0);
-      cset_cand += p.e1 - p.e0;
-      if (++cset.n == (uint32_t)kMaxConcatParts && (r = flush_concat()) != REI_OK) return r;
-      continue;
-    }
-    if (b.op == OP_UNION) {
-      uset.p[uset.n] = UnionPart{in->lstart[b.L], in->lcount[b.L], in->lstart[b.R], in->lcount[b.R], p.e0, p.e1,
-                                 (uint32_t)(p.e_base + p.e0 - chunk_e0), b.same ? 1u : 0u, 0, 0};
-      uset_cand += p.e1 - p.e0;
-      if (++uset.n == (uint32_t)kMaxUnionParts && (r = flush_union()) != REI_OK) return r;
-      continue;
-    }
-    g.e0 = p.e0;
-    g.e1 = p.e1;
-    g.rel0 = (uint32_t)(p.e_base + p.e0 - chunk_e0);
-    g.char_index = in->d_char_index;
-    if (b.op == OP_CHAR) {
-      uint32_t first = 0, count = 0;
-      chars_at(in, c, &first, &count);
-      g.char_index = in->d_char_index + first;
-    }
-    g.lstart = g.lcount = g.rstart = g.rcount = 0;
-    if (b.op != OP_CHAR) {
-      g.lstart = in->lstart[b.L];
-      g.lcount = in->lcount[b.L];
-      if (b.op == OP_CONCAT || b.op == OP_UNION) {
-        g.rstart = in->lstart[b.R];
-        g.rcount = in->lcount[b.R];
+      cp.rel0 = rel0;
+    } else if (b.op == OP_UNION) {
+      if (cl.unions.empty() || cl.unions.back().n == (uint32_t)kMaxUnionParts) cl.unions.push_back(UnionSet{});
+      UnionSet& uset = cl.unions.back();
+      UnionPart& up = uset.p[uset.n++];
+      up.lstart = in->lstart[b.L];
+      up.lcount = in->lcount[b.L];
+      up.rstart = in->lstart[b.R];
+      up.rcount = in->lcount[b.R];
+      up.e0 = p.e0;
+      up.e1 = p.e1;
+      up.rel0 = rel0;
+      up.same = b.same ? 1u : 0u;
+    } else {
+      GenArgs q = g;
+      q.e0 = p.e0;
+      q.e1 = p.e1;
+      q.rel0 = rel0;
+      if (b.op == OP_CHAR) {
+        uint32_t first = 0, count = 0;
+        chars_at(in, c, &first, &count);
+        q.char_index = in->d_char_index + first;
+      } else {
+        q.lstart = in->lstart[b.L];
+        q.lcount = in->lcount[b.L];
       }
+      cl.singles.push_back({b.op, q});
     }
-    LAUNCH(in, s, REI_K_GEN_CHAR + b.op, p.e1 - p.e0, launch_gen(W, b.op, g, b.same, s));
   }
-  if ((r = flush_pieces()) != REI_OK) return r;
-  if ((r = flush_concat()) != REI_OK) return r;
-  if ((r = flush_union()) != REI_OK) return r;
+  const uint64_t dense_cap = sp.slots;
+  for (auto& x : cl.singles) HIP_OK(in, plan_gen(x.first, &x.second, &sp));
+  for (auto& x : cl.concats) HIP_OK(in, plan_concat_set(W, g, &x, &sp));
+  for (auto& x : cl.unions) HIP_OK(in, plan_union_set(&x, &sp));
+
+  // a level enumerated in OnTheFly mode stores nothing: no buffer grows but
+  // the ranges' (written, empty, by every generator wave)
+  const bool otf_level = in->otf_level != 0;
+  if ((!otf_level && (worst_rows() > in->rows_alloc || 2 * worst_entries() > in->slots_cap ||
+                      sp.slots > in->surv_cap || words > in->bitmap_cap)) ||
+      sp.regions > in->reg_cap) {
+    if ((r = sync_state(in, s, true)) != REI_OK) return r;
+    if (in->h_state->stop) {
+      *stopped = true;
+      return REI_OK;
+    }
+    if (otf_level) {
+      if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions)) != REI_OK) return r;
+    } else {
+      if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions)) != REI_OK) return r;
+      if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + len), s)) != REI_OK) return r;
+      if ((r = ensure_table(in, in->known_rows + len, s, false)) != REI_OK) return r;
+    }
+  }
+
+  auto set_buffers = [&](GenArgs& q) {
+    q.rows = in->d_rows;
+    q.slots = in->d_slots;
+    q.slot_mask = in->slots_cap - 1;
+    q.skey = in->d_skey;
+    q.se = in->d_se;
+    q.spos = in->d_spos;
+    q.reg = in->d_reg;
+    q.ctrl = in->d_ctrl;
+    q.pmask = in->d_pmask;
+    q.nmask = in->d_nmask;
+    q.gt_off = in->d_gt_off;
+    q.gt_pair = in->d_gt_pair;
+    q.len_off = in->d_len_off;
+    q.st = in->d_state;
+  };
+  set_buffers(g);
+  for (auto& x : cl.singles) {
+    set_buffers(x.second);
+    LAUNCH(in, s, REI_K_GEN_CHAR + x.first, x.second.e1 - x.second.e0, launch_gen(W, x.first, x.second, s));
+  }
+  for (const PieceArgs& pa : cl.pieces) {
+    GenArgs gp = g;  // pieces carry their own ranges; characters index from the table's start
+    gp.char_index = in->d_char_index;
+    LAUNCH(in, s, REI_K_GEN_MIXED, pa.items_cand, launch_gen_pieces(W, gp, pa, s));
+  }
+  for (const ConcatSet& x : cl.concats) {
+    uint64_t cand = 0;
+    for (uint32_t k = 0; k < x.n; ++k) cand += x.p[k].e1 - x.p[k].e0;
+    LAUNCH(in, s, REI_K_GEN_CONCAT, cand, launch_concat_set(W, g, x, s));
+  }
+  for (const UnionSet& x : cl.unions) {
+    uint64_t cand = 0;
+    for (uint32_t k = 0; k < x.n; ++k) cand += x.p[k].e1 - x.p[k].e0;
+    LAUNCH(in, s, REI_K_GEN_UNION, cand, launch_union_set(W, g, x, s));
+  }
 
   ChunkArgs ca{};
   ca.rows = in->d_rows;
@@ -667,6 +698,9 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   ca.skey = in->d_skey;
   ca.se = in->d_se;
   ca.spos = in->d_spos;
+  ca.reg = in->d_reg;
+  ca.n_reg = (uint32_t)sp.regions;
+  ca.dense_cap = dense_cap;
   ca.bitmap = in->d_bitmap;
   ca.word_prefix = in->d_prefix;
   ca.block_sums = in->d_bsums;
@@ -1360,7 +1394,7 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
       continue;
     }
     const uint64_t R = batch_rows(in, arena_bytes);
-    if ((r = ensure_chunk_buffers(in, kBatchChunk)) != REI_OK) return r;
+    if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0)) != REI_OK) return r;
     if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
     if ((r = ensure_table(in, in->rows_alloc + kBatchChunk, s, false)) != REI_OK) return r;
     const int g = in->inl ? 0 : in->st.W;
@@ -1618,12 +1652,14 @@ void free_search_buffers(rei_instance* in) {
   dfree(in, in->d_skey);
   dfree(in, in->d_se);
   dfree(in, in->d_spos);
+  dfree(in, in->d_reg);
   dfree(in, in->d_bitmap);
   dfree(in, in->d_prefix);
   dfree(in, in->d_bsums);
   in->rows_alloc = 0;
   in->slots_cap = 0;
   in->surv_cap = 0;
+  in->reg_cap = 0;
   in->bitmap_cap = 0;
   in->known_rows = 0;
   in->h_aux_valid = false;
@@ -1644,6 +1680,7 @@ void free_device(rei_instance* in) {
   dfree(in, in->d_skey);
   dfree(in, in->d_se);
   dfree(in, in->d_spos);
+  dfree(in, in->d_reg);
   dfree(in, in->d_bitmap);
   dfree(in, in->d_prefix);
   dfree(in, in->d_bsums);
@@ -2876,7 +2913,7 @@ void server_sched_queue(rei_server* sv) {
             continue;
           }
           const uint64_t R = batch_rows(in, sv->arena);
-          if ((a.r = ensure_chunk_buffers(in, kBatchChunk)) != REI_OK) continue;
+          if ((a.r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0)) != REI_OK) continue;
           if ((a.r = ensure_rows(in, R, sv->setup)) != REI_OK) continue;
           if ((a.r = ensure_table(in, in->rows_alloc + kBatchChunk, sv->setup, false)) != REI_OK) continue;
           setup_used = true;
@@ -3278,7 +3315,7 @@ BatchDesc graph_desc(const rei_instance* in) {
 rei_status graph_arena(rei_instance* in, uint64_t arena_bytes, hipStream_t s) {
   rei_status r;
   const uint64_t R = batch_rows(in, arena_bytes);
-  if ((r = ensure_chunk_buffers(in, kBatchChunk)) != REI_OK) return r;
+  if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0)) != REI_OK) return r;
   if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
   return ensure_table(in, in->rows_alloc + kBatchChunk, s, false);
 }

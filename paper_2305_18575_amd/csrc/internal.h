@@ -113,8 +113,13 @@ struct GenArgs {
   const DevState* st;
   uint32_t inl;               // inline-key table (one word per language, |ic| <= 63)
   // concatenation launch shape (0 = defaults): workgroups the grid aims at,
-  // and the most left rows one workgroup takes
+  // and the most uniform rows one workgroup takes
   uint32_t concat_wg, concat_xi;
+  // the large generators' survivors: first slot and survivor count of each
+  // wave's range; this launch's first slot and range, and (question, star)
+  // its 64-candidate iterations per wave
+  uint2* reg;
+  uint32_t slot0, reg0, per_wave;
 };
 
 // Tunable launch parameters of the per-chunk grid path (per word width):
@@ -157,7 +162,16 @@ struct ChunkArgs {
   uint64_t* hlev;
   uint64_t nlev;
   uint32_t clear_words;       // bitmap words insert_survivors clears (the grid finalize path)
+  const uint2* reg;           // the large generators' ranges: first slot, survivors
+  uint32_t n_reg;
+  uint64_t dense_cap;         // most survivors the pieces can append (slots 0 .. dense_cap - 1)
 };
+
+// Survivor slots and ranges a chunk's launches take, as they are planned.
+struct SlotPlan {
+  uint64_t slots, regions;
+};
+constexpr uint64_t kMaxSlots = 1ull << 31;
 // Whether a chunk is finalized by one workgroup (else by the grid kernels,
 // which need the bitmap cleared by insert_survivors).
 bool finalize_in_one_workgroup(int W, uint64_t len);
@@ -186,7 +200,11 @@ inline void launch_timed(F kernel, dim3 grid, dim3 block, uint32_t shmem, hipStr
 hipError_t launch_fill(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 hipError_t launch_rehash(int W, bool inl, const uint64_t* rows, uint64_t nrows, uint64_t* slots,
                          uint64_t slot_mask, hipStream_t s);
-hipError_t launch_gen(int W, int op, const GenArgs& a, bool same_level, hipStream_t s);
+// The large generators are planned before they are launched: plan_* chooses
+// the launch's shape and takes its slots and ranges from the chunk's plan (so
+// that the buffers can be made large enough), launch_* runs it as planned.
+hipError_t plan_gen(int op, GenArgs* a, SlotPlan* sp);  // CHAR, QUESTION or STAR
+hipError_t launch_gen(int W, int op, const GenArgs& a, hipStream_t s);
 hipError_t launch_insert(int W, const ChunkArgs& a, hipStream_t s);
 // Winners, their ranks, the stored rows and the accounting of the chunk:
 // one workgroup when the chunk is small (LDS bitmap), else a grid pipeline.
@@ -257,11 +275,13 @@ struct ConcatPart {
   uint32_t yt, xi, gx;              // tiles and uniform rows per workgroup, tile groups (launcher)
   uint32_t wg0;                     // first workgroup of this part (launcher)
   uint32_t left;                    // left rows across the lanes, else right rows (launcher)
+  uint32_t slot0, reg0;             // first survivor slot and range (launcher)
 };
 struct ConcatSet {
-  uint32_t n, pad;
+  uint32_t n, wgs;
   ConcatPart p[kMaxConcatParts];
 };
+hipError_t plan_concat_set(int W, const GenArgs& a, ConcatSet* cs, SlotPlan* sp);
 hipError_t launch_concat_set(int W, const GenArgs& a, const ConcatSet& cs, hipStream_t s);
 
 // Several large union blocks of one chunk in one gen_union launch (one
@@ -272,12 +292,13 @@ struct UnionPart {
   uint64_t e0, e1;                          // block-local candidate range
   uint32_t rel0;                            // chunk-relative index of candidate e0
   uint32_t same;                            // both operands from one level: pairs x < y
-  uint32_t wg0, pad;                        // first workgroup of this part (launcher)
+  uint32_t wg0, slot0, reg0;                // first workgroup, survivor slot and range (launcher)
 };
 struct UnionSet {
-  uint32_t n, pad;
+  uint32_t n, wgs, per_wave;
   UnionPart p[kMaxUnionParts];
 };
+hipError_t plan_union_set(UnionSet* us, SlotPlan* sp);
 hipError_t launch_union_set(int W, const GenArgs& a, const UnionSet& us, hipStream_t s);
 
 // ---- batched solver: one workgroup runs the whole search of one instance --

@@ -44,36 +44,89 @@ __device__ __forceinline__ void filter_emit(const GenArgs& a, bool valid, bool k
   filter_emit<W, kInl>(p, k, valid, known_dup, key, e_rel);
 }
 
+// One wave's own range of survivor slots: the large generators append there,
+// so that no counter is shared.  (One counter for the whole launch cost a
+// returning atomic on one address per wave iteration with a survivor, 4-7 ns
+// each one after the other: 835 us per 16.7 M-candidate gen_concat launch
+// and 545 us per gen_union launch of one-word languages, 58 infixes.)
+struct Region {
+  uint32_t base, n;
+};
+
+template <int W, bool kInl>
+__device__ __forceinline__ void region_emit(const GenArgs& a, Region& r, bool valid, bool known_dup,
+                                            const uint64_t (&key)[W], uint32_t e_rel) {
+  if (a.st->otf) {
+    if (valid && !known_dup && misclassified<W>(a.pmask, a.nmask, key) <= (int)a.max_err)
+      atomicMin(&a.ctrl->answer_e, e_rel);
+    return;
+  }
+  bool surv = false;
+  uint64_t h = 0;
+  if (valid && !known_dup) {
+    h = hash_key<W>(key);
+    surv = !table_find<W, kInl>(a.slots, a.slot_mask, a.rows, key, h);
+  }
+  const uint64_t m = __ballot(surv);
+  if (surv) {
+    const uint32_t sid = r.base + r.n + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1));
+    uint64_t* dst = a.skey + (uint64_t)sid * W;
+#pragma unroll
+    for (int k = 0; k < W; ++k) dst[k] = key[k];
+    a.se[sid] = e_rel;
+    a.spos[sid] = h;
+    if (misclassified<W>(a.pmask, a.nmask, key) <= (int)a.max_err) atomicMin(&a.ctrl->answer_e, e_rel);
+  }
+  r.n += (uint32_t)__popcll(m);
+}
+
+// Records the wave's range (every wave of a launch with ranges does).
+__device__ __forceinline__ void region_close(const GenArgs& a, uint32_t id, const Region& r) {
+  if (lane_id() == 0) a.reg[id] = make_uint2(r.base, r.n);
+}
+
 // ---- generators -----------------------------------------------------------
 
+// A wave of the one-candidate-per-lane generators takes a.per_wave * 64
+// consecutive candidates.
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void gen_char(GenArgs a) {
   if (a.st->stop) return;
-  const uint64_t e = a.e0 + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = e < a.e1;
-  uint64_t key[W];
-  const int idx = valid ? a.char_index[e] : -1;
+  const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  Region rg{a.slot0 + wave * a.per_wave * 64, 0};
+  const uint64_t w0 = a.e0 + (uint64_t)wave * a.per_wave * 64;
+  for (uint32_t it = 0; it < a.per_wave && w0 + 64 * it < a.e1; ++it) {
+    const uint64_t e = w0 + 64 * it + lane;
+    const bool valid = e < a.e1;
+    uint64_t key[W];
+    const int idx = valid ? a.char_index[e] : -1;
 #pragma unroll
-  for (int k = 0; k < W; ++k) key[k] = (idx >= 0 && (idx >> 6) == k) ? (1ull << (idx & 63)) : 0ull;
-  filter_emit<W, kInl>(a, valid, false, key, (uint32_t)(e - a.e0) + a.rel0);
+    for (int k = 0; k < W; ++k) key[k] = (idx >= 0 && (idx >> 6) == k) ? (1ull << (idx & 63)) : 0ull;
+    region_emit<W, kInl>(a, rg, valid, false, key, (uint32_t)(e - a.e0) + a.rel0);
+  }
+  region_close(a, a.reg0 + wave, rg);
 }
 
 // r? = eps + r; eps is word 0 of ic (shortlex puts the empty word first).
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void gen_question(GenArgs a) {
   if (a.st->stop) return;
-  const uint64_t e = a.e0 + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = e < a.e1;
-  uint64_t key[W];
-  const uint64_t* src = a.rows + (a.lstart + (valid ? e : 0)) * W;
-#pragma unroll
-  for (int k = 0; k < W; ++k) key[k] = valid ? src[k] : 0ull;
-  const bool dup = (key[0] & 1ull) != 0;  // already contains eps: r? = r
-  key[0] |= 1ull;
-  filter_emit<W, kInl>(a, valid, dup, key, (uint32_t)(e - a.e0) + a.rel0);
+  const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  Region rg{a.slot0 + wave * a.per_wave * 64, 0};
+  const uint64_t w0 = a.e0 + (uint64_t)wave * a.per_wave * 64;
+  for (uint32_t it = 0; it < a.per_wave && w0 + 64 * it < a.e1; ++it) {
+    const uint64_t e = w0 + 64 * it + lane;
+    const bool valid = e < a.e1;
+    uint64_t key[W];
+    load_row<W>(a.rows, a.lstart + e, valid, key);
+    const bool dup = (key[0] & 1ull) != 0;  // already contains eps: r? = r
+    key[0] |= 1ull;
+    region_emit<W, kInl>(a, rg, valid, dup, key, (uint32_t)(e - a.e0) + a.rel0);
+  }
+  region_close(a, a.reg0 + wave, rg);
 }
 
-// r* for 64 rows per workgroup, bit-sliced: Xt[w] / Yt[w] hold bit t = row t's
+// r* for a.per_wave groups of 64 rows per workgroup, bit-sliced: Xt[w] / Yt[w] hold bit t = row t's
 // membership of word w.  Y(eps) = 1 and, by increasing length,
 // Y(w) = OR over cuts w = u v with u non-empty of X(u) & Y(v) (v is shorter).
 template <int W, bool kInl>
@@ -82,27 +135,33 @@ __global__ __launch_bounds__(256) void gen_star(GenArgs a) {
   __shared__ uint64_t Yt[64 * W];
   if (a.st->stop) return;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t base = a.e0 + (uint64_t)blockIdx.x * 64;
-  for (int k = wave; k < W; k += 4) {
-    const uint64_t e = base + lane;
-    const uint64_t v = (e < a.e1) ? a.rows[(a.lstart + e) * W + k] : 0ull;
-    Xt[64 * k + lane] = transpose64(v);
-  }
-  for (uint32_t w = threadIdx.x; w < 64u * W; w += 256) Yt[w] = (w == 0) ? ~0ull : 0ull;
-  __syncthreads();
-  for (uint32_t l = 1; l <= a.max_len; ++l) {
-    const uint32_t lo = a.len_off[l], hi = a.len_off[l + 1];
-    for (uint32_t w = lo + threadIdx.x; w < hi; w += 256)
-      Yt[w] = star_fold(Xt, Yt, a.gt_pair, a.gt_off[w], l);  // cuts 1..l (cut 0 has u = eps)
+  Region rg{a.slot0 + blockIdx.x * a.per_wave * 64, 0};
+  for (uint32_t it = 0; it < a.per_wave; ++it) {
+    const uint64_t base = a.e0 + ((uint64_t)blockIdx.x * a.per_wave + it) * 64;
+    if (base >= a.e1) break;
+    for (int k = wave; k < W; k += 4) {
+      const uint64_t e = base + lane;
+      const uint64_t v = (e < a.e1) ? a.rows[(a.lstart + e) * W + k] : 0ull;
+      Xt[64 * k + lane] = transpose64(v);
+    }
+    for (uint32_t w = threadIdx.x; w < 64u * W; w += 256) Yt[w] = (w == 0) ? ~0ull : 0ull;
     __syncthreads();
-  }
-  if (wave == 0) {
-    uint64_t key[W];
+    for (uint32_t l = 1; l <= a.max_len; ++l) {
+      const uint32_t lo = a.len_off[l], hi = a.len_off[l + 1];
+      for (uint32_t w = lo + threadIdx.x; w < hi; w += 256)
+        Yt[w] = star_fold(Xt, Yt, a.gt_pair, a.gt_off[w], l);  // cuts 1..l (cut 0 has u = eps)
+      __syncthreads();
+    }
+    if (wave == 0) {
+      uint64_t key[W];
 #pragma unroll
-    for (int k = 0; k < W; ++k) key[k] = transpose64(Yt[64 * k + lane]);
-    const uint64_t e = base + lane;
-    filter_emit<W, kInl>(a, e < a.e1, false, key, (uint32_t)(e - a.e0) + a.rel0);
+      for (int k = 0; k < W; ++k) key[k] = transpose64(Yt[64 * k + lane]);
+      const uint64_t e = base + lane;
+      region_emit<W, kInl>(a, rg, e < a.e1, false, key, (uint32_t)(e - a.e0) + a.rel0);
+    }
+    __syncthreads();  // the tiles are rewritten by the next group
   }
+  if (wave == 0) region_close(a, a.reg0 + blockIdx.x, rg);
 }
 
 // x.y, bit-sliced over 64 values of one operand.  A workgroup owns up to YT
@@ -194,6 +253,12 @@ __device__ __forceinline__ void concat_part(const GenArgs& a, const ConcatPart& 
   // a wave takes whole uniform rows, or every 2nd or 4th tile of one when
   // there are only two rows or one
   const uint32_t per_row = nx >= 3 ? 1u : 4u / nx;
+  // this wave's slots: the workgroup's tiles and rows are a dense range of
+  // the part's nT x (u1 - u0) tiles of 64, its waves' shares lie in order
+  uint32_t before = 0;  // wave iterations of this workgroup's lower waves
+  for (uint32_t v = 0; v < wave; ++v)
+    before += ((nx + 4 / per_row - 1 - v / per_row) / (4 / per_row)) * ((nt + per_row - 1 - v % per_row) / per_row);
+  Region rg{cp.slot0 + (uint32_t)(((x0 - u0) * nT + nx * t0 + before) * 64), 0};
   for (uint32_t xi = wave / per_row; xi < nx; xi += 4 / per_row) {
     const uint64_t* xr = Xs + (size_t)xi * W;
     // bit q of m[k]: the uniform row contains its factor of cut q of word 64k+lane
@@ -237,9 +302,10 @@ __device__ __forceinline__ void concat_part(const GenArgs& a, const ConcatPart& 
       const uint64_t r = l0 + (t0 + tq) * 64 + lane;  // this lane's row
       const uint64_t e = kLeft ? r * nR + (x0 + xi) : (x0 + xi) * nR + r;
       const bool valid = r < l1 && e >= cp.e0 && e < cp.e1;
-      filter_emit<W, kInl>(a, valid, false, key, (uint32_t)(e - cp.e0) + cp.rel0);
+      region_emit<W, kInl>(a, rg, valid, false, key, (uint32_t)(e - cp.e0) + cp.rel0);
     }
   }
+  region_close(a, cp.reg0 + bid * 4 + wave, rg);
 }
 
 template <int W, bool kShort, bool kInl, bool kGtLds>
@@ -256,40 +322,44 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
     concat_part<W, kShort, kInl, kGtLds, false>(a, cp, blockIdx.x - cp.wg0, lds);
 }
 
-// One thread per candidate x + y; several union blocks of a chunk share a
-// launch (UnionSet), each workgroup in one block.
+// One lane per candidate x + y, us.per_wave * 64 consecutive candidates per
+// wave; several union blocks of a chunk share a launch (UnionSet), each
+// workgroup in one block.
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void gen_union(GenArgs a, UnionSet us) {
   if (a.st->stop) return;
   uint32_t part = 0;
   while (part + 1 < us.n && us.p[part + 1].wg0 <= blockIdx.x) ++part;
   const UnionPart& up = us.p[part];
-  a.e0 = up.e0;
-  a.rel0 = up.rel0;
-  const uint64_t e = up.e0 + (uint64_t)(blockIdx.x - up.wg0) * blockDim.x + threadIdx.x;
-  const bool valid = e < up.e1;
-  uint64_t i = 0, j = 0;
-  if (valid) {
-    if (up.same) {
-      tri_decode(e, up.lcount, &i, &j);
-    } else {
-      i = e / up.rcount;
-      j = e - i * up.rcount;
+  const uint32_t wave = (blockIdx.x - up.wg0) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  Region rg{up.slot0 + wave * us.per_wave * 64, 0};
+  const uint64_t w0 = up.e0 + (uint64_t)wave * us.per_wave * 64;
+  for (uint32_t it = 0; it < us.per_wave && w0 + 64 * it < up.e1; ++it) {
+    const uint64_t e = w0 + 64 * it + lane;
+    const bool valid = e < up.e1;
+    uint64_t i = 0, j = 0;
+    if (valid) {
+      if (up.same) {
+        tri_decode(e, up.lcount, &i, &j);
+      } else {
+        i = e / up.rcount;
+        j = e - i * up.rcount;
+      }
     }
-  }
-  const uint64_t* x = a.rows + (up.lstart + i) * W;
-  const uint64_t* y = a.rows + (up.rstart + j) * W;
-  uint64_t key[W];
-  bool eqx = true, eqy = true;
+    uint64_t x[W], y[W], key[W];
+    load_row<W>(a.rows, up.lstart + i, valid, x);
+    load_row<W>(a.rows, up.rstart + j, valid, y);
+    bool eqx = true, eqy = true;
 #pragma unroll
-  for (int k = 0; k < W; ++k) {
-    const uint64_t xv = valid ? x[k] : 0ull, yv = valid ? y[k] : 0ull;
-    key[k] = xv | yv;
-    eqx = eqx && key[k] == xv;
-    eqy = eqy && key[k] == yv;
+    for (int k = 0; k < W; ++k) {
+      key[k] = x[k] | y[k];
+      eqx = eqx && key[k] == x[k];
+      eqy = eqy && key[k] == y[k];
+    }
+    // x+y equals x or y (one contains the other): that language is stored
+    region_emit<W, kInl>(a, rg, valid, eqx || eqy, key, (uint32_t)(e - up.e0) + up.rel0);
   }
-  // x+y equals x or y (one contains the other): that language is stored
-  filter_emit<W, kInl>(a, valid, eqx || eqy, key, (uint32_t)(e - a.e0) + a.rel0);
+  region_close(a, up.reg0 + wave, rg);
 }
 
 // Many small pieces of one chunk (see PieceArgs): one wave per item of 64
@@ -607,22 +677,34 @@ __global__ __launch_bounds__(256) void rehash_rows(const uint64_t* rows, uint64_
   }
 }
 
+// Every survivor of the chunk once, over the grid: the pieces' (slots 0 ..
+// n_surv - 1), then those in the large generators' per-wave ranges, a wave
+// per range.
+template <typename F>
+__device__ __forceinline__ void for_survivors(const ChunkArgs& a, F f) {
+  const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, threads = gridDim.x * blockDim.x;
+  const uint32_t ns = a.ctrl->n_surv;
+  for (uint32_t sid = tid; sid < ns; sid += threads) f(sid);
+  for (uint32_t r = tid >> 6; r < a.n_reg; r += threads >> 6) {
+    const uint2 g = a.reg[r];
+    for (uint32_t k = tid & 63; k < g.y; k += 64) f(g.x + k);
+  }
+}
+
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void insert_survivors(ChunkArgs a) {
   if (a.st->stop) return;
   // the winner bitmap of the grid finalize path starts empty
   for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < a.clear_words; w += gridDim.x * blockDim.x)
     a.bitmap[w] = 0;
-  const uint32_t ns = a.ctrl->n_surv;
-  for (uint32_t sid = blockIdx.x * blockDim.x + threadIdx.x; sid < ns; sid += gridDim.x * blockDim.x) {
+  for_survivors(a, [&](uint32_t sid) {
     uint64_t key[W];
-#pragma unroll
-    for (int k = 0; k < W; ++k) key[k] = a.skey[(uint64_t)sid * W + k];
+    load_row<W>(a.skey, sid, true, key);
     const uint64_t h = a.spos[sid];
     const uint64_t pos = table_insert<W, kInl>(a.slots, a.sref, a.slot_mask, a.rows, a.skey, key, h,
                                                new_ref(a.se[sid], sid));
     a.spos[sid] = spos_pack(pos, h);
-  }
+  });
 }
 
 // Outcome of a chunk, in enumeration order: the answer (first precise
@@ -826,12 +908,11 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
 template <bool kInl>
 __global__ __launch_bounds__(256) void mark_winners(ChunkArgs a) {
   if (a.st->stop) return;
-  const uint32_t ns = a.ctrl->n_surv;
-  for (uint32_t sid = blockIdx.x * blockDim.x + threadIdx.x; sid < ns; sid += gridDim.x * blockDim.x) {
+  for_survivors(a, [&](uint32_t sid) {
     const uint32_t e = a.se[sid];
     if (table_is_winner<kInl>(a.slots, a.sref, a.spos[sid], new_ref(e, sid)))
       atomicOr(&a.bitmap[e >> 5], 1u << (e & 31));
-  }
+  });
 }
 
 constexpr uint32_t kScanBlock = 1024;  // bitmap words per scan block (256 threads x 4)
@@ -940,23 +1021,22 @@ __global__ __launch_bounds__(256) void scan_down(ChunkArgs a) {
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void compact_winners(ChunkArgs a) {
   if (a.st->stop) return;
-  const uint32_t ns = a.ctrl->n_surv;
   const uint32_t ans = a.ctrl->answer_e;
   const uint64_t row_base = a.st->total_rows;
   const uint64_t room = a.st->row_cap > row_base ? a.st->row_cap - row_base : 0;
-  for (uint32_t sid = blockIdx.x * blockDim.x + threadIdx.x; sid < ns; sid += gridDim.x * blockDim.x) {
+  for_survivors(a, [&](uint32_t sid) {
     const uint32_t e = a.se[sid];
     const uint32_t word = a.bitmap[e >> 5];
     const uint32_t bit = 1u << (e & 31);
-    if (!(word & bit)) continue;
+    if (!(word & bit)) return;
     const uint32_t rank = a.word_prefix[e >> 5] + (uint32_t)__popc(word & (bit - 1));
     if (e == ans) a.ctrl->answer_rank = rank;
-    if (ans != ~0u && e >= ans) continue;
+    if (ans != ~0u && e >= ans) return;
     if (rank < room)
       store_winner<W, kInl>(a, sid, e, row_base + rank);
     else if (rank == room)
       a.ctrl->overflow_e = e;
-  }
+  });
 }
 
 __global__ void account_large(ChunkArgs a) {
@@ -964,53 +1044,29 @@ __global__ void account_large(ChunkArgs a) {
   account_chunk(a, a.ctrl->answer_e, a.ctrl->answer_rank, a.ctrl->winners, a.ctrl->overflow_e);
 }
 
-inline uint32_t grid_for(uint64_t n, uint32_t block, uint32_t cap = 0x7fffffffu) {
+inline uint32_t grid_for(uint64_t n, uint64_t block, uint32_t cap = 0x7fffffffu) {
   uint64_t g = (n + block - 1) / block;
   if (g < 1) g = 1;
   if (g > cap) g = cap;
   return (uint32_t)g;
 }
 
+// Candidates (times 64) per wave of the one-candidate-per-lane generators:
+// one iteration while the launch would leave waves idle (8192 fill the
+// device at 32 per compute unit), up to 16.
+uint32_t iterations_per_wave(uint64_t candidates) {
+  return (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(1, candidates / (64 * 8192)));
+}
+
+size_t concat_lds(int W, const ConcatPart& p) { return (size_t)p.yt * 64 * W * 8 + (size_t)p.xi * W * 8; }
+
 template <int W, bool kInl>
-hipError_t launch_concat_w(const GenArgs& a, ConcatSet cs, hipStream_t s) {
-  if (cs.n == 0 || cs.n > (uint32_t)kMaxConcatParts) return hipErrorInvalidValue;
-  // tiles in LDS: at most 32 KB
-  const uint32_t yt_cap = (uint32_t)std::max(1, std::min(kConcatYT, 32768 / (512 * W)));
-  // per part: uniform rows per workgroup at most concat_xi (16 by default),
-  // fewer (down to 4), then fewer tiles, while its grid has under concat_wg
-  // workgroups (2048 by default)
-  const uint64_t target = a.concat_wg ? a.concat_wg : 2048;
-  const uint32_t xi_max = a.concat_xi ? std::min<uint32_t>(a.concat_xi, 64) : 16;
+hipError_t launch_concat_w(const GenArgs& a, const ConcatSet& cs, hipStream_t s) {
   size_t lds = 0;
-  uint64_t wgs_total = 0;
-  for (uint32_t k = 0; k < cs.n; ++k) {
-    ConcatPart& p = cs.p[k];
-    const uint64_t nR = p.rcount;
-    if (nR == 0 || p.e1 <= p.e0) return hipErrorInvalidValue;
-    p.i_lo = p.e0 / nR;
-    p.i_hi = (p.e1 - 1) / nR;
-    const uint64_t rowsx = p.i_hi - p.i_lo + 1;
-    // the operand across the lanes: the one whose tiles of 64 fill better
-    // (fewer wave iterations; left rows when the right level is small)
-    p.left = ((rowsx + 63) / 64) * nR < rowsx * ((nR + 63) / 64) ? 1u : 0u;
-    const uint64_t nT = ((p.left ? rowsx : nR) + 63) / 64, nU = p.left ? nR : rowsx;
-    uint32_t yt = (uint32_t)std::min<uint64_t>(yt_cap, nT);
-    uint32_t xi = xi_max;
-    auto wgs = [&](uint32_t y, uint32_t x) { return ((nT + y - 1) / y) * ((nU + x - 1) / x); };
-    while (xi > 4 && (wgs(yt, xi) < target || xi >= 2 * nU)) xi /= 2;
-    while (yt > 1 && wgs(yt, xi) < target) yt /= 2;
-    lds = std::max(lds, (size_t)yt * 64 * W * 8 + (size_t)xi * W * 8);
-    const uint64_t gx = (nT + yt - 1) / yt, gy = (nU + xi - 1) / xi;
-    p.yt = yt;
-    p.xi = xi;
-    p.gx = (uint32_t)gx;
-    p.wg0 = (uint32_t)wgs_total;
-    wgs_total += gx * gy;
-    if (wgs_total > 0x7fffffffull) return hipErrorInvalidConfiguration;
-  }
+  for (uint32_t k = 0; k < cs.n; ++k) lds = std::max(lds, concat_lds(W, cs.p[k]));
   const uint32_t gt_lds = (lds + (size_t)a.n_pairs * 4 <= 60 * 1024) ? 1u : 0u;
   if (gt_lds) lds += (size_t)a.n_pairs * 4;
-  const dim3 grid((uint32_t)wgs_total);
+  const dim3 grid(cs.wgs);
   const bool shrt = a.max_len < 32;
   if (shrt && gt_lds)
     launch_timed(gen_concat<W, true, kInl, true>, grid, dim3(256), lds, s, a, cs);
@@ -1023,56 +1079,20 @@ hipError_t launch_concat_w(const GenArgs& a, ConcatSet cs, hipStream_t s) {
   return hipGetLastError();
 }
 
-// One block of candidates [a.e0, a.e1) as a one-part set.
 template <int W, bool kInl>
-hipError_t launch_concat_one(const GenArgs& a, hipStream_t s) {
-  ConcatSet cs{};
-  cs.n = 1;
-  cs.p[0].lstart = a.lstart;
-  cs.p[0].rstart = a.rstart;
-  cs.p[0].rcount = a.rcount;
-  cs.p[0].e0 = a.e0;
-  cs.p[0].e1 = a.e1;
-  cs.p[0].rel0 = a.rel0;
-  return launch_concat_w<W, kInl>(a, cs, s);
-}
-
-template <int W, bool kInl>
-hipError_t launch_union_w(const GenArgs& a, UnionSet us, hipStream_t s) {
-  if (us.n == 0 || us.n > (uint32_t)kMaxUnionParts) return hipErrorInvalidValue;
-  uint64_t wgs = 0;
-  for (uint32_t k = 0; k < us.n; ++k) {
-    UnionPart& p = us.p[k];
-    if (p.e1 <= p.e0 || p.lcount == 0 || (!p.same && p.rcount == 0)) return hipErrorInvalidValue;
-    p.wg0 = (uint32_t)wgs;
-    wgs += (p.e1 - p.e0 + 255) / 256;
-    if (wgs > 0x7fffffffull) return hipErrorInvalidConfiguration;
-  }
-  launch_timed(gen_union<W, kInl>, dim3((uint32_t)wgs), dim3(256), 0, s, a, us);
-  return hipGetLastError();
-}
-
-template <int W, bool kInl>
-hipError_t launch_gen_w(int op, const GenArgs& a, bool same_level, hipStream_t s) {
+hipError_t launch_gen_w(int op, const GenArgs& a, hipStream_t s) {
+  const uint64_t per = (uint64_t)a.per_wave * 64;
   const uint64_t cnt = a.e1 - a.e0;
   switch (op) {
     case OP_CHAR:
-      launch_timed(gen_char<W, kInl>, dim3(grid_for(cnt, 256)), dim3(256), 0, s, a);
+      launch_timed(gen_char<W, kInl>, dim3(grid_for(cnt, 4 * per)), dim3(256), 0, s, a);
       break;
     case OP_QUESTION:
-      launch_timed(gen_question<W, kInl>, dim3(grid_for(cnt, 256)), dim3(256), 0, s, a);
+      launch_timed(gen_question<W, kInl>, dim3(grid_for(cnt, 4 * per)), dim3(256), 0, s, a);
       break;
     case OP_STAR:
-      launch_timed(gen_star<W, kInl>, dim3(grid_for(cnt, 64)), dim3(256), 0, s, a);
+      launch_timed(gen_star<W, kInl>, dim3(grid_for(cnt, per)), dim3(256), 0, s, a);
       break;
-    case OP_CONCAT:
-      return launch_concat_one<W, kInl>(a, s);
-    case OP_UNION: {
-      UnionSet us{};
-      us.n = 1;
-      us.p[0] = UnionPart{a.lstart, a.lcount, a.rstart, a.rcount, a.e0, a.e1, a.rel0, same_level ? 1u : 0u, 0, 0};
-      return launch_union_w<W, kInl>(a, us, s);
-    }
     default:
       return hipErrorInvalidValue;
   }
@@ -1122,22 +1142,103 @@ hipError_t launch_rehash(int W, bool inl, const uint64_t* rows, uint64_t nrows, 
   return hipGetLastError();
 }
 
-hipError_t launch_gen(int W, int op, const GenArgs& a, bool same_level, hipStream_t s) {
-  if (a.e1 <= a.e0) return hipSuccess;
-  REI_DISPATCH_WI(W, a.inl, return (launch_gen_w<kW, kI>(op, a, same_level, s)));
+// Adds a launch's survivor slots and ranges to the chunk's; false when they
+// do not fit 32-bit indices.
+bool take_slots(SlotPlan* sp, uint64_t slots, uint64_t regions) {
+  if (sp->slots + slots > kMaxSlots || sp->regions + regions > kMaxSlots) return false;
+  sp->slots += slots;
+  sp->regions += regions;
+  return true;
+}
+
+hipError_t plan_gen(int op, GenArgs* a, SlotPlan* sp) {
+  const uint64_t cnt = a->e1 - a->e0;
+  if (a->e1 <= a->e0) return hipErrorInvalidValue;
+  // (a star's workgroup is one wave of candidates)
+  a->per_wave = op == OP_STAR ? (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(1, cnt / (64 * 4096)))
+                              : iterations_per_wave(cnt);
+  const uint64_t per = (uint64_t)a->per_wave * 64;
+  const uint64_t waves = op == OP_STAR ? (cnt + per - 1) / per : 4 * ((cnt + 4 * per - 1) / (4 * per));
+  a->slot0 = (uint32_t)sp->slots;
+  a->reg0 = (uint32_t)sp->regions;
+  return take_slots(sp, waves * per, waves) ? hipSuccess : hipErrorInvalidConfiguration;
+}
+
+hipError_t plan_concat_set(int W, const GenArgs& a, ConcatSet* cs, SlotPlan* sp) {
+  if (cs->n == 0 || cs->n > (uint32_t)kMaxConcatParts) return hipErrorInvalidValue;
+  // tiles in LDS: at most 32 KB
+  const uint32_t yt_cap = (uint32_t)std::max(1, std::min(kConcatYT, 32768 / (512 * W)));
+  // per part: uniform rows per workgroup at most concat_xi (16 by default),
+  // fewer (down to 4), then fewer tiles, while its grid has under concat_wg
+  // workgroups (2048 by default)
+  const uint64_t target = a.concat_wg ? a.concat_wg : 2048;
+  const uint32_t xi_max = a.concat_xi ? std::min<uint32_t>(a.concat_xi, 64) : 16;
+  uint64_t wgs_total = 0;
+  for (uint32_t k = 0; k < cs->n; ++k) {
+    ConcatPart& p = cs->p[k];
+    const uint64_t nR = p.rcount;
+    if (nR == 0 || p.e1 <= p.e0) return hipErrorInvalidValue;
+    p.i_lo = p.e0 / nR;
+    p.i_hi = (p.e1 - 1) / nR;
+    const uint64_t rowsx = p.i_hi - p.i_lo + 1;
+    // the operand across the lanes: the one whose tiles of 64 fill better
+    // (fewer wave iterations; left rows when the right level is small)
+    p.left = ((rowsx + 63) / 64) * nR < rowsx * ((nR + 63) / 64) ? 1u : 0u;
+    const uint64_t nT = ((p.left ? rowsx : nR) + 63) / 64, nU = p.left ? nR : rowsx;
+    uint32_t yt = (uint32_t)std::min<uint64_t>(yt_cap, nT);
+    uint32_t xi = xi_max;
+    auto wgs = [&](uint32_t y, uint32_t x) { return ((nT + y - 1) / y) * ((nU + x - 1) / x); };
+    while (xi > 4 && (wgs(yt, xi) < target || xi >= 2 * nU)) xi /= 2;
+    while (yt > 1 && wgs(yt, xi) < target) yt /= 2;
+    const uint64_t gx = (nT + yt - 1) / yt, gy = (nU + xi - 1) / xi;
+    p.yt = yt;
+    p.xi = xi;
+    p.gx = (uint32_t)gx;
+    p.wg0 = (uint32_t)wgs_total;
+    p.slot0 = (uint32_t)sp->slots;
+    p.reg0 = (uint32_t)sp->regions;
+    wgs_total += gx * gy;
+    if (wgs_total > 0x7fffffffull || !take_slots(sp, nT * nU * 64, gx * gy * 4)) return hipErrorInvalidConfiguration;
+  }
+  cs->wgs = (uint32_t)wgs_total;
+  return hipSuccess;
+}
+
+hipError_t plan_union_set(UnionSet* us, SlotPlan* sp) {
+  if (us->n == 0 || us->n > (uint32_t)kMaxUnionParts) return hipErrorInvalidValue;
+  uint64_t total = 0, wgs = 0;
+  for (uint32_t k = 0; k < us->n; ++k) total += us->p[k].e1 - us->p[k].e0;
+  us->per_wave = iterations_per_wave(total);
+  const uint64_t per = 4ull * 64 * us->per_wave;  // candidates per workgroup
+  for (uint32_t k = 0; k < us->n; ++k) {
+    UnionPart& p = us->p[k];
+    if (p.e1 <= p.e0 || p.lcount == 0 || (!p.same && p.rcount == 0)) return hipErrorInvalidValue;
+    const uint64_t g = (p.e1 - p.e0 + per - 1) / per;
+    p.wg0 = (uint32_t)wgs;
+    p.slot0 = (uint32_t)sp->slots;
+    p.reg0 = (uint32_t)sp->regions;
+    wgs += g;
+    if (wgs > 0x7fffffffull || !take_slots(sp, g * per, 4 * g)) return hipErrorInvalidConfiguration;
+  }
+  us->wgs = (uint32_t)wgs;
+  return hipSuccess;
+}
+
+hipError_t launch_gen(int W, int op, const GenArgs& a, hipStream_t s) {
+  if (a.e1 <= a.e0 || a.per_wave == 0) return hipErrorInvalidValue;
+  REI_DISPATCH_WI(W, a.inl, return (launch_gen_w<kW, kI>(op, a, s)));
   return hipGetLastError();
 }
 
 hipError_t launch_union_set(int W, const GenArgs& a, const UnionSet& us, hipStream_t s) {
-  if (us.n == 0) return hipSuccess;
-  if (!a.rows || !a.st || !a.ctrl) return hipErrorInvalidValue;
-  REI_DISPATCH_WI(W, a.inl, return (launch_union_w<kW, kI>(a, us, s)));
+  if (!a.rows || !a.st || !a.ctrl || !a.reg || us.wgs == 0) return hipErrorInvalidValue;
+  REI_DISPATCH_WI(W, a.inl,
+                  launch_timed(gen_union<kW, kI>, dim3(us.wgs), dim3(256), 0, s, a, us));
   return hipGetLastError();
 }
 
 hipError_t launch_concat_set(int W, const GenArgs& a, const ConcatSet& cs, hipStream_t s) {
-  if (cs.n == 0) return hipSuccess;
-  if (!a.rows || !a.gt_off || !a.gt_pair || !a.st || !a.ctrl) return hipErrorInvalidValue;
+  if (!a.rows || !a.gt_off || !a.gt_pair || !a.st || !a.ctrl || !a.reg || cs.wgs == 0) return hipErrorInvalidValue;
   REI_DISPATCH_WI(W, a.inl, return (launch_concat_w<kW, kI>(a, cs, s)));
   return hipGetLastError();
 }
@@ -1189,9 +1290,15 @@ hipError_t launch_gen_pieces(int W, const GenArgs& a, const PieceArgs& p, hipStr
   return hipGetLastError();
 }
 
+// Workgroups that walk a chunk's survivors: a thread per possible survivor of
+// the pieces, a wave per range, 8192 workgroups at most.
+uint32_t survivor_grid(const ChunkArgs& a) {
+  return grid_for(std::max<uint64_t>(a.dense_cap, 64ull * a.n_reg), 256, 8192);
+}
+
 hipError_t launch_insert(int W, const ChunkArgs& a, hipStream_t s) {
-  REI_DISPATCH_WI(W, a.inl, hipLaunchKernelGGL((insert_survivors<kW, kI>), dim3(grid_for(a.len, 256, 8192)),
-                                               dim3(256), 0, s, a));
+  REI_DISPATCH_WI(W, a.inl, hipLaunchKernelGGL((insert_survivors<kW, kI>), dim3(survivor_grid(a)), dim3(256), 0, s,
+                                               a));
   return hipGetLastError();
 }
 
@@ -1203,12 +1310,13 @@ bool finalize_in_one_workgroup(int W, uint64_t len) {
 
 hipError_t launch_finalize(int W, const ChunkArgs& a, hipStream_t s) {
   if (finalize_in_one_workgroup(W, a.len)) {
+    if (a.n_reg) return hipErrorInvalidValue;  // (reads the pieces' survivors only)
     REI_DISPATCH_WI(W, a.inl, hipLaunchKernelGGL((finalize_small<kW, kI>), dim3(1), dim3(1024), 0, s, a));
     return hipGetLastError();
   }
   // the bitmap was cleared by insert_survivors
   if (a.clear_words != a.n_bitmap_words) return hipErrorInvalidValue;
-  const uint32_t g = grid_for(a.len, 256, 8192);
+  const uint32_t g = survivor_grid(a);
   if (a.inl)
     hipLaunchKernelGGL(mark_winners<true>, dim3(g), dim3(256), 0, s, a);
   else
