@@ -267,10 +267,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
   const Sink sink{d.skey, d.se, d.spos, &s_nsurv, &s_ans};
 
   // start: empty table, zero counters
-  for (uint64_t i = tid; i <= tmask; i += kT) {
-    d.slots[i] = kEmpty;
-    if (kInl) d.sref[i] = kEmpty;
-  }
+  for (uint64_t i = tid; i < (tmask + 1) * kSlotWords<kInl>; i += kT) d.slots[i] = kEmpty;
   // guide table and words-by-length offsets into LDS (batchable instances
   // have at most batch_max_ic(W) words and batch_max_pairs(W) cuts)
   for (uint32_t i = tid; i <= d.n; i += kT) s_gto[i] = d.gt_off[i];
@@ -345,10 +342,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
           uint64_t cap = tmask + 1;
           while (cap < 4 * (total + len) && cap <= d.slot_mask) cap *= 2;
           tmask = min(d.slot_mask, cap - 1);
-          for (uint64_t i = tid; i <= tmask; i += kT) {
-            d.slots[i] = kEmpty;
-            if (kInl) d.sref[i] = kEmpty;
-          }
+          for (uint64_t i = tid; i < (tmask + 1) * kSlotWords<kInl>; i += kT) d.slots[i] = kEmpty;
           __syncthreads();
           for (uint64_t row = tid; row < total; row += kT) {
             uint64_t key[W];
@@ -535,8 +529,9 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
 #pragma unroll
           for (int k = 0; k < W; ++k) key[k] = d.skey[(uint64_t)sid * W + k];
           const uint64_t h = d.spos[sid];
-          const uint64_t pos = table_insert<W, kInl>(d.slots, d.sref, tmask, d.rows, d.skey, key, h,
-                                                     new_ref(d.se[sid], sid));
+          uint64_t old;
+          const uint64_t pos = table_insert<W, kInl>(d.slots, tmask, d.rows, d.skey, key, h,
+                                                     new_ref(d.se[sid], sid), &old);
           d.spos[sid] = spos_pack(pos, h);
         }
         phase_barrier();
@@ -547,7 +542,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
         __syncthreads();
         for (uint32_t sid = tid; sid < ns; sid += kT) {
           const uint32_t e = d.se[sid];
-          if (table_is_winner<kInl>(d.slots, d.sref, d.spos[sid], new_ref(e, sid)))
+          if (table_is_winner<kInl>(d.slots, d.spos[sid], new_ref(e, sid)))
             atomicOr(&s_bm[e >> 5], 1u << (e & 31));
         }
         __syncthreads();
@@ -583,7 +578,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
 #pragma unroll
             for (int k = 0; k < W; ++k) d.rows[row * W + k] = d.skey[(uint64_t)sid * W + k];
             d.aux[row] = E0 + e;
-            table_publish<kInl>(d.slots, d.sref, d.spos[sid], row);
+            table_publish<kInl>(d.slots, d.spos[sid], row);
           }
         } else {
           // wide rows: ranks into LDS (over the tiles, idle in this phase),
@@ -600,7 +595,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
             d.rows[row * W + k] = d.skey[(uint64_t)q * W + k];
             if (k == 0) {
               d.aux[row] = E0 + d.se[q];
-              table_publish<kInl>(d.slots, d.sref, d.spos[q], row);
+              table_publish<kInl>(d.slots, d.spos[q], row);
             }
           }
         }

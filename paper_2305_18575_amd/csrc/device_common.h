@@ -179,9 +179,13 @@ __device__ __forceinline__ uint64_t star_fold(const uint64_t* X, const uint64_t*
 // (0 | fingerprint | row) or a survivor of the running chunk (1 | e | sid);
 // equal keys are confirmed against the row or the survivor's key.
 // Inline form (kInl: one word per language and |ic| <= 63, so no language is
-// all ones): a slot holds the key itself; sref[pos] holds the smallest
-// survivor reference of the running chunk for that key (EMPTY otherwise).
-// A probe is then a single read.
+// all ones): a slot is a pair, the key itself and the smallest survivor
+// reference for it, so that a probe is a single read and an insertion's two
+// atomics meet in one line.
+
+// 64-bit words per slot.
+template <bool kInl>
+constexpr uint32_t kSlotWords = kInl ? 2 : 1;
 
 template <int W>
 __device__ __forceinline__ bool key_eq(const uint64_t* p, const uint64_t (&key)[W]) {
@@ -202,7 +206,7 @@ __device__ __forceinline__ bool table_find(const uint64_t* slots, uint64_t mask,
   uint64_t pos = h & mask;
   if constexpr (kInl) {
     for (;;) {
-      const uint64_t v = slots[pos];
+      const uint64_t v = slots[2 * pos];
       if (v == kEmpty) return false;
       if (v == key[0]) return true;
       pos = (pos + 1) & mask;
@@ -220,21 +224,22 @@ __device__ __forceinline__ bool table_find(const uint64_t* slots, uint64_t mask,
 
 // Inserts a survivor (reference `mine` = 1 | e | sid); equal keys meet in one
 // slot and keep the smallest reference.  Returns the slot.
+// old: the reference the slot held for this key before (EMPTY: none).
 template <int W, bool kInl>
-__device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t* sref, uint64_t mask,
-                                                 const uint64_t* rows, const uint64_t* skey,
-                                                 const uint64_t (&key)[W], uint64_t h, uint64_t mine) {
+__device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask, const uint64_t* rows,
+                                                 const uint64_t* skey, const uint64_t (&key)[W], uint64_t h,
+                                                 uint64_t mine, uint64_t* old) {
   uint64_t pos = h & mask;
   if constexpr (kInl) {
     for (;;) {
-      uint64_t v = slots[pos];
+      uint64_t v = slots[2 * pos];
       if (v == kEmpty) {
-        v = atomicCAS((unsigned long long*)&slots[pos], (unsigned long long)kEmpty,
+        v = atomicCAS((unsigned long long*)&slots[2 * pos], (unsigned long long)kEmpty,
                       (unsigned long long)key[0]);
         if (v == kEmpty) v = key[0];  // claimed
       }
       if (v == key[0]) {
-        atomicMin((unsigned long long*)&sref[pos], (unsigned long long)mine);
+        *old = atomicMin((unsigned long long*)&slots[2 * pos + 1], (unsigned long long)mine);
         return pos;
       }
       pos = (pos + 1) & mask;
@@ -246,16 +251,20 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t* sref
       if (v == kEmpty) {
         v = atomicCAS((unsigned long long*)&slots[pos], (unsigned long long)kEmpty,
                       (unsigned long long)mine);
-        if (v == kEmpty) return pos;  // claimed
+        if (v == kEmpty) {  // claimed
+          *old = kEmpty;
+          return pos;
+        }
       }
       if (v & kNewFlag) {
         // another survivor owns the slot; its key never changes
         if (key_eq<W>(skey + (uint64_t)(uint32_t)v * W, key)) {
-          atomicMin((unsigned long long*)&slots[pos], (unsigned long long)mine);
+          *old = atomicMin((unsigned long long*)&slots[pos], (unsigned long long)mine);
           return pos;
         }
       } else if (((v >> kRowBits) & 0xFFFFFFull) == fp && key_eq<W>(rows + (v & kRowMask) * W, key)) {
-        return pos;  // stored already (the generators filter these; kept for safety)
+        *old = 0;  // stored already (the generators filter these; kept for safety): below any survivor
+        return pos;
       }
       pos = (pos + 1) & mask;
     }
@@ -272,18 +281,17 @@ __device__ __forceinline__ uint64_t spos_pack(uint64_t pos, uint64_t h) { return
 // After all inserts of the chunk: does `mine` own its key's slot?  rec is
 // the survivor's slot record.
 template <bool kInl>
-__device__ __forceinline__ bool table_is_winner(const uint64_t* slots, const uint64_t* sref, uint64_t rec,
-                                                uint64_t mine) {
+__device__ __forceinline__ bool table_is_winner(const uint64_t* slots, uint64_t rec, uint64_t mine) {
   const uint64_t pos = rec & kPosMask;
-  return kInl ? sref[pos] == mine : slots[pos] == mine;
+  return kInl ? slots[2 * pos + 1] == mine : slots[pos] == mine;
 }
 
 // The winner (slot record rec) is now stored as `row`.
 template <bool kInl>
-__device__ __forceinline__ void table_publish(uint64_t* slots, uint64_t* sref, uint64_t rec, uint64_t row) {
+__device__ __forceinline__ void table_publish(uint64_t* slots, uint64_t rec, uint64_t row) {
   const uint64_t pos = rec & kPosMask;
   if constexpr (kInl)
-    sref[pos] = kEmpty;  // the key is in the slot already
+    slots[2 * pos + 1] = kEmpty;  // the key is in the slot already
   else
     slots[pos] = ((rec >> 40) << kRowBits) | row;
 }
@@ -295,8 +303,8 @@ __device__ __forceinline__ void table_rebuild_one(uint64_t* slots, uint64_t mask
   const uint64_t h = hash_key<W>(key);
   const uint64_t v = kInl ? key[0] : ((fingerprint(h) << kRowBits) | row);
   uint64_t pos = h & mask;
-  while (atomicCAS((unsigned long long*)&slots[pos], (unsigned long long)kEmpty, (unsigned long long)v) !=
-         kEmpty)
+  while (atomicCAS((unsigned long long*)&slots[pos * kSlotWords<kInl>], (unsigned long long)kEmpty,
+                   (unsigned long long)v) != kEmpty)
     pos = (pos + 1) & mask;
 }
 

@@ -117,7 +117,6 @@ struct rei_instance {
   uint64_t rows_alloc = 0;
   // dedup table
   uint64_t* d_slots = nullptr;
-  uint64_t* d_sref = nullptr;  // inline-key table only
   uint64_t slots_cap = 0;
   bool inl = false;            // one word per language and |ic| <= 63: keys live in the slots
   // chunk buffers
@@ -127,7 +126,13 @@ struct rei_instance {
   uint64_t surv_cap = 0;
   uint2* d_reg = nullptr;      // the large generators' survivor ranges
   uint64_t reg_cap = 0;
+  // two winner bitmaps, taken in turn by the chunks: words of each that the
+  // next insertion has to clear, and the most a chunk has used since both were
+  // all zero (chunks after a stop clear nothing)
   uint32_t* d_bitmap = nullptr;
+  int bm_turn = 0;
+  uint32_t bm_dirty[2] = {0, 0}, bm_high = 0;
+  uint64_t ref_gen = (1ull << 36) - 2;  // inline-key references' generation, one lower each chunk
   uint32_t* d_prefix = nullptr;
   uint32_t* d_bsums = nullptr;
   uint64_t bitmap_cap = 0;  // words
@@ -339,28 +344,33 @@ rei_status ensure_rows(rei_instance* in, uint64_t need, hipStream_t s) {
   return REI_OK;
 }
 
+// Bytes per table slot: with inline keys a pair, the key and its reference.
+uint64_t slot_bytes(const rei_instance* in) { return in->inl ? 16 : 8; }
+
+// A table of cap slots (not filled) in place of the present one.
+rei_status table_alloc(rei_instance* in, uint64_t cap) {
+  dfree(in, in->d_slots);
+  in->slots_cap = 0;
+  HIP_OK(in, dev_alloc(in, &in->d_slots, cap * slot_bytes(in)));
+  in->slots_cap = cap;
+  return REI_OK;
+}
+
 // The table keeps its load at most 1/2: entries = stored rows + possible new ones.
 rei_status ensure_table(rei_instance* in, uint64_t entries, hipStream_t s, bool force) {
   if (!force && in->slots_cap >= 2 * entries) return REI_OK;
   uint64_t cap = std::max<uint64_t>(4096, pow2_at_least(4 * entries));
   if (force && in->slots_cap >= cap) cap = in->slots_cap;
-  if (cap != in->slots_cap) {
-    dfree(in, in->d_slots);
-    dfree(in, in->d_sref);
-    in->slots_cap = 0;
-    HIP_OK(in, dev_alloc(in, &in->d_slots, cap * 8));
-    if (in->inl) HIP_OK(in, dev_alloc(in, &in->d_sref, cap * 8));
-    in->slots_cap = cap;
-  }
-  LAUNCH(in, s, REI_K_OTHER, cap, launch_fill(in->d_slots, cap, kEmpty, s));
-  if (in->inl) LAUNCH(in, s, REI_K_OTHER, cap, launch_fill(in->d_sref, cap, kEmpty, s));
+  rei_status r;
+  if (cap != in->slots_cap && (r = table_alloc(in, cap)) != REI_OK) return r;
+  LAUNCH(in, s, REI_K_OTHER, cap, launch_fill(in->d_slots, cap * (slot_bytes(in) / 8), kEmpty, s));
   LAUNCH(in, s, REI_K_OTHER, in->known_rows,
          launch_rehash(in->st.W, in->inl, in->d_rows, in->known_rows, in->d_slots, cap - 1, s));
   return REI_OK;
 }
 
 // slots: survivor slots; len: candidates (bitmap bits); regions: survivor ranges.
-rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, uint64_t regions) {
+rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, uint64_t regions, hipStream_t s) {
   const int W = in->st.W;
   if (slots > in->surv_cap) {
     dfree(in, in->d_skey);
@@ -385,10 +395,12 @@ rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, 
     dfree(in, in->d_prefix);
     dfree(in, in->d_bsums);
     in->bitmap_cap = 0;
-    HIP_OK(in, dev_alloc(in, &in->d_bitmap, words * 4));
+    in->bm_dirty[0] = in->bm_dirty[1] = in->bm_high = 0;
+    HIP_OK(in, dev_alloc(in, &in->d_bitmap, words * 8));  // both
     HIP_OK(in, dev_alloc(in, &in->d_prefix, words * 4));
     HIP_OK(in, dev_alloc(in, &in->d_bsums, ((words + 1023) / 1024 + 1) * 4));
     in->bitmap_cap = words;
+    LAUNCH(in, s, REI_K_OTHER, words, launch_fill((uint64_t*)in->d_bitmap, words, 0, s));
   }
   return REI_OK;
 }
@@ -642,9 +654,9 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       return REI_OK;
     }
     if (otf_level) {
-      if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions)) != REI_OK) return r;
+      if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions, s)) != REI_OK) return r;
     } else {
-      if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions)) != REI_OK) return r;
+      if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s)) != REI_OK) return r;
       if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + len), s)) != REI_OK) return r;
       if ((r = ensure_table(in, in->known_rows + len, s, false)) != REI_OK) return r;
     }
@@ -692,7 +704,6 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   ca.rows_w = in->d_rows;
   ca.aux = in->d_aux;
   ca.slots = in->d_slots;
-  ca.sref = in->d_sref;
   ca.inl = in->inl ? 1u : 0u;
   ca.slot_mask = in->slots_cap - 1;
   ca.skey = in->d_skey;
@@ -701,7 +712,10 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   ca.reg = in->d_reg;
   ca.n_reg = (uint32_t)sp.regions;
   ca.dense_cap = dense_cap;
-  ca.bitmap = in->d_bitmap;
+  ca.bitmap = in->d_bitmap + in->bm_turn * in->bitmap_cap;
+  ca.bitmap_next = in->d_bitmap + (1 - in->bm_turn) * in->bitmap_cap;
+  ca.clear_words = in->bm_dirty[1 - in->bm_turn];
+  ca.ref_gen = in->ref_gen;
   ca.word_prefix = in->d_prefix;
   ca.block_sums = in->d_bsums;
   ca.n_bitmap_words = (uint32_t)words;
@@ -717,12 +731,16 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   ca.hst = in->v_state;
   ca.hlev = in->v_levels;
   ca.nlev = L;
-  ca.clear_words = finalize_in_one_workgroup(W, len) ? 0u : (uint32_t)words;
   if (otf_level) {
     LAUNCH(in, s, REI_K_COMPACT, len, launch_account(ca, s));
     ++in->chunks_enq;
     return REI_OK;
   }
+  in->bm_dirty[in->bm_turn] = (uint32_t)words;
+  in->bm_high = std::max(in->bm_high, (uint32_t)words);
+  in->bm_dirty[1 - in->bm_turn] = 0;
+  in->bm_turn = 1 - in->bm_turn;
+  --in->ref_gen;
   LAUNCH(in, s, REI_K_INSERT, len, launch_insert(W, ca, s));
   LAUNCH(in, s, REI_K_COMPACT, len, launch_finalize(W, ca, s));
   ++in->chunks_enq;
@@ -1015,7 +1033,18 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
   in->resume_level = 0;
   in->otf_level = 0;
   in->otf_blocked = false;
-  LAUNCH(in, s, REI_K_OTHER, 1, launch_state_reset(in->d_ctrl, in->d_state, in->row_cap, in->otf_on, s));
+  ResetArgs ra{};
+  ra.ctrl = in->d_ctrl;
+  ra.st = in->d_state;
+  ra.row_cap = in->row_cap;
+  ra.otf_on = in->otf_on ? 1u : 0u;
+  for (int b = 0; b < 2; ++b) {
+    ra.bitmap[b] = in->d_bitmap + b * in->bitmap_cap;
+    ra.bitmap_words[b] = in->bm_high;
+    in->bm_dirty[b] = 0;
+  }
+  in->bm_high = 0;
+  in->bm_turn = 0;
   in->chunks_enq = 0;
   if (c_from > c1) {
     // The batched solver stored every level below c_from (rows and
@@ -1040,6 +1069,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     hs->answer_e = 0;
     hs->resume_level = 0;
     hs->chunks = 0;
+    LAUNCH(in, s, REI_K_OTHER, 1, launch_search_reset(ra, s));
     HIP_OK(in, hipMemcpyAsync(in->d_state, hs, sizeof(DevState), hipMemcpyHostToDevice, s));
     HIP_OK(in, hipMemcpyAsync(in->d_levels, in->h_levels, 3 * L * 8, hipMemcpyHostToDevice, s));
     // the batched solver used a prefix of the table: rebuild it at full size
@@ -1048,7 +1078,12 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     // a fresh search: nothing stored yet (also when a batched attempt ran out
     // of its preallocated rows and left some behind)
     in->known_rows = 0;
-    LAUNCH(in, s, REI_K_OTHER, 3 * L, launch_fill(in->d_levels, 3 * L, 0, s));
+    if (in->slots_cap == 0 && (r = table_alloc(in, 4096)) != REI_OK) return r;
+    ra.levels = in->d_levels;
+    ra.n_levels = 3 * L;
+    ra.slots = in->d_slots;
+    ra.n_slot_words = in->slots_cap * (slot_bytes(in) / 8);
+    LAUNCH(in, s, REI_K_OTHER, ra.n_slot_words, launch_search_reset(ra, s));
     // the host mirrors of the state just reset (the stream has no earlier
     // work of this instance that writes them)
     std::memset(in->h_levels, 0, 3 * L * 8);
@@ -1062,7 +1097,6 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     hs->otf_on = in->otf_on ? 1u : 0u;
     hs->otf = 0;
     hs->chunks = 0;
-    if ((r = ensure_table(in, 1024, s, true)) != REI_OK) return r;
   }
   std::vector<Block> blocks;
   bool stopped = false;
@@ -1350,7 +1384,6 @@ BatchDesc make_desc(const rei_instance* in) {
   d.rows_alloc = in->rows_alloc;
   d.row_cap = in->row_cap;
   d.slots = in->d_slots;
-  d.sref = in->d_sref;
   d.inl = in->inl ? 1u : 0u;
   d.level_max = level_max_of(in);
   const int64_t us = in->batch_time_us < 0 ? kBatchTimeUs : in->batch_time_us;
@@ -1394,7 +1427,7 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
       continue;
     }
     const uint64_t R = batch_rows(in, arena_bytes);
-    if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0)) != REI_OK) return r;
+    if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, s)) != REI_OK) return r;
     if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
     if ((r = ensure_table(in, in->rows_alloc + kBatchChunk, s, false)) != REI_OK) return r;
     const int g = in->inl ? 0 : in->st.W;
@@ -1648,7 +1681,6 @@ void free_search_buffers(rei_instance* in) {
   dfree(in, in->d_rows);
   dfree(in, in->d_aux);
   dfree(in, in->d_slots);
-  dfree(in, in->d_sref);
   dfree(in, in->d_skey);
   dfree(in, in->d_se);
   dfree(in, in->d_spos);
@@ -1661,6 +1693,7 @@ void free_search_buffers(rei_instance* in) {
   in->surv_cap = 0;
   in->reg_cap = 0;
   in->bitmap_cap = 0;
+  in->bm_dirty[0] = in->bm_dirty[1] = in->bm_high = 0;
   in->known_rows = 0;
   in->h_aux_valid = false;
 }
@@ -1676,7 +1709,6 @@ void free_device(rei_instance* in) {
   dfree(in, in->d_rows);
   dfree(in, in->d_aux);
   dfree(in, in->d_slots);
-  dfree(in, in->d_sref);
   dfree(in, in->d_skey);
   dfree(in, in->d_se);
   dfree(in, in->d_spos);
@@ -2070,8 +2102,6 @@ rei_status rei_solve_batch_noalloc(rei_instance* const* insts, size_t n, void* h
       d.aux = (uint64_t*)p;
       p += up(R * 8);
       d.slots = (uint64_t*)p;
-      p += T * 8;
-      d.sref = in->inl ? (uint64_t*)p : nullptr;
       d.rows_alloc = R;
       d.slot_mask = T - 1;
       d.level_max = ~0ull;  // the whole search stays in the workgroup
@@ -2913,7 +2943,7 @@ void server_sched_queue(rei_server* sv) {
             continue;
           }
           const uint64_t R = batch_rows(in, sv->arena);
-          if ((a.r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0)) != REI_OK) continue;
+          if ((a.r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, sv->setup)) != REI_OK) continue;
           if ((a.r = ensure_rows(in, R, sv->setup)) != REI_OK) continue;
           if ((a.r = ensure_table(in, in->rows_alloc + kBatchChunk, sv->setup, false)) != REI_OK) continue;
           setup_used = true;
@@ -3315,7 +3345,7 @@ BatchDesc graph_desc(const rei_instance* in) {
 rei_status graph_arena(rei_instance* in, uint64_t arena_bytes, hipStream_t s) {
   rei_status r;
   const uint64_t R = batch_rows(in, arena_bytes);
-  if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0)) != REI_OK) return r;
+  if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, s)) != REI_OK) return r;
   if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
   return ensure_table(in, in->rows_alloc + kBatchChunk, s, false);
 }

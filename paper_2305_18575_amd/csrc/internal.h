@@ -138,13 +138,13 @@ struct ChunkArgs {
   uint64_t* rows_w;
   uint64_t* aux;
   uint64_t* slots;
-  uint64_t* sref;             // inline-key table: smallest survivor per slot
   uint64_t slot_mask;
+  uint64_t ref_gen;           // inline-key table: this chunk's references (see chunk_ref)
   uint32_t inl;
   uint64_t* skey;
   uint32_t* se;
   uint64_t* spos;             // slot of each survivor after insertion
-  uint32_t* bitmap;           // one bit per chunk-relative index: winner
+  uint32_t* bitmap;           // one bit per chunk-relative index: winner (all zero before insertion)
   uint32_t* word_prefix;      // exclusive prefix of popcounts
   uint32_t* block_sums;
   uint32_t n_bitmap_words;
@@ -161,7 +161,8 @@ struct ChunkArgs {
   DevState* hst;
   uint64_t* hlev;
   uint64_t nlev;
-  uint32_t clear_words;       // bitmap words insert_survivors clears (the grid finalize path)
+  uint32_t* bitmap_next;      // the next chunk's bitmap: insert_survivors clears
+  uint32_t clear_words;       // this many words of it
   const uint2* reg;           // the large generators' ranges: first slot, survivors
   uint32_t n_reg;
   uint64_t dense_cap;         // most survivors the pieces can append (slots 0 .. dense_cap - 1)
@@ -172,8 +173,7 @@ struct SlotPlan {
   uint64_t slots, regions;
 };
 constexpr uint64_t kMaxSlots = 1ull << 31;
-// Whether a chunk is finalized by one workgroup (else by the grid kernels,
-// which need the bitmap cleared by insert_survivors).
+// Whether a chunk is finalized by one workgroup (else by the grid kernels).
 bool finalize_in_one_workgroup(int W, uint64_t len);
 
 // Events of this thread's next timed kernel launch (set by the library's
@@ -230,7 +230,22 @@ struct TreeArgs {
   uint32_t ccost[kTreeMaxChars];  // character costs in enumeration order
 };
 hipError_t launch_decode_tree(const TreeArgs& t, hipStream_t s);
-hipError_t launch_state_reset(Ctrl* c, DevState* st, uint64_t row_cap, bool otf_on, hipStream_t s);
+// Start of a per-chunk search, one launch: state and control block reset,
+// level counters to zero, the table's words to EMPTY, both winner bitmaps'
+// used words to zero (any count may be 0).
+struct ResetArgs {
+  Ctrl* ctrl;
+  DevState* st;
+  uint64_t row_cap;
+  uint32_t otf_on;
+  uint64_t* levels;
+  uint64_t n_levels;
+  uint64_t* slots;
+  uint64_t n_slot_words;
+  uint32_t* bitmap[2];
+  uint32_t bitmap_words[2];
+};
+hipError_t launch_search_reset(const ResetArgs& a, hipStream_t s);
 constexpr uint64_t kSmallChunk = 1ull << 14;   // candidates finalized by one workgroup
 
 
@@ -334,8 +349,7 @@ struct BatchDesc {
   uint64_t* aux;
   uint64_t rows_alloc;        // rows the buffers hold
   uint64_t row_cap;           // rows the cache budget allows
-  uint64_t* slots;
-  uint64_t* sref;
+  uint64_t* slots;            // (pairs with inline keys)
   uint64_t slot_mask;         // arena's table: rows_alloc + kBatchChunk entries at load <= 1/2
                               // (the kernel uses a growing prefix of it)
   uint32_t inl, pad2;

@@ -9,9 +9,8 @@
 //             lower ctrl->answer_e (Algorithm 2: uniqueness, then precision);
 //   insert    survivors claim table slots; equal languages meet in one slot
 //             and keep the smallest enumeration index (deterministic
-//             atomicMin), so the first occurrence wins;
-//   mark      winners set their bit in a per-chunk bitmap indexed by
-//             enumeration index;
+//             atomicMin), so the first occurrence wins; winners' bits end up
+//             set in a per-chunk bitmap indexed by enumeration index;
 //   scan      exclusive prefix of the bitmap popcounts = rank of each winner
 //             in enumeration order;
 //   compact   winners before the answer are appended to the level in rank
@@ -638,12 +637,6 @@ __global__ void fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
     p[i] = v;
 }
 
-__global__ void fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
 __device__ __forceinline__ void ctrl_clear(Ctrl* c) {
   c->n_surv = 0;
   c->answer_e = ~0u;
@@ -652,17 +645,25 @@ __device__ __forceinline__ void ctrl_clear(Ctrl* c) {
   c->overflow_e = ~0u;
 }
 
-__global__ void state_reset(Ctrl* c, DevState* st, uint64_t row_cap, uint32_t otf_on) {
-  ctrl_clear(c);
-  st->total_rows = 0;
-  st->row_cap = row_cap;
-  st->stop = STOP_NONE;
-  st->answer_cost = 0;
-  st->answer_e = 0;
-  st->resume_level = 0;
-  st->otf_on = otf_on;
-  st->otf = 0;
-  st->chunks = 0;
+__global__ __launch_bounds__(256) void search_reset(ResetArgs a) {
+  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (uint64_t)gridDim.x * blockDim.x;
+  if (t == 0) {
+    ctrl_clear(a.ctrl);
+    DevState* st = a.st;
+    st->total_rows = 0;
+    st->row_cap = a.row_cap;
+    st->stop = STOP_NONE;
+    st->answer_cost = 0;
+    st->answer_e = 0;
+    st->resume_level = 0;
+    st->otf_on = a.otf_on;
+    st->otf = 0;
+    st->chunks = 0;
+  }
+  for (uint64_t i = t; i < a.n_levels; i += n) a.levels[i] = 0;
+  for (uint64_t i = t; i < a.n_slot_words; i += n) a.slots[i] = kEmpty;
+  for (int b = 0; b < 2; ++b)
+    for (uint64_t i = t; i < a.bitmap_words[b]; i += n) a.bitmap[b][i] = 0;
 }
 
 template <int W, bool kInl>
@@ -679,31 +680,90 @@ __global__ __launch_bounds__(256) void rehash_rows(const uint64_t* rows, uint64_
 
 // Every survivor of the chunk once, over the grid: the pieces' (slots 0 ..
 // n_surv - 1), then those in the large generators' per-wave ranges, a wave
-// per range.
+// per range.  f(sid, have) is called by whole waves; lanes without a survivor
+// get have = false.
 template <typename F>
 __device__ __forceinline__ void for_survivors(const ChunkArgs& a, F f) {
-  const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, threads = gridDim.x * blockDim.x;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, waves = (gridDim.x * blockDim.x) >> 6;
   const uint32_t ns = a.ctrl->n_surv;
-  for (uint32_t sid = tid; sid < ns; sid += threads) f(sid);
-  for (uint32_t r = tid >> 6; r < a.n_reg; r += threads >> 6) {
+  for (uint32_t k = 64 * wave; k < ns; k += 64 * waves) f(k + lane, k + lane < ns);
+  for (uint32_t r = wave; r < a.n_reg; r += waves) {
     const uint2 g = a.reg[r];
-    for (uint32_t k = tid & 63; k < g.y; k += 64) f(g.x + k);
+    for (uint32_t k = 0; k < g.y; k += 64) f(g.x + k + lane, k + lane < g.y);
   }
 }
 
+// Toggles bit e of the bitmap for every lane with `on`, lanes next to each
+// other that share a word in one atomic (survivors lie in enumeration order
+// along a wave, mostly several to a word).  Called by the whole wave.
+__device__ __forceinline__ void toggle_bits(uint32_t* bitmap, uint32_t e, bool on) {
+  const uint32_t lane = lane_id();
+  const uint32_t w = on ? e >> 5 : ~0u;
+  uint32_t m = on ? 1u << (e & 31) : 0u;
+  const uint32_t w_before = (uint32_t)__shfl_up((int)w, 1, kWave);
+  const bool head = lane == 0 || w_before != w;
+  const uint64_t heads = __ballot(head);
+  // first lane after this lane's run of equal words
+  const uint64_t above = lane == 63 ? 0ull : heads >> (lane + 1);
+  const uint32_t end = above ? lane + (uint32_t)__ffsll((unsigned long long)above) : 64u;
+#pragma unroll
+  for (uint32_t d = 1; d < 64; d <<= 1) {
+    const uint32_t o = (uint32_t)__shfl_down((int)m, d, kWave);
+    if (lane + d < end) m |= o;
+  }
+  if (head && on) atomicXor(&bitmap[w], m);
+}
+
+// A survivor's reference in this chunk: the smaller wins its key's slot.
+// With keys inline (no survivor id needed) references of later chunks are
+// smaller than any of earlier ones (ref_gen counts down above bit 28), so
+// they need no reset once the chunk is over.
+constexpr int kRefBits = 28;
+static_assert(kMaxChunk <= (1ull << kRefBits), "chunk-relative indices fit a reference");
+template <bool kInl>
+__device__ __forceinline__ uint64_t chunk_ref(const ChunkArgs& a, uint32_t e, uint32_t sid) {
+  return kInl ? (a.ref_gen << kRefBits) | e : new_ref(e, sid);
+}
+
+// Insertion, and the winners' bits: a survivor that takes its slot toggles
+// its bit on, one that is displaced has its bit toggled off by the displacing
+// survivor.  Toggles commute, so each winner's bit ends up set and every
+// other clear, whatever the order.  (A pass of its own that read each slot
+// again cost 64 us per 16.7 M-candidate chunk of one-word languages beside
+// 105 us for the insertion.)
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void insert_survivors(ChunkArgs a) {
   if (a.st->stop) return;
-  // the winner bitmap of the grid finalize path starts empty
   for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < a.clear_words; w += gridDim.x * blockDim.x)
-    a.bitmap[w] = 0;
-  for_survivors(a, [&](uint32_t sid) {
-    uint64_t key[W];
-    load_row<W>(a.skey, sid, true, key);
-    const uint64_t h = a.spos[sid];
-    const uint64_t pos = table_insert<W, kInl>(a.slots, a.sref, a.slot_mask, a.rows, a.skey, key, h,
-                                               new_ref(a.se[sid], sid));
-    a.spos[sid] = spos_pack(pos, h);
+    a.bitmap_next[w] = 0;
+  for_survivors(a, [&](uint32_t sid, bool have) {
+    uint32_t e = 0;
+    bool won = false;
+    if (have) {
+      uint64_t key[W];
+      load_row<W>(a.skey, sid, true, key);
+      const uint64_t h = a.spos[sid];
+      e = a.se[sid];
+      const uint64_t mine = chunk_ref<kInl>(a, e, sid);
+      uint64_t old;
+      const uint64_t pos = table_insert<W, kInl>(a.slots, a.slot_mask, a.rows, a.skey, key, h, mine, &old);
+      if constexpr (!kInl) a.spos[sid] = spos_pack(pos, h);
+      won = mine < old;  // else an earlier candidate has it
+      // displaced: another survivor of this chunk (EMPTY and, inline, earlier
+      // chunks' references are not)
+      uint32_t oe;
+      bool displaced;
+      if constexpr (kInl) {
+        displaced = won && (old >> kRefBits) == a.ref_gen;
+        oe = (uint32_t)(old & ((1ull << kRefBits) - 1));
+      } else {
+        displaced = won && old != kEmpty;
+        oe = (uint32_t)(old >> 32) & 0x7FFFFFFFu;
+      }
+      if (displaced) atomicXor(&a.bitmap[oe >> 5], 1u << (oe & 31));
+    }
+    toggle_bits(a.bitmap, e, won);
   });
 }
 
@@ -790,21 +850,21 @@ __device__ void account_chunk(const ChunkArgs& a, uint32_t ans, uint32_t answer_
 template <int W, bool kInl>
 __device__ __forceinline__ void store_winner(const ChunkArgs& a, uint32_t sid, uint32_t e, uint64_t row) {
   uint64_t key[W];
-#pragma unroll
-  for (int k = 0; k < W; ++k) key[k] = a.skey[(uint64_t)sid * W + k];
-  const uint64_t rec = a.spos[sid];
+  load_row<W>(a.skey, sid, true, key);
+  uint64_t rec = 0;
+  if constexpr (!kInl) rec = a.spos[sid];
 #pragma unroll
   for (int k = 0; k < W; ++k) a.rows_w[row * W + k] = key[k];
   a.aux[row] = a.chunk_e0 + e;
-  table_publish<kInl>(a.slots, a.sref, rec, row);
+  if constexpr (!kInl) table_publish<kInl>(a.slots, rec, row);
 }
 
 constexpr uint32_t kSmallWords = (uint32_t)(kSmallChunk / 32);
 constexpr uint64_t kSmallCopyWords = 1ull << 16;
 static_assert(kSmallChunk <= 0xFFFFu, "survivor ranks of a small chunk fit 16 bits");
 
-// Whole finalization of a small chunk in one workgroup: winner bitmap in LDS,
-// its prefix scan, ordered append, accounting.
+// Whole finalization of a small chunk in one workgroup: winner bitmap copied
+// to LDS, its prefix scan, ordered append, accounting.
 template <int W, bool kInl>
 __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
   __shared__ uint32_t bm[kSmallWords];
@@ -816,26 +876,11 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
   const uint32_t t = threadIdx.x;
   const uint32_t ns = a.ctrl->n_surv, ans = a.ctrl->answer_e;
   const uint32_t words = (uint32_t)((a.len + 31) / 32);
-  for (uint32_t i = t; i < words; i += 1024) bm[i] = 0;
+  for (uint32_t i = t; i < words; i += 1024) bm[i] = a.bitmap[i];
   if (t == 0) {
     s_rank = ~0u;
     s_over = ~0u;
   }
-  __syncthreads();
-  // four survivors per thread and round, their reads issued together
-  auto mark = [&](uint32_t sid, uint32_t e, uint64_t pos) {
-    if (table_is_winner<kInl>(a.slots, a.sref, pos, new_ref(e, sid))) atomicOr(&bm[e >> 5], 1u << (e & 31));
-  };
-  uint32_t sid = t;
-  for (; sid + 3 * 1024 < ns; sid += 4 * 1024) {
-    const uint32_t e0 = a.se[sid], e1 = a.se[sid + 1024], e2 = a.se[sid + 2048], e3 = a.se[sid + 3072];
-    const uint64_t p0 = a.spos[sid], p1 = a.spos[sid + 1024], p2 = a.spos[sid + 2048], p3 = a.spos[sid + 3072];
-    mark(sid, e0, p0);
-    mark(sid + 1024, e1, p1);
-    mark(sid + 2048, e2, p2);
-    mark(sid + 3072, e3, p3);
-  }
-  for (; sid < ns; sid += 1024) mark(sid, a.se[sid], a.spos[sid]);
   __syncthreads();
   if (t < 64) {
     const uint32_t tot = wave_popc_scan<kSmallWords / 64>(bm, pre, words);
@@ -858,7 +903,8 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
     return kNotStored;
   };
   if constexpr (W <= 2) {
-    sid = t;
+    // four survivors per thread and round, their reads issued together
+    uint32_t sid = t;
     for (; sid + 3 * 1024 < ns; sid += 4 * 1024) {
       const uint32_t e0 = a.se[sid], e1 = a.se[sid + 1024], e2 = a.se[sid + 2048], e3 = a.se[sid + 3072];
       const uint32_t r0 = place(sid, e0), r1 = place(sid + 1024, e1), r2 = place(sid + 2048, e2),
@@ -876,7 +922,7 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
   } else {
     // wide rows: ranks first, then W consecutive lanes copy one row, so
     // that each wave reads and writes whole rows (coalesced)
-    sid = t;
+    uint32_t sid = t;
     for (; sid + 3 * 1024 < ns; sid += 4 * 1024) {
       const uint32_t e0 = a.se[sid], e1 = a.se[sid + 1024], e2 = a.se[sid + 2048], e3 = a.se[sid + 3072];
       dst[sid] = (uint16_t)place(sid, e0);
@@ -895,7 +941,7 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
       a.rows_w[row * W + k] = a.skey[(uint64_t)q * W + k];
       if (k == 0) {
         a.aux[row] = a.chunk_e0 + a.se[q];
-        table_publish<kInl>(a.slots, a.sref, a.spos[q], row);
+        table_publish<kInl>(a.slots, a.spos[q], row);
       }
     }
   }
@@ -904,16 +950,6 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
 }
 
 // ---- grid path for large chunks ----
-
-template <bool kInl>
-__global__ __launch_bounds__(256) void mark_winners(ChunkArgs a) {
-  if (a.st->stop) return;
-  for_survivors(a, [&](uint32_t sid) {
-    const uint32_t e = a.se[sid];
-    if (table_is_winner<kInl>(a.slots, a.sref, a.spos[sid], new_ref(e, sid)))
-      atomicOr(&a.bitmap[e >> 5], 1u << (e & 31));
-  });
-}
 
 constexpr uint32_t kScanBlock = 1024;  // bitmap words per scan block (256 threads x 4)
 
@@ -1024,7 +1060,8 @@ __global__ __launch_bounds__(256) void compact_winners(ChunkArgs a) {
   const uint32_t ans = a.ctrl->answer_e;
   const uint64_t row_base = a.st->total_rows;
   const uint64_t room = a.st->row_cap > row_base ? a.st->row_cap - row_base : 0;
-  for_survivors(a, [&](uint32_t sid) {
+  for_survivors(a, [&](uint32_t sid, bool have) {
+    if (!have) return;
     const uint32_t e = a.se[sid];
     const uint32_t word = a.bitmap[e >> 5];
     const uint32_t bit = 1u << (e & 31);
@@ -1129,8 +1166,12 @@ hipError_t launch_fill(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_state_reset(Ctrl* c, DevState* st, uint64_t row_cap, bool otf_on, hipStream_t s) {
-  hipLaunchKernelGGL(state_reset, dim3(1), dim3(1), 0, s, c, st, row_cap, otf_on ? 1u : 0u);
+hipError_t launch_search_reset(const ResetArgs& a, hipStream_t s) {
+  if (!a.ctrl || !a.st || (a.n_levels && !a.levels) || (a.n_slot_words && !a.slots)) return hipErrorInvalidValue;
+  for (int b = 0; b < 2; ++b)
+    if (a.bitmap_words[b] && !a.bitmap[b]) return hipErrorInvalidValue;
+  const uint64_t most = std::max<uint64_t>({a.n_levels, a.n_slot_words, a.bitmap_words[0], a.bitmap_words[1], 1});
+  hipLaunchKernelGGL(search_reset, dim3(grid_for(most, 1024, 65536)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1225,7 +1266,7 @@ hipError_t plan_union_set(UnionSet* us, SlotPlan* sp) {
 }
 
 hipError_t launch_gen(int W, int op, const GenArgs& a, hipStream_t s) {
-  if (a.e1 <= a.e0 || a.per_wave == 0) return hipErrorInvalidValue;
+  if (a.e1 <= a.e0 || a.per_wave == 0 || !a.reg) return hipErrorInvalidValue;
   REI_DISPATCH_WI(W, a.inl, return (launch_gen_w<kW, kI>(op, a, s)));
   return hipGetLastError();
 }
@@ -1297,6 +1338,7 @@ uint32_t survivor_grid(const ChunkArgs& a) {
 }
 
 hipError_t launch_insert(int W, const ChunkArgs& a, hipStream_t s) {
+  if (!a.bitmap || (a.clear_words && !a.bitmap_next) || (a.n_reg && !a.reg)) return hipErrorInvalidValue;
   REI_DISPATCH_WI(W, a.inl, hipLaunchKernelGGL((insert_survivors<kW, kI>), dim3(survivor_grid(a)), dim3(256), 0, s,
                                                a));
   return hipGetLastError();
@@ -1314,13 +1356,7 @@ hipError_t launch_finalize(int W, const ChunkArgs& a, hipStream_t s) {
     REI_DISPATCH_WI(W, a.inl, hipLaunchKernelGGL((finalize_small<kW, kI>), dim3(1), dim3(1024), 0, s, a));
     return hipGetLastError();
   }
-  // the bitmap was cleared by insert_survivors
-  if (a.clear_words != a.n_bitmap_words) return hipErrorInvalidValue;
   const uint32_t g = survivor_grid(a);
-  if (a.inl)
-    hipLaunchKernelGGL(mark_winners<true>, dim3(g), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(mark_winners<false>, dim3(g), dim3(256), 0, s, a);
   if (a.n_bitmap_words <= kScanSingleWords) {
     hipLaunchKernelGGL(scan_single, dim3(1), dim3(1024), 0, s, a);
   } else {
