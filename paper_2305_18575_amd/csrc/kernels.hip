@@ -729,9 +729,12 @@ __device__ __forceinline__ uint64_t chunk_ref(const ChunkArgs& a, uint32_t e, ui
 // Insertion, and the winners' bits: a survivor that takes its slot toggles
 // its bit on, one that is displaced has its bit toggled off by the displacing
 // survivor.  Toggles commute, so each winner's bit ends up set and every
-// other clear, whatever the order.  (A pass of its own that read each slot
-// again cost 64 us per 16.7 M-candidate chunk of one-word languages beside
-// 105 us for the insertion.)
+// other clear, whatever the order.  Bound by the table's random atomics
+// (probe and atomicMin reach 14-16 G/s on this card).  One-word languages,
+// 58 infixes, per chunk of up to 16.7 M candidates: 121 us with a marking
+// pass of 75 us that read each slot again, and 48 us for the ordered append,
+// which reset the reference beside each key; now 122 us, none, and 20 us.
+// (One toggle per lane instead of one per run of lanes: 166 us.)
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void insert_survivors(ChunkArgs a) {
   if (a.st->stop) return;
