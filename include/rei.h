@@ -435,9 +435,12 @@ rei_status rei_set_profiling(rei_instance *inst, int enable);
  * untouched by events.  Clears the statistics; rei_set_profiling(inst, 0)
  * turns it off. */
 rei_status rei_set_profiling_class(rei_instance *inst, rei_kernel_class k);
-/* Launch count, total device milliseconds and work units (candidates for the
- * generator classes, survivors for REI_K_INSERT) of one kernel class,
- * accumulated over the solves since profiling was enabled. */
+/* Launch count, total device milliseconds and work units (candidates built for
+ * the generator classes, survivors for REI_K_INSERT) of one kernel class,
+ * accumulated over the solves since profiling was enabled.  Candidates that
+ * need no generation, because an algebraic identity makes them equal to an
+ * earlier one, are counted under REI_K_GEN_CHAR, which launches nothing for
+ * them. */
 rei_status rei_kernel_stats(const rei_instance *inst, rei_kernel_class k, uint64_t *launches,
                             double *ms, uint64_t *units);
 /* Testing: keep only the low `bits` bits of every language hash (0 = all 64)

@@ -44,6 +44,20 @@ struct Block {
   bool same;         // union of a level with itself (pairs x before y)
 };
 
+// Where a stored level's rows change constructor: rows [0, q0) characters,
+// [q0, s0) r?, [s0, k0) r*, [k0, u0) concatenations, [u0, ...) unions, those
+// by the left operand's cost (ascending; with the level index of the block's
+// first candidate).
+struct LevelMarks {
+  bool have = false;
+  uint64_t q0 = 0, s0 = 0, k0 = 0, u0 = 0;
+  struct U {
+    uint32_t left_cost;
+    uint64_t row, e;
+  };
+  std::vector<U> u;
+};
+
 // The launches of one chunk, as planned (kept between chunks for its storage).
 struct ChunkLaunches {
   std::vector<std::pair<int, GenArgs>> singles;  // constructor, arguments
@@ -167,6 +181,13 @@ struct rei_instance {
 
   // levels, indexed by cost
   std::vector<uint64_t> lstart, lcount;
+  // constructor boundaries of the stored levels, as far as they were asked
+  // for, and the pinned buffer the device writes them to (kMaxMarks, then the
+  // number of the last launch that is done)
+  std::vector<LevelMarks> marks;
+  uint64_t* h_marks = nullptr;
+  uint64_t* v_marks = nullptr;
+  uint32_t marks_seq = 0;
   // host copy of the back-pointers for printing (filled on first use)
   std::vector<uint64_t> h_aux;
   bool h_aux_valid = false;
@@ -515,7 +536,8 @@ rei_status sync_state(rei_instance* in, hipStream_t s, bool drain) {
   return REI_OK;
 }
 
-// Enqueues one chunk (no host synchronisation unless a buffer may have to
+// Enqueues one chunk, level indices [chunk_e0, chunk_e0 + len), of which the
+// pieces are generated (no host synchronisation unless a buffer may have to
 // grow: then the stream is drained first and the buffer grown for the worst
 // case of this chunk).
 // A piece of a chunk: candidates [e0, e1) of one block, whose first
@@ -524,18 +546,198 @@ rei_status sync_state(rei_instance* in, hipStream_t s, bool drain) {
 struct Piece {
   Block b;
   uint64_t e_base, e0, e1;
+  bool pruned;  // a union whose operand rows are left out by the levels' marks
 };
 
+// ---- candidates that need no generation ------------------------------------
+// Some candidates equal a candidate that comes earlier in (cost, enumeration
+// index) whatever the languages are, because the constructors' costs add up:
+//   (p.q).y   = p.(q.y): the language q.y is stored at its cost or below, and
+//               p costs less than p.q, so p.(q.y) comes at a lower cost or in
+//               an earlier block: left operands that are concatenations;
+//   (p+q)+r   = p+(q+r) likewise: left operands that are unions;
+//   l+(p+q)   = p+(l+q), earlier if p lies before l: right operands that are
+//               unions of a row p at or before l;
+//   p?+r      = (p+r)?, in an earlier block: operands that are r?;
+//   (p?)* = (p*)* = p*, (p?)? = p?, (p*)? = p*.
+// (q+r or q.y may be stored at a lower cost; the equal candidate then has a
+// lower cost too, or is a stored row.)  By induction the first candidate of
+// every language is none of these, so leaving them out changes no winner, no
+// answer and no count: they are counted as enumerated.  It needs every lower
+// level complete (not in OnTheFly mode).  About half of a deep level's
+// candidates go (one-word searches of 0.1-4 G candidates: 45-55 %).
+//
+// Rows of a level lie in enumeration order, so its rows of one constructor
+// are a range, found by level_marks.
+
+// Levels of at least this many candidates leave such candidates out; smaller
+// ones are a few waves' work either way, and the ranges cost a launch.
+constexpr uint64_t kPruneMin = 1ull << 15;
+constexpr uint64_t kSplitMin = 1ull << 11;  // and blocks of at least this many
+
+// Enqueues the search for the marks of levels [lo, hi) (stored, or enqueued
+// on s before); false when they are more than one launch takes.
+rei_status marks_launch(rei_instance* in, hipStream_t s, const std::vector<uint32_t>& levels,
+                        std::vector<LevelMarks>* plan, uint32_t* n_out) {
+  MarksArgs a{};
+  *n_out = 0;
+  if (!in->h_marks) {
+    HIP_OK(in, hipHostMalloc((void**)&in->h_marks, (kMaxMarks + 1) * 8,
+                             hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent));
+    HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_marks, in->h_marks, 0));
+    in->h_marks[kMaxMarks] = 0;
+    in->marks_seq = 0;
+  }
+  std::vector<Block> blocks;
+  plan->clear();
+  for (uint32_t c : levels) {
+    LevelMarks m;
+    if (!make_blocks(in, c, &blocks)) return REI_OK;
+    uint64_t e = 0, eq = 0, es = 0, ek = 0, eu = 0;
+    for (const Block& b : blocks) {
+      if (b.op == OP_UNION) m.u.push_back({b.L, 0, e});
+      e += b.count;
+      if (b.op == OP_CHAR) eq = e;
+      if (b.op <= OP_QUESTION) es = e;
+      if (b.op <= OP_STAR) ek = e;
+      if (b.op <= OP_CONCAT) eu = e;
+    }
+    // blocks come in constructor order: an absent one starts where the next does
+    es = std::max(es, eq);
+    ek = std::max(ek, es);
+    eu = std::max(eu, ek);
+    if (a.n + 4 + m.u.size() > kMaxMarks) return REI_OK;
+    for (uint64_t thr : {eq, es, ek, eu}) a.m[a.n++] = {thr, in->lstart[c], c, 0};
+    for (const LevelMarks::U& u : m.u) a.m[a.n++] = {u.e, in->lstart[c], c, 0};
+    plan->push_back(m);
+  }
+  a.aux = in->d_aux;
+  a.levels = in->d_levels;
+  a.out = in->v_marks;
+  a.seq_out = (uint32_t*)(in->v_marks + kMaxMarks);
+  a.seq = ++in->marks_seq;
+  LAUNCH(in, s, REI_K_OTHER, a.n, launch_level_marks(a, s));
+  *n_out = a.n;
+  return REI_OK;
+}
+
+// Waits for the last marks_launch and keeps its results.
+rei_status marks_take(rei_instance* in, hipStream_t s, const std::vector<uint32_t>& levels,
+                      const std::vector<LevelMarks>& plan) {
+  const double t0 = now_s();
+  const uint32_t* seq = (const uint32_t*)(in->h_marks + kMaxMarks);
+  while (__atomic_load_n(seq, __ATOMIC_ACQUIRE) != in->marks_seq)
+    if ((now_s() - t0) * 1e6 > kSpinUs) {
+      HIP_OK(in, hipStreamSynchronize(s));
+      break;
+    }
+  uint32_t k = 0;
+  for (size_t q = 0; q < levels.size(); ++q) {
+    LevelMarks m = plan[q];
+    m.q0 = in->h_marks[k++];
+    m.s0 = in->h_marks[k++];
+    m.k0 = in->h_marks[k++];
+    m.u0 = in->h_marks[k++];
+    for (LevelMarks::U& u : m.u) u.row = in->h_marks[k++];
+    m.have = true;
+    in->marks[levels[q]] = m;
+  }
+  return REI_OK;
+}
+
+// Marks of every stored level below c that has none yet.
+rei_status marks_below(rei_instance* in, hipStream_t s, uint32_t c) {
+  std::vector<uint32_t> todo;
+  std::vector<LevelMarks> plan;
+  auto flush = [&]() -> rei_status {
+    uint32_t n = 0;
+    rei_status r;
+    if (todo.empty()) return REI_OK;
+    if ((r = marks_launch(in, s, todo, &plan, &n)) != REI_OK) return r;
+    if (n && (r = marks_take(in, s, todo, plan)) != REI_OK) return r;
+    todo.clear();
+    return REI_OK;
+  };
+  rei_status r;
+  uint32_t entries = 0;
+  for (uint32_t k = in->costs.c_char; k < c; ++k) {
+    if (in->marks[k].have || in->lcount[k] == 0) continue;
+    const uint32_t most = 4 + k / 2 + 1;  // unions: one block per left cost, at most half the level's cost
+    if (most > kMaxMarks) continue;
+    if (entries + most > kMaxMarks) {
+      if ((r = flush()) != REI_OK) return r;
+      entries = 0;
+    }
+    todo.push_back(k);
+    entries += most;
+  }
+  return flush();
+}
+
+// The candidates of a block that have to be generated, as ranges of its
+// candidates (unions: their left operand's share of the rule).
+void ranges_left(const rei_instance* in, const Block& b, std::vector<std::pair<uint64_t, uint64_t>>* out) {
+  out->clear();
+  const LevelMarks* m = b.op == OP_CHAR ? nullptr : &in->marks[b.L];
+  if (!m || !m->have || (b.op == OP_UNION && b.same)) {
+    out->push_back({0, b.count});
+    return;
+  }
+  const uint64_t n = in->lcount[b.L];
+  const uint64_t width = b.op == OP_CONCAT || b.op == OP_UNION ? in->lcount[b.R] : 1;
+  auto add = [&](uint64_t lo, uint64_t hi) {
+    if (lo >= hi) return;
+    if (!out->empty() && out->back().second == lo * width)
+      out->back().second = hi * width;
+    else
+      out->push_back({lo * width, hi * width});
+  };
+  if (b.op == OP_CONCAT) {
+    add(0, m->k0);
+    add(m->u0, n);
+  } else if (b.op == OP_UNION) {
+    add(0, m->q0);
+    add(m->s0, m->u0);
+  } else {  // r?, r* of rows that are neither
+    add(0, m->q0);
+    add(m->k0, n);
+  }
+}
+
+// The right operand's share of the rule for a union block.
+void union_columns(const rei_instance* in, const Block& b, bool pruned, UnionPart* p) {
+  const uint64_t n = in->lcount[b.R];
+  p->n0 = p->s0 = p->us = p->ue = n;
+  p->n1 = 0;
+  p->eq_base = p->eq_n = 0;
+  p->eq_tri = 0;
+  const LevelMarks& m = in->marks[b.R];
+  if (!pruned || !m.have) return;
+  p->n0 = m.q0;
+  p->s0 = m.s0;
+  p->n1 = m.u0 - m.s0;
+  if (b.same) return;  // a union row's left operand costs less than it
+  for (const LevelMarks::U& u : m.u) {
+    if (u.left_cost < b.L) continue;
+    p->us = std::min(p->us, u.row);
+    if (u.left_cost == b.L) {
+      const uint64_t rc = b.R - in->costs.c_union - b.L;  // that block's right operand level
+      p->eq_base = u.e;
+      p->eq_tri = rc == b.L ? 1u : 0u;
+      p->eq_n = in->lcount[rc];
+    } else {
+      p->ue = u.row;
+      break;
+    }
+  }
+  if (!p->eq_n) p->ue = p->us;
+}
+
 rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std::vector<Piece>& pieces,
-                         bool* stopped) {
+                         uint64_t chunk_e0, uint64_t len, bool* stopped) {
   const int W = in->st.W;
-  uint64_t len = 0;
-  for (const Piece& p : pieces) len += p.e1 - p.e0;
-  const uint64_t chunk_e0 = pieces[0].e_base + pieces[0].e0;
   const uint64_t words = (len + 31) / 32;
   rei_status r;
-  auto worst_rows = [&] { return std::min(in->row_cap, in->known_rows + in->pending + len); };
-  auto worst_entries = [&] { return in->known_rows + in->pending + len; };
   // The chunk's launches.  Small pieces (W <= kPiecesMaxW) share gen_pieces
   // launches of up to kMaxPieces pieces; large concatenation and union blocks
   // share launches of up to kMaxConcatParts and kMaxUnionParts blocks; other
@@ -621,6 +823,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       up.e1 = p.e1;
       up.rel0 = rel0;
       up.same = b.same ? 1u : 0u;
+      union_columns(in, b, p.pruned, &up);
     } else {
       GenArgs q = g;
       q.e0 = p.e0;
@@ -642,6 +845,16 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   for (auto& x : cl.concats) HIP_OK(in, plan_concat_set(W, g, &x, &sp));
   for (auto& x : cl.unions) HIP_OK(in, plan_union_set(&x, &sp));
 
+  uint64_t generated = 0;  // candidates the launches build: the rest of len needs none
+  for (const auto& x : cl.singles) generated += x.second.e1 - x.second.e0;
+  for (const PieceArgs& x : cl.pieces) generated += x.items_cand;
+  for (const ConcatSet& x : cl.concats)
+    for (uint32_t k = 0; k < x.n; ++k) generated += x.p[k].e1 - x.p[k].e0;
+  for (const UnionSet& x : cl.unions)
+    for (uint32_t k = 0; k < x.n; ++k) generated += x.p[k].lanes;
+  auto worst_rows = [&] { return std::min(in->row_cap, in->known_rows + in->pending + generated); };
+  auto worst_entries = [&] { return in->known_rows + in->pending + generated; };
+
   // a level enumerated in OnTheFly mode stores nothing: no buffer grows but
   // the ranges' (written, empty, by every generator wave)
   const bool otf_level = in->otf_level != 0;
@@ -657,13 +870,14 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions, s)) != REI_OK) return r;
     } else {
       if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s)) != REI_OK) return r;
-      if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + len), s)) != REI_OK) return r;
-      if ((r = ensure_table(in, in->known_rows + len, s, false)) != REI_OK) return r;
+      if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + generated), s)) != REI_OK) return r;
+      if ((r = ensure_table(in, in->known_rows + generated, s, false)) != REI_OK) return r;
     }
   }
 
   auto set_buffers = [&](GenArgs& q) {
     q.rows = in->d_rows;
+    q.aux = in->d_aux;
     q.slots = in->d_slots;
     q.slot_mask = in->slots_cap - 1;
     q.skey = in->d_skey;
@@ -695,9 +909,13 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   }
   for (const UnionSet& x : cl.unions) {
     uint64_t cand = 0;
-    for (uint32_t k = 0; k < x.n; ++k) cand += x.p[k].e1 - x.p[k].e0;
+    for (uint32_t k = 0; k < x.n; ++k) cand += x.p[k].lanes;
     LAUNCH(in, s, REI_K_GEN_UNION, cand, launch_union_set(W, g, x, s));
   }
+
+  // candidates left out, in the statistics of a class that launches nothing
+  // for them
+  if (profiled(in, REI_K_GEN_CHAR) && len > generated) in->st_units[REI_K_GEN_CHAR] += len - generated;
 
   ChunkArgs ca{};
   ca.rows = in->d_rows;
@@ -731,7 +949,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   ca.hst = in->v_state;
   ca.hlev = in->v_levels;
   ca.nlev = L;
-  if (otf_level) {
+  if (otf_level || generated == 0) {  // nothing to store
     LAUNCH(in, s, REI_K_COMPACT, len, launch_account(ca, s));
     ++in->chunks_enq;
     return REI_OK;
@@ -744,7 +962,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   LAUNCH(in, s, REI_K_INSERT, len, launch_insert(W, ca, s));
   LAUNCH(in, s, REI_K_COMPACT, len, launch_finalize(W, ca, s));
   ++in->chunks_enq;
-  in->pending += len;
+  in->pending += generated;
   return REI_OK;
 }
 
@@ -1029,6 +1247,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
   in->tree.clear();
   std::fill(in->lstart.begin(), in->lstart.end(), 0);
   std::fill(in->lcount.begin(), in->lcount.end(), 0);
+  in->marks.assign(in->lcount.size(), LevelMarks{});
   const uint32_t c_from = in->resume_level;
   in->resume_level = 0;
   in->otf_level = 0;
@@ -1113,20 +1332,34 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     // level: an answer early in a large level ends it after a few small
     // chunks (later chunks see the stop flag and exit at once), while a level
     // without one costs a handful of extra launches.
-    uint64_t e_base = 0, acc = 0;
+    uint64_t e_base = 0, acc = 0, level_total = 0;
+    for (const Block& b : blocks)
+      if (__builtin_add_overflow(level_total, b.count, &level_total)) level_total = ~0ull;
+    const bool prune = level_total >= kPruneMin && !in->otf_level;
+    if (prune && (r = marks_below(in, s, c)) != REI_OK) return r;
     const GridTune gt = grid_params(in);
     const uint64_t cmax = std::max<uint64_t>(1, std::min(in->chunk_max, gt.chunk_max));
     uint64_t cur = std::min(cmax, gt.first_chunk);
     std::vector<Piece> pieces;
+    std::vector<std::pair<uint64_t, uint64_t>> left;
+    uint64_t chunk_e0 = 0;
     for (const Block& b : blocks) {
+      const bool split = prune && b.count >= kSplitMin;
+      if (split)
+        ranges_left(in, b, &left);
+      else
+        left.assign(1, {0, b.count});
       for (uint64_t e0 = 0; e0 < b.count && !stopped;) {
         const uint64_t e1 = std::min(b.count, e0 + (cur - acc));
-        pieces.push_back({b, e_base, e0, e1});
+        for (const auto& x : left)
+          if (std::max(x.first, e0) < std::min(x.second, e1))
+            pieces.push_back({b, e_base, std::max(x.first, e0), std::min(x.second, e1), split});
         acc += e1 - e0;
         e0 = e1;
         if (acc == cur) {
-          if ((r = enqueue_chunk(in, s, c, pieces, &stopped)) != REI_OK) return r;
+          if ((r = enqueue_chunk(in, s, c, pieces, chunk_e0, acc, &stopped)) != REI_OK) return r;
           pieces.clear();
+          chunk_e0 += acc;
           acc = 0;
           cur = std::min(cmax, 2 * cur);
         }
@@ -1134,7 +1367,14 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
       if (stopped) break;
       e_base += b.count;
     }
-    if (!stopped && !pieces.empty() && (r = enqueue_chunk(in, s, c, pieces, &stopped)) != REI_OK) return r;
+    if (!stopped && acc && (r = enqueue_chunk(in, s, c, pieces, chunk_e0, acc, &stopped)) != REI_OK) return r;
+    // this level's own marks, for the levels above it (taken below, once its
+    // size is known)
+    std::vector<uint32_t> own(1, c);
+    std::vector<LevelMarks> plan;
+    uint32_t own_marks = 0;
+    if (prune && !stopped && 4 + c / 2 + 1 <= kMaxMarks && (r = marks_launch(in, s, own, &plan, &own_marks)) != REI_OK)
+      return r;
     // level boundary: the next level's blocks depend on this level's size
     if ((r = sync_state(in, s, false)) != REI_OK) return r;
     in->lcount[c] = in->h_levels[c];
@@ -1144,6 +1384,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
       stopped = true;
     }
     if (in->h_state->otf && !in->otf_level) in->otf_level = c;
+    if (own_marks && !stopped && !in->otf_level && (r = marks_take(in, s, own, plan)) != REI_OK) return r;
   }
   // a stopped search's last wait was on the stream; one that ran out of
   // levels last waited on the mirrors: its launches end before the caller
@@ -1722,9 +1963,11 @@ void free_device(rei_instance* in) {
   if (in->h_state) (void)hipHostFree(in->h_state);
   if (in->h_levels) (void)hipHostFree(in->h_levels);
   if (in->h_tree) (void)hipHostFree(in->h_tree);
+  if (in->h_marks) (void)hipHostFree(in->h_marks);
   in->h_state = nullptr;
   in->h_levels = nullptr;
   in->h_tree = nullptr;
+  in->h_marks = nullptr;
   for (auto& r : in->recs) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);

@@ -85,6 +85,7 @@ struct DevState {
 struct GenArgs {
   // language cache
   const uint64_t* rows;       // all rows, W words each
+  const uint64_t* aux;        // level index of each row
   // dedup table
   const uint64_t* slots;
   uint64_t slot_mask;
@@ -299,14 +300,26 @@ struct ConcatSet {
 hipError_t plan_concat_set(int W, const GenArgs& a, ConcatSet* cs, SlotPlan* sp);
 hipError_t launch_concat_set(int W, const GenArgs& a, const ConcatSet& cs, hipStream_t s);
 
-// Several large union blocks of one chunk in one gen_union launch (one
-// thread per candidate; the launcher gives each part its workgroups).
+// Several large union blocks of one chunk in one gen_union launch (the
+// launcher gives each part its workgroups).
 constexpr int kMaxUnionParts = 16;
+// A part's candidates are the pairs (i, j) of the rows that are left of each
+// operand level: left rows as the range [e0, e1) has them, right rows [0, n0),
+// [s0, s0 + n1) and [us, rcount) (one level paired with itself: rows [0, n0)
+// and [s0, s0 + n1), i before j).  A pair whose right row j in [us, ue) is the
+// union of a row p of the left level, p <= i, is left out too: j's stored
+// index in its level, less eq_base, is below the one of the first union with
+// left row i + 1 (pairs of eq_n rows if eq_tri, else eq_n right rows per left
+// row).  Whole levels: n0 = rcount, n1 = 0, s0 = us = ue = rcount.
 struct UnionPart {
   uint64_t lstart, lcount, rstart, rcount;  // operand levels: first row, number of rows
   uint64_t e0, e1;                          // block-local candidate range
+  uint64_t n0, s0, n1, us, ue;
+  uint64_t eq_base, eq_n;
+  uint64_t k0, lanes;                       // first pair and number of pairs (launcher)
   uint32_t rel0;                            // chunk-relative index of candidate e0
   uint32_t same;                            // both operands from one level: pairs x < y
+  uint32_t eq_tri;
   uint32_t wg0, slot0, reg0;                // first workgroup, survivor slot and range (launcher)
 };
 struct UnionSet {
@@ -315,6 +328,24 @@ struct UnionSet {
 };
 hipError_t plan_union_set(UnionSet* us, SlotPlan* sp);
 hipError_t launch_union_set(int W, const GenArgs& a, const UnionSet& us, hipStream_t s);
+
+// Rows of stored levels by the constructor block they came from: rows of a
+// level lie in enumeration order, so the block that starts at level index thr
+// starts at row lower_bound(aux[level], thr).  One thread per threshold;
+// then *seq_out = seq (host-visible, after the results).
+constexpr uint32_t kMaxMarks = 128;
+struct MarksArgs {
+  const uint64_t* aux;
+  const uint64_t* levels;  // stored rows per cost level (device)
+  uint64_t* out;           // host-visible, kMaxMarks
+  uint32_t* seq_out;
+  uint32_t seq, n;
+  struct Entry {
+    uint64_t thr, lstart;
+    uint32_t level, pad;
+  } m[kMaxMarks];
+};
+hipError_t launch_level_marks(const MarksArgs& a, hipStream_t s);
 
 // ---- batched solver: one workgroup runs the whole search of one instance --
 constexpr uint32_t kBatchChunk = 8192;   // candidates per chunk

@@ -321,9 +321,16 @@ __global__ __launch_bounds__(256) void gen_concat(GenArgs a, ConcatSet cs) {
     concat_part<W, kShort, kInl, kGtLds, false>(a, cp, blockIdx.x - cp.wg0, lds);
 }
 
-// One lane per candidate x + y, us.per_wave * 64 consecutive candidates per
-// wave; several union blocks of a chunk share a launch (UnionSet), each
-// workgroup in one block.
+// Row of a level from its position among the rows that are left (UnionPart).
+__device__ __forceinline__ uint64_t kept_row(const UnionPart& p, uint64_t c) {
+  if (c < p.n0) return c;
+  c -= p.n0;
+  return c < p.n1 ? p.s0 + c : p.us + (c - p.n1);
+}
+
+// One lane per pair x + y of the rows left (UnionPart), us.per_wave * 64
+// consecutive ones per wave; several union blocks of a chunk share a launch,
+// each workgroup in one block.
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void gen_union(GenArgs a, UnionSet us) {
   if (a.st->stop) return;
@@ -332,28 +339,50 @@ __global__ __launch_bounds__(256) void gen_union(GenArgs a, UnionSet us) {
   const UnionPart& up = us.p[part];
   const uint32_t wave = (blockIdx.x - up.wg0) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   Region rg{up.slot0 + wave * us.per_wave * 64, 0};
-  const uint64_t w0 = up.e0 + (uint64_t)wave * us.per_wave * 64;
-  for (uint32_t it = 0; it < us.per_wave && w0 + 64 * it < up.e1; ++it) {
-    const uint64_t e = w0 + 64 * it + lane;
-    const bool valid = e < up.e1;
-    uint64_t i = 0, j = 0;
+  const uint64_t w0 = (uint64_t)wave * us.per_wave * 64;
+  const uint64_t i0 = up.same ? 0 : up.e0 / up.rcount;          // first left row
+  const uint64_t cols = up.n0 + up.n1 + (up.rcount - up.us);    // right rows left
+  const bool narrow = up.k0 + up.lanes <= 0xFFFFFFFFull && cols <= 0xFFFFFFFFull;
+  for (uint32_t it = 0; it < us.per_wave && w0 + 64 * it < up.lanes; ++it) {
+    const uint64_t q = w0 + 64 * it + lane, k = up.k0 + q;
+    bool valid = q < up.lanes;
+    uint64_t i = 0, j = 0, e = 0;
     if (valid) {
       if (up.same) {
-        tri_decode(e, up.lcount, &i, &j);
+        tri_decode(k, up.n0 + up.n1, &i, &j);
+        i = kept_row(up, i);
+        j = kept_row(up, j);
+        e = i * up.rcount - i * (i + 1) / 2 + (j - i - 1);
       } else {
-        i = e / up.rcount;
-        j = e - i * up.rcount;
+        uint64_t c;
+        if (narrow) {
+          i = (uint32_t)k / (uint32_t)cols;
+          c = (uint32_t)k - (uint32_t)i * (uint32_t)cols;
+        } else {
+          i = k / cols;
+          c = k - i * cols;
+        }
+        i += i0;
+        j = kept_row(up, c);
+        e = i * up.rcount + j;
+        if (j >= up.us && j < up.ue) {
+          const uint64_t r = a.aux[up.rstart + j] - up.eq_base;
+          const uint64_t first = up.eq_tri ? (i + 1) * up.eq_n - (i + 1) * (i + 2) / 2 : (i + 1) * up.eq_n;
+          valid = r >= first;
+        }
       }
+      valid = valid && e >= up.e0 && e < up.e1;
     }
+    if (!__any(valid)) continue;
     uint64_t x[W], y[W], key[W];
     load_row<W>(a.rows, up.lstart + i, valid, x);
     load_row<W>(a.rows, up.rstart + j, valid, y);
     bool eqx = true, eqy = true;
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-      key[k] = x[k] | y[k];
-      eqx = eqx && key[k] == x[k];
-      eqy = eqy && key[k] == y[k];
+    for (int w = 0; w < W; ++w) {
+      key[w] = x[w] | y[w];
+      eqx = eqx && key[w] == x[w];
+      eqy = eqy && key[w] == y[w];
     }
     // x+y equals x or y (one contains the other): that language is stored
     region_emit<W, kInl>(a, rg, valid, eqx || eqy, key, (uint32_t)(e - up.e0) + up.rel0);
@@ -1248,16 +1277,52 @@ hipError_t plan_concat_set(int W, const GenArgs& a, ConcatSet* cs, SlotPlan* sp)
   return hipSuccess;
 }
 
+// Pairs (i, j), i < j, of m rows before row i's first.
+uint64_t pairs_before(uint64_t i, uint64_t m) { return i * m - i * (i + 1) / 2; }
+
+// Pairs of a part's kept rows that come before candidate e of the block.
+uint64_t kept_before(const UnionPart& p, uint64_t e) {
+  // kept rows below row r
+  auto below = [&](uint64_t r) -> uint64_t {
+    uint64_t n = std::min(r, p.n0);
+    if (r > p.s0) n += std::min(r - p.s0, p.n1);
+    if (!p.same && r > p.us) n += r - p.us;
+    return n;
+  };
+  if (!p.same) {
+    const uint64_t cols = p.n0 + p.n1 + (p.rcount - p.us), i = e / p.rcount, i0 = p.e0 / p.rcount;
+    return (i - i0) * cols + below(e - i * p.rcount);
+  }
+  const uint64_t m = p.n0 + p.n1, n = p.rcount;
+  if (e >= pairs_before(n, n)) return m ? pairs_before(m - 1, m) : 0;
+  uint64_t lo = 0, hi = n;  // row of e: the last whose first pair is at or before it
+  while (hi - lo > 1) {
+    const uint64_t mid = lo + (hi - lo) / 2;
+    (pairs_before(mid, n) <= e ? lo : hi) = mid;
+  }
+  const uint64_t i = lo, j = i + 1 + (e - pairs_before(i, n));
+  const uint64_t a = below(i);
+  if (a + 1 >= m) return m ? pairs_before(m - 1, m) : 0;
+  if (below(i + 1) == a) return pairs_before(a, m);  // row i is not kept
+  return pairs_before(a, m) + (std::max(below(j), a + 1) - (a + 1));
+}
+
 hipError_t plan_union_set(UnionSet* us, SlotPlan* sp) {
   if (us->n == 0 || us->n > (uint32_t)kMaxUnionParts) return hipErrorInvalidValue;
   uint64_t total = 0, wgs = 0;
-  for (uint32_t k = 0; k < us->n; ++k) total += us->p[k].e1 - us->p[k].e0;
+  for (uint32_t k = 0; k < us->n; ++k) {
+    UnionPart& p = us->p[k];
+    if (p.e1 <= p.e0 || p.lcount == 0 || p.rcount == 0 || p.n0 + p.n1 > p.rcount || p.us > p.rcount)
+      return hipErrorInvalidValue;
+    p.k0 = kept_before(p, p.e0);
+    p.lanes = kept_before(p, p.e1) - p.k0;
+    total += p.lanes;
+  }
   us->per_wave = iterations_per_wave(total);
   const uint64_t per = 4ull * 64 * us->per_wave;  // candidates per workgroup
   for (uint32_t k = 0; k < us->n; ++k) {
     UnionPart& p = us->p[k];
-    if (p.e1 <= p.e0 || p.lcount == 0 || (!p.same && p.rcount == 0)) return hipErrorInvalidValue;
-    const uint64_t g = (p.e1 - p.e0 + per - 1) / per;
+    const uint64_t g = (p.lanes + per - 1) / per;
     p.wg0 = (uint32_t)wgs;
     p.slot0 = (uint32_t)sp->slots;
     p.reg0 = (uint32_t)sp->regions;
@@ -1275,7 +1340,8 @@ hipError_t launch_gen(int W, int op, const GenArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_union_set(int W, const GenArgs& a, const UnionSet& us, hipStream_t s) {
-  if (!a.rows || !a.st || !a.ctrl || !a.reg || us.wgs == 0) return hipErrorInvalidValue;
+  if (us.wgs == 0) return hipSuccess;  // no pair is left
+  if (!a.rows || !a.aux || !a.st || !a.ctrl || !a.reg) return hipErrorInvalidValue;
   REI_DISPATCH_WI(W, a.inl,
                   launch_timed(gen_union<kW, kI>, dim3(us.wgs), dim3(256), 0, s, a, us));
   return hipGetLastError();
@@ -1375,6 +1441,32 @@ hipError_t launch_finalize(int W, const ChunkArgs& a, hipStream_t s) {
 
 namespace {
 __global__ void noop_kernel() {}
+
+__global__ __launch_bounds__(kMaxMarks) void level_marks(MarksArgs a) {
+  const uint32_t k = threadIdx.x;
+  if (k < a.n) {
+    const MarksArgs::Entry& m = a.m[k];
+    const uint64_t* aux = a.aux + m.lstart;
+    uint64_t lo = 0, hi = a.levels[m.level];
+    while (lo < hi) {
+      const uint64_t mid = lo + (hi - lo) / 2;
+      if (aux[mid] < m.thr)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    a.out[k] = lo;
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (k == 0) __hip_atomic_store(a.seq_out, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+}
+
+hipError_t launch_level_marks(const MarksArgs& a, hipStream_t s) {
+  if (!a.aux || !a.levels || !a.out || !a.seq_out || a.n > kMaxMarks) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(level_marks, dim3(1), dim3(kMaxMarks), 0, s, a);
+  return hipGetLastError();
 }
 
 namespace {

@@ -9,6 +9,8 @@ bitwise: exact agreement.
 """
 import pytest
 
+import oracle
+
 from paper_2305_18575_amd import instances
 from test_gpu_parity import run_both
 
@@ -35,3 +37,36 @@ def test_large_levels_equal_oracle(rei, kind, seed, p, le, sigma, costs, max_cos
     g, _ = run_both(rei, sigma, it.pos, it.neg, costs, max_cost, 4 << 30, max_errors=errors, chunk=chunk,
                     rows=True, row_limit=200)
     print(f"infixes={g.ic_size} words={g.cs_words} status={g.status} candidates={sum(g.candidates)}", flush=True)
+
+
+@pytest.mark.parametrize("kind,seed,p,le,sigma,costs,max_cost,errors,chunk", [SPECS[0], SPECS[2], SPECS[7]])
+def test_large_levels_after_hand_off(rei, kind, seed, p, le, sigma, costs, max_cost, errors, chunk):
+    """The same levels continued on the grid after the one-workgroup solver
+    stored the levels below (its rows' constructors are found from their
+    back-pointers)."""
+    it = instances.type1_instance(seed, p, p, le, sigma=sigma, costs=costs, max_cost=max_cost)
+    h = rei.Instance(sigma, it.pos, it.neg, costs, max_cost, 4 << 30)
+    h.set_batch_level(2000)
+    g = rei.solve_batch([h])[0]
+    o = oracle.Oracle(sigma, it.pos, it.neg, costs, max_cost, 1 << 40, 0, threads=8).solve()
+    assert (g.status, g.cost, g.regex) == (o.status, o.cost, o.regex)
+    for c in range(max_cost + 1):
+        assert (g.unique_at(c), g.candidates_at(c)) == (o.unique[c], o.candidates[c]), c
+    h.close()
+
+
+@pytest.mark.parametrize("char_costs,max_cost", [([1, 2], 17), ([3, 1], 18)])
+def test_large_levels_with_character_costs(rei, char_costs, max_cost):
+    """Characters of different costs: a level may hold characters beside r?,
+    r*, concatenations and unions."""
+    costs = (1, 1, 1, 1, 1)
+    it = instances.type1_instance(11, 9, 9, 5, costs=costs, max_cost=max_cost)
+    h = rei.Instance("01", it.pos, it.neg, costs, max_cost, 4 << 30)
+    h.set_char_costs(char_costs)
+    g = h.solve()
+    o = oracle.solve("01", it.pos, it.neg, costs=costs, max_cost=max_cost, char_costs=char_costs, threads=8)
+    assert (g.status, g.cost, g.regex) == (o.status, o.cost, o.regex)
+    for c in range(max_cost + 1):
+        assert (g.unique_at(c), g.candidates_at(c)) == (o.unique[c], o.candidates[c]), c
+    assert max(g.candidates) > 1 << 16
+    h.close()
