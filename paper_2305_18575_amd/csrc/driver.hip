@@ -841,7 +841,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
     }
   }
   const uint64_t dense_cap = sp.slots;
-  for (auto& x : cl.singles) HIP_OK(in, plan_gen(x.first, &x.second, &sp));
+  for (auto& x : cl.singles) HIP_OK(in, plan_gen(W, x.first, &x.second, &sp));
   for (auto& x : cl.concats) HIP_OK(in, plan_concat_set(W, g, &x, &sp));
   for (auto& x : cl.unions) HIP_OK(in, plan_union_set(&x, &sp));
 

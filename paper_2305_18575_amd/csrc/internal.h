@@ -204,7 +204,7 @@ hipError_t launch_rehash(int W, bool inl, const uint64_t* rows, uint64_t nrows, 
 // The large generators are planned before they are launched: plan_* chooses
 // the launch's shape and takes its slots and ranges from the chunk's plan (so
 // that the buffers can be made large enough), launch_* runs it as planned.
-hipError_t plan_gen(int op, GenArgs* a, SlotPlan* sp);  // CHAR, QUESTION or STAR
+hipError_t plan_gen(int W, int op, GenArgs* a, SlotPlan* sp);  // CHAR, QUESTION or STAR
 hipError_t launch_gen(int W, int op, const GenArgs& a, hipStream_t s);
 hipError_t launch_insert(int W, const ChunkArgs& a, hipStream_t s);
 // Winners, their ranks, the stored rows and the accounting of the chunk:

@@ -163,6 +163,54 @@ __global__ __launch_bounds__(256) void gen_star(GenArgs a) {
   if (wave == 0) region_close(a, a.reg0 + blockIdx.x, rg);
 }
 
+// The same with a wave per group: its own tiles, no workgroup barrier per word
+// length, and the guide table in LDS.  A workgroup per group spends its time
+// in those barriers, each for a handful of words (237 us per launch of one-
+// word languages with 58 infixes; a wave per group: 65 us, of which its probes
+// are most; four words: 58 -> 27 us); taken where the tiles of four waves and
+// the table fit (star_by_wave).
+constexpr uint32_t kStarPairs = 3072;
+constexpr uint32_t kStarMaxLen = 62;
+template <int W, bool kInl>
+__global__ __launch_bounds__(256) void gen_star_wave(GenArgs a) {
+  __shared__ uint64_t tiles[4][2 * 64 * W];
+  __shared__ uint32_t gp[kStarPairs], go[64 * W + 1], lo[kStarMaxLen + 2];
+  if (a.st->stop) return;
+  stage_u32(gp, a.gt_pair, a.n_pairs, threadIdx.x, 256);
+  for (uint32_t i = threadIdx.x; i <= a.n; i += 256) go[i] = a.gt_off[i];
+  for (uint32_t i = threadIdx.x; i < a.max_len + 2; i += 256) lo[i] = a.len_off[i];
+  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63, wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+  uint64_t* Xt = tiles[threadIdx.x >> 6];
+  uint64_t* Yt = Xt + 64 * W;
+  Region rg{a.slot0 + wave * a.per_wave * 64, 0};
+  const uint64_t w0 = a.e0 + (uint64_t)wave * a.per_wave * 64;
+  for (uint32_t it = 0; it < a.per_wave && w0 + 64 * it < a.e1; ++it) {
+    const uint64_t e = w0 + 64 * it + lane;
+    uint64_t key[W];
+    load_row<W>(a.rows, a.lstart + e, e < a.e1, key);
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      Xt[64 * k + lane] = transpose64(key[k]);
+      Yt[64 * k + lane] = (k == 0 && lane == 0) ? ~0ull : 0ull;
+    }
+    wave_sync_lds();
+    for (uint32_t l = 1; l <= a.max_len; ++l) {
+      for (uint32_t w = lo[l] + lane; w < lo[l + 1]; w += 64) Yt[w] = star_fold(Xt, Yt, gp, go[w], l);
+      wave_sync_lds();
+    }
+#pragma unroll
+    for (int k = 0; k < W; ++k) key[k] = transpose64(Yt[64 * k + lane]);
+    region_emit<W, kInl>(a, rg, e < a.e1, false, key, (uint32_t)(e - a.e0) + a.rel0);
+    wave_sync_lds();  // the tiles are rewritten by the next group
+  }
+  region_close(a, a.reg0 + wave, rg);
+}
+
+bool star_by_wave(int W, const GenArgs& a) {
+  return W <= 4 && a.n_pairs <= kStarPairs && a.max_len <= kStarMaxLen && a.n <= 64u * W;
+}
+
 // x.y, bit-sliced over 64 values of one operand.  A workgroup owns up to YT
 // tiles of 64 rows of the operand across the lanes (transposed into LDS:
 // Yt[tile][w], bit t = row t contains word w) and a group of rows of the
@@ -1160,6 +1208,12 @@ hipError_t launch_gen_w(int op, const GenArgs& a, hipStream_t s) {
       launch_timed(gen_question<W, kInl>, dim3(grid_for(cnt, 4 * per)), dim3(256), 0, s, a);
       break;
     case OP_STAR:
+      if constexpr (W <= 4) {
+        if (star_by_wave(W, a)) {
+          launch_timed(gen_star_wave<W, kInl>, dim3(grid_for(cnt, 4 * per)), dim3(256), 0, s, a);
+          break;
+        }
+      }
       launch_timed(gen_star<W, kInl>, dim3(grid_for(cnt, per)), dim3(256), 0, s, a);
       break;
     default:
@@ -1224,14 +1278,15 @@ bool take_slots(SlotPlan* sp, uint64_t slots, uint64_t regions) {
   return true;
 }
 
-hipError_t plan_gen(int op, GenArgs* a, SlotPlan* sp) {
+hipError_t plan_gen(int W, int op, GenArgs* a, SlotPlan* sp) {
   const uint64_t cnt = a->e1 - a->e0;
   if (a->e1 <= a->e0) return hipErrorInvalidValue;
-  // (a star's workgroup is one wave of candidates)
-  a->per_wave = op == OP_STAR ? (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(1, cnt / (64 * 4096)))
+  // (a workgroup per group of a star is one wave of candidates)
+  const bool by_group = op == OP_STAR && !star_by_wave(W, *a);
+  a->per_wave = by_group ? (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(1, cnt / (64 * 4096)))
                               : iterations_per_wave(cnt);
   const uint64_t per = (uint64_t)a->per_wave * 64;
-  const uint64_t waves = op == OP_STAR ? (cnt + per - 1) / per : 4 * ((cnt + 4 * per - 1) / (4 * per));
+  const uint64_t waves = by_group ? (cnt + per - 1) / per : 4 * ((cnt + 4 * per - 1) / (4 * per));
   a->slot0 = (uint32_t)sp->slots;
   a->reg0 = (uint32_t)sp->regions;
   return take_slots(sp, waves * per, waves) ? hipSuccess : hipErrorInvalidConfiguration;
