@@ -28,19 +28,99 @@ struct BlockD {
   uint64_t count;
 };
 
-// Work items of block b's candidates [e0, e1) in the current chunk: 64
-// consecutive candidates each, or one 64-candidate concatenation tile (64
-// right operands of one left operand, or 64 left operands of one right
-// operand when the right level is small and shorter than the left).
-__device__ inline uint64_t block_items(const BlockD& b, uint64_t e0, uint64_t e1, uint64_t nL, uint64_t nR) {
-  if (b.op != OP_CONCAT) return (e1 - e0 + 63) / 64;
-  if (nR >= 64 || nR >= nL) {
-    const uint64_t nT = (nR + 63) / 64;
-    const uint64_t f0 = (e0 / nR) * nT + (e0 % nR) / 64;
-    const uint64_t f1 = ((e1 - 1) / nR) * nT + ((e1 - 1) % nR) / 64;
-    return f1 - f0 + 1;
+// The rows of a level that a block takes as one operand: [0, a) and [b, n).
+// The others give candidates that equal an earlier one by an identity (see
+// the per-chunk path: concatenations as left operands of concatenations,
+// unions and r? as left operands and r? as right operands of unions, r? and
+// r* as operands of ? and *).
+struct Kept {
+  uint32_t a, b, n;
+  __device__ uint32_t count() const { return a + (n - b); }
+  __device__ uint32_t below(uint32_t r) const {
+    r = min(r, n);
+    return r <= a ? r : (r > b ? r - (b - a) : a);
   }
-  return ((e1 - 1) / nR / 64 - (e0 / nR) / 64 + 1) * nR;
+  __device__ uint32_t row(uint32_t k) const { return k < a ? k : b + (k - a); }
+  __device__ bool has(uint32_t r) const { return r < a || (r >= b && r < n); }
+};
+
+// A level's rows by constructor: characters below q, r? below s, r* below k,
+// concatenations below u, then unions.
+struct Marks {
+  uint32_t q, s, k, u;
+};
+
+__device__ inline Kept left_kept(uint32_t op, const Marks& m, uint32_t n) {
+  if (op == OP_CONCAT) return Kept{m.k, m.u, n};
+  if (op == OP_UNION) return Kept{m.q, m.s, m.u};
+  if (op == OP_CHAR) return Kept{n, n, n};
+  return Kept{m.q, m.k, n};
+}
+
+// Work of block b's candidates [e0, e1): the first kept index and the items.
+// Concatenations: an item is a 64-candidate tile, 64 right operands of one
+// left operand (`a` kept left row, `b` tile), or 64 left operands of one right
+// operand when the right level is small and shorter than the left (`a` tile
+// of kept left rows); others: 64 consecutive kept candidates from `k`
+// (unions of two levels: kept left row `a`, kept right row `b`).
+struct Span {
+  uint64_t k;
+  uint32_t a, b, items;
+};
+
+__device__ __forceinline__ bool right_lanes(uint32_t nL, uint32_t nR) { return nR >= 64 || nR >= nL; }
+
+__device__ inline Span block_span(const BlockD& blk, uint64_t e0, uint64_t e1, uint32_t nL, uint32_t nR, const Kept& kl,
+                                  const Kept& kr) {
+  Span sp{0, 0, 0, 0};
+  if (blk.op == OP_CONCAT) {
+    const uint64_t i0 = e0 / nR, i1 = (e1 - 1) / nR;
+    if (right_lanes(nL, nR)) {
+      const uint32_t nT = (nR + 63) / 64;
+      const uint32_t r0 = kl.below((uint32_t)i0), r1 = kl.below((uint32_t)i1);
+      sp.a = r0;
+      sp.b = kl.has((uint32_t)i0) ? (uint32_t)((e0 - i0 * nR) / 64) : 0u;
+      const uint32_t last = kl.has((uint32_t)i1) ? (uint32_t)((e1 - 1 - i1 * nR) / 64) + 1 : 0u;
+      sp.items = (r1 - r0) * nT + last - sp.b;
+    } else {
+      const uint32_t r0 = kl.below((uint32_t)i0), r1 = kl.below((uint32_t)i1 + 1);
+      sp.a = r0 / 64;
+      sp.items = r1 > r0 ? ((r1 - 1) / 64 - sp.a + 1) * nR : 0u;
+    }
+    return sp;
+  }
+  uint64_t k1;
+  if (blk.op != OP_UNION) {
+    sp.k = kl.below((uint32_t)e0);
+    k1 = kl.below((uint32_t)e1);
+  } else if (!blk.same) {
+    const uint32_t cols = kr.count();
+    const uint64_t i0 = e0 / nR, i1 = e1 / nR;
+    sp.a = kl.below((uint32_t)i0);
+    sp.b = kl.has((uint32_t)i0) ? kr.below((uint32_t)(e0 - i0 * nR)) : 0u;
+    const uint32_t a1 = kl.below((uint32_t)i1);
+    const uint32_t b1 = kl.has((uint32_t)i1) ? kr.below((uint32_t)(e1 - i1 * nR)) : 0u;
+    sp.k = 0;
+    k1 = (uint64_t)(a1 - sp.a) * cols + b1 - sp.b;
+  } else {
+    // pairs of kept rows before pair e of all rows
+    const uint64_t m = kl.count();
+    auto before = [&](uint64_t e) -> uint64_t {
+      if (e >= blk.count) return m ? m * (m - 1) / 2 : 0;
+      uint64_t i, j;
+      tri_decode(e, nL, &i, &j);
+      const uint64_t a = kl.below((uint32_t)i);
+      if (a + 1 >= m) return m ? m * (m - 1) / 2 : 0;
+      const uint64_t first = a * m - a * (a + 1) / 2;
+      if (!kl.has((uint32_t)i)) return first;
+      const uint64_t b = kl.below((uint32_t)j);
+      return first + (b > a + 1 ? b - (a + 1) : 0);
+    };
+    sp.k = before(e0);
+    k1 = before(e1);
+  }
+  sp.items = (uint32_t)((k1 - sp.k + 63) / 64);
+  return sp;
 }
 
 // Barrier between phases whose global-memory effects later phases read.  An
@@ -101,18 +181,26 @@ __device__ __forceinline__ void concat_tile(const uint64_t* T, const uint64_t* u
       for (int k = 0; k < 8; ++k) key[k0 + k] = transpose64(acc[k]);
     }
   } else {
+    // four cuts of a word at a time: their reads overlap (one by one, the
+    // three reads of a cut and the next cut's are a chain)
 #pragma unroll
     for (int k = 0; k < W; ++k) {
       const uint32_t w = 64u * k + lane;
+      const uint32_t q0 = w < n ? gto[w] : 0u, q1 = w < n ? gto[w + 1] : 0u;
       uint64_t acc = 0;
-      if (w < n) {
-        const uint32_t q1 = gto[w + 1];
-        for (uint32_t q = gto[w]; q < q1; ++q) {
-          const uint32_t p = gtp[q];
-          const uint32_t ui = kLeft ? (p & 0xFFFFu) : (p >> 16);
-          const uint32_t si = kLeft ? (p >> 16) : (p & 0xFFFFu);
-          if ((uni[ui >> 6] >> (ui & 63)) & 1ull) acc |= T[si];
+      for (uint32_t q = q0; q < q1; q += 4) {
+        uint32_t p[4];
+        uint64_t t[4], u[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) p[z] = gtp[min(q + z, q1 - 1)];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+          const uint32_t ui = kLeft ? (p[z] & 0xFFFFu) : (p[z] >> 16);
+          t[z] = T[kLeft ? (p[z] >> 16) : (p[z] & 0xFFFFu)];
+          u[z] = uni[ui >> 6] >> (ui & 63);  // (the last cut again is harmless)
         }
+#pragma unroll
+        for (int z = 0; z < 4; ++z) acc |= (u[z] & 1ull) ? t[z] : 0ull;
       }
       key[k] = transpose64(acc);
     }
@@ -208,12 +296,19 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
   __shared__ BlockD s_blk[kMaxBlocks];
   __shared__ uint64_t s_bstart[kMaxBlocks + 1];  // level index of each block's first candidate
   __shared__ uint32_t s_item0[kMaxBlocks + 1];   // each block's first work item in the current chunk
+  __shared__ Span s_span[kMaxBlocks];            // and its work there
+  __shared__ Marks s_mk[kBatchMaxCost + 2];      // each level's rows by constructor
+  __shared__ uint64_t s_thr[4];                  // this level's first index after its characters, r?, r*, r.s
   __shared__ uint32_t s_nblk;
-  __shared__ uint32_t s_nsurv, s_ans, s_rank, s_over, s_stop, s_resume;
+  __shared__ uint32_t s_nsurv, s_ans, s_rank, s_over, s_stop, s_resume, s_leave;
   __shared__ uint64_t s_total;
   __shared__ uint32_t s_bm[kWords], s_pre[kWords];
   __shared__ uint32_t s_winners;
-  __shared__ uint64_t s_tile[kWaves][64 * W];
+  // a star item needs two tiles: up to two words per language each wave has
+  // its own two, from four on waves pair up for the star blocks (more tiles
+  // would leave room for fewer workgroups on a compute unit)
+  constexpr bool kStarItems = W <= 2;
+  __shared__ uint64_t s_tile[kWaves][(kStarItems ? 2 : 1) * 64 * W];
   static_assert(W < 8 || sizeof(s_tile) >= kBatchChunk * sizeof(uint16_t), "ranks of a chunk fit the tiles");
   static_assert(kBatchChunk <= 0xFFFFu, "ranks of a chunk fit 16 bits");
   __shared__ uint64_t s_uni[kWaves][W];
@@ -288,46 +383,86 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
 
   uint32_t ans_cost = 0;
   uint64_t ans_e = 0;
+  uint64_t ref_gen = (1ull << 36) - 2;  // inline-key references: one lower each chunk, so older ones need no reset
   const long long t_start = wall_clock64();
   for (uint32_t c = d.c1; c <= d.max_cost && s_stop == STOP_NONE; ++c) {
-    if (tid == 0) {
-      s_lstart[c] = s_total;
-      // constructor blocks of level c, in enumeration order
-      uint32_t nb = 0;
+    if (wave == 0) {
+      // constructor blocks of level c, in enumeration order, one per lane:
+      // characters, or r?, r*, r.s by left cost, r+s by left cost
       auto lc = [&](int64_t k) -> uint64_t { return (k >= (int64_t)d.c1 && k < (int64_t)c) ? s_lcount[k] : 0ull; };
-      if (c == d.c1) {
-        s_blk[nb++] = {OP_CHAR, 0, 0, 0, (uint64_t)d.nsigma};
-      } else {
-        const int64_t cc = c;
-        if (lc(cc - d.c2)) s_blk[nb++] = {OP_QUESTION, (uint32_t)(cc - d.c2), 0, 0, lc(cc - d.c2)};
-        if (lc(cc - d.c3)) s_blk[nb++] = {OP_STAR, (uint32_t)(cc - d.c3), 0, 0, lc(cc - d.c3)};
-        for (int64_t L = d.c1; cc - (int64_t)d.c4 - L >= (int64_t)d.c1; ++L) {
-          const int64_t R = cc - d.c4 - L;
-          const uint64_t n = lc(L) * lc(R);
-          if (n) s_blk[nb++] = {OP_CONCAT, (uint32_t)L, (uint32_t)R, 0, n};
+      const int64_t cc = c, c1 = d.c1;
+      const int32_t n_cat = c == d.c1 ? 0 : (int32_t)max((int64_t)0, cc - (int64_t)d.c4 - 2 * c1 + 1);
+      const int32_t n_uni = c == d.c1 ? 0 : (int32_t)max((int64_t)0, (cc - (int64_t)d.c5 >= 0 ? (cc - (int64_t)d.c5) / 2 : -1) - c1 + 1);
+      const int32_t n_all = 2 + n_cat + n_uni;  // (at c1: the characters and nothing)
+      uint32_t nb = 0;
+      uint64_t run = 0, thr[4] = {0, 0, 0, 0};
+      for (int32_t k0 = 0; k0 < n_all; k0 += 64) {
+        const int32_t k = k0 + (int32_t)lane;
+        BlockD b{0, 0, 0, 0, 0};
+        if (c == d.c1) {
+          if (k == 0) b = BlockD{OP_CHAR, 0, 0, 0, (uint64_t)d.nsigma};
+        } else if (k == 0) {
+          b = BlockD{OP_QUESTION, (uint32_t)(cc - d.c2), 0, 0, lc(cc - d.c2)};
+        } else if (k == 1) {
+          b = BlockD{OP_STAR, (uint32_t)(cc - d.c3), 0, 0, lc(cc - d.c3)};
+        } else if (k < 2 + n_cat) {
+          const int64_t L = c1 + (k - 2), R = cc - d.c4 - L;
+          b = BlockD{OP_CONCAT, (uint32_t)L, (uint32_t)R, 0, lc(L) * lc(R)};
+        } else if (k < n_all) {
+          const int64_t L = c1 + (k - 2 - n_cat), R = cc - d.c5 - L;
+          const uint64_t x = lc(L), y = lc(R);
+          b = BlockD{OP_UNION, (uint32_t)L, (uint32_t)R, L == R ? 1u : 0u, L < R ? x * y : (x ? x * (x - 1) / 2 : 0)};
         }
-        for (int64_t L = d.c1; L <= cc - (int64_t)d.c5 - L; ++L) {
-          const int64_t R = cc - d.c5 - L;
-          const uint64_t a = lc(L), b = lc(R);
-          const uint64_t n = (L < R) ? a * b : (a ? a * (a - 1) / 2 : 0);
-          if (n) s_blk[nb++] = {OP_UNION, (uint32_t)L, (uint32_t)R, L == R ? 1u : 0u, n};
+        uint64_t incl = b.count;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+          const uint64_t v = __shfl_up((unsigned long long)incl, off, kWave);
+          if ((int)lane >= off) incl += v;
         }
+        const uint64_t some = __ballot(b.count != 0);
+        if (b.count) {
+          const uint32_t at = nb + (uint32_t)__popcll(some & ((1ull << lane) - 1));
+          s_blk[at] = b;
+          s_bstart[at] = run + incl - b.count;
+        }
+        // ends of the constructors' index ranges
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const uint64_t mine = __ballot(b.count != 0 && (int)b.op <= t);
+          if (mine) {
+            const int last = 63 - __clzll((long long)mine);
+            thr[t] = run + __shfl((unsigned long long)incl, last, kWave);
+          }
+        }
+        nb += (uint32_t)__popcll(some);
+        run += __shfl((unsigned long long)incl, kWave - 1, kWave);
       }
-      s_nblk = nb;
-      s_bstart[0] = 0;
-      for (uint32_t b = 0; b < nb; ++b) s_bstart[b + 1] = s_bstart[b] + s_blk[b].count;
-      // a level this large is work for the whole device: hand the instance,
-      // with its lower levels stored, to the per-chunk path; so is a
-      // mid-sized level of an instance that has kept its workgroup long
-      // (the deep searches of a batch), while the device has room beside it
-      const bool late = d.time_ticks && s_bstart[nb] > kBatchTimeMinLevel &&
-                        (uint64_t)(wall_clock64() - t_start) > d.time_ticks;
-      if (s_bstart[nb] > d.level_max || late) {
-        s_stop = STOP_HANDOFF;
-        s_resume = c;
+      if (lane == 0) {
+        s_lstart[c] = s_total;
+        s_nblk = nb;
+        s_bstart[nb] = run;
+        uint64_t t = 0;
+        for (int q = 0; q < 4; ++q) s_thr[q] = t = thr[q] > t ? thr[q] : t;
+        s_mk[c] = Marks{~0u, ~0u, ~0u, ~0u};
+        // a level this large is work for the whole device: hand the instance,
+        // with its lower levels stored, to the per-chunk path; so is a
+        // mid-sized level of an instance that has kept its workgroup long
+        // (the deep searches of a batch), while the device has room beside it
+        const bool late = d.time_ticks && run > kBatchTimeMinLevel &&
+                          (uint64_t)(wall_clock64() - t_start) > d.time_ticks;
+        s_leave = run > d.level_max || late ? 1u : 0u;
       }
     }
     __syncthreads();
+    // (s_stop is written where no wave reads it: other waves may still be at
+    // the loop's condition while the blocks are built)
+    if (s_leave) {
+      if (tid == 0) {
+        s_stop = STOP_HANDOFF;
+        s_resume = c;
+      }
+      break;
+    }
     const uint32_t nblk = s_nblk;
     const uint64_t level_total = s_bstart[nblk];
     // Chunks cover consecutive level indices [E0, E1) and may span several
@@ -354,15 +489,47 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
           __syncthreads();
         }
       }
-      if (tid == 0) {
-        s_nsurv = 0;
-        s_ans = ~0u;
-        s_rank = ~0u;
-        s_over = ~0u;
+      --ref_gen;
+      for (uint32_t i = tid; i < (len + 31) / 32; i += kT) s_bm[i] = 0;
+      if (wave == 0) {
+        if (lane == 0) {
+          s_nsurv = 0;
+          s_ans = ~0u;
+          s_rank = ~0u;
+          s_over = ~0u;
+        }
+        // each block's work in this chunk, a block per lane
+        uint32_t run = 0;
+        for (uint32_t b0 = 0; b0 < nblk; b0 += 64) {
+          const uint32_t bi = b0 + lane;
+          Span sp{0, 0, 0, 0};
+          if (bi < nblk) {
+            const uint64_t bs = s_bstart[bi], be = s_bstart[bi + 1];
+            const BlockD blk = s_blk[bi];
+            if (be > E0 && bs < E1) {
+              const uint32_t nL = blk.op == OP_CHAR ? d.nsigma : (uint32_t)s_lcount[blk.L], nR = (uint32_t)s_lcount[blk.R];
+              const Marks mr = s_mk[blk.R];
+              sp = block_span(blk, max(E0, bs) - bs, min(E1, be) - bs, nL, nR, left_kept(blk.op, s_mk[blk.L], nL),
+                              Kept{mr.q, mr.s, nR});
+            }
+            s_span[bi] = sp;
+          }
+          const uint32_t dealt = bi < nblk && (kStarItems || s_blk[bi].op != OP_STAR) ? sp.items : 0u;
+          uint32_t incl = dealt;
+#pragma unroll
+          for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t v = (uint32_t)__shfl_up((int)incl, off, kWave);
+            if ((int)lane >= off) incl += v;
+          }
+          if (bi < nblk) s_item0[bi] = run + incl - dealt;
+          run += (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        }
+        if (lane == 0) s_item0[nblk] = run;
       }
       __syncthreads();
-      // Star blocks first, one at a time: they pair the waves and need the
-      // workgroup barriers around them.
+      // Star blocks first, one at a time, where they pair the waves: they
+      // need the workgroup barriers around them.
+      if constexpr (!kStarItems)
       for (uint32_t bi = 0; bi < nblk; ++bi) {
         const uint64_t bs = s_bstart[bi], be = s_bstart[bi + 1];
         if (be <= E0) continue;
@@ -384,8 +551,11 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
           uint64_t* Xt = s_tile[wave];
           uint64_t* Yt = s_tile[wave + 1];
           constexpr uint32_t kPairs = kWaves / 2;
-          for (uint64_t g0 = e0 + 64 * (uint64_t)(wave >> 1); g0 < e1; g0 += 64 * (uint64_t)kPairs) {
-            const uint64_t e = g0 + lane;
+          const Kept kl = left_kept(OP_STAR, s_mk[blk.L], (uint32_t)s_lcount[blk.L]);
+          const Span sp = s_span[bi];
+          for (uint32_t g = wave >> 1; g < sp.items; g += kPairs) {
+            const uint32_t kk = (uint32_t)sp.k + 64 * g + lane;
+            const uint64_t e = kk < kl.count() ? kl.row(kk) : e1;
 #pragma unroll
             for (int k = 0; k < W; ++k) {
               const uint64_t v = (e < e1) ? d.rows[(lst + e) * W + k] : 0ull;
@@ -406,7 +576,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
             uint64_t key[W];
 #pragma unroll
             for (int k = 0; k < W; ++k) key[k] = transpose64(Yt[64 * k + lane]);
-            filter_emit<W, kInl>(probe, sink, e < e1, false, key, (uint32_t)(rel0 + e));
+            filter_emit<W, kInl>(probe, sink, e >= e0 && e < e1, false, key, (uint32_t)(rel0 + e));
             wave_sync_lds();  // the tiles are rewritten by the next group
           }
         }
@@ -415,18 +585,6 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
       // Every other block's work items (64 consecutive candidates, or one
       // concatenation tile) are dealt to the waves together, so a chunk that
       // spans many small blocks keeps every wave busy.
-      if (tid == 0) {
-        uint32_t n = 0;
-        for (uint32_t bi = 0; bi < nblk; ++bi) {
-          s_item0[bi] = n;
-          const uint64_t bs = s_bstart[bi], be = s_bstart[bi + 1];
-          const BlockD blk = s_blk[bi];
-          if (be > E0 && bs < E1 && blk.op != OP_STAR)
-            n += (uint32_t)block_items(blk, max(E0, bs) - bs, min(E1, be) - bs, s_lcount[blk.L], s_lcount[blk.R]);
-        }
-        s_item0[nblk] = n;
-      }
-      __syncthreads();
       {
         const uint32_t n_items = s_item0[nblk];
         uint32_t bi = 0;
@@ -439,12 +597,55 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
           const uint64_t rst = s_lstart[blk.R], rct = s_lcount[blk.R];
           const uint64_t e0 = max(E0, bs) - bs, e1 = min(E1, be) - bs;
           const uint64_t rel0 = bs - E0;
+          const Span sp = s_span[bi];
+          const Kept kl = left_kept(blk.op, s_mk[blk.L], blk.op == OP_CHAR ? d.nsigma : (uint32_t)lct);
           if (blk.op != OP_CONCAT) {
-            const uint64_t e = e0 + 64 * (uint64_t)li + lane;
-            const bool valid = e < e1;
+            // kept candidate 64 li + lane of the block's in this chunk
+            uint64_t e = ~0ull, i = 0, j = 0;
+            if (blk.op != OP_UNION) {
+              const uint32_t kk = (uint32_t)sp.k + 64 * li + lane;
+              if (kk < kl.count()) e = kl.row(kk);
+            } else if (blk.same) {
+              const uint64_t m = kl.count(), kk = sp.k + 64 * li + lane;
+              if (kk < m * (m - 1) / 2) {
+                tri_decode(kk, m, &i, &j);
+                i = kl.row((uint32_t)i);
+                j = kl.row((uint32_t)j);
+                e = i * lct - i * (i + 1) / 2 + (j - i - 1);
+              }
+            } else {
+              const Marks mr = s_mk[blk.R];
+              const Kept kr{mr.q, mr.s, (uint32_t)rct};
+              const uint32_t cols = kr.count(), t = sp.b + 64 * li + lane;
+              const uint32_t ai = sp.a + t / cols;
+              if (ai < kl.count()) {
+                i = kl.row(ai);
+                j = kr.row(t - (ai - sp.a) * cols);
+                e = i * rct + j;
+              }
+            }
+            const bool valid = e >= e0 && e < e1;
             uint64_t key[W];
             bool dup = false;
-            if (blk.op == OP_CHAR) {
+            if (kStarItems && blk.op == OP_STAR) {
+              // r* of 64 rows (as for the paired waves above)
+              uint64_t* Xt = s_tile[wave];
+              uint64_t* Yt = s_tile[wave] + 64 * W;
+#pragma unroll
+              for (int k = 0; k < W; ++k) {
+                Xt[64 * k + lane] = transpose64(valid ? d.rows[(lst + e) * W + k] : 0ull);
+                Yt[64 * k + lane] = (k == 0 && lane == 0) ? ~0ull : 0ull;
+              }
+              wave_sync_lds();
+              for (uint32_t l = 1; l <= d.max_len; ++l) {
+                const uint32_t lo = s_lo[l], hi = s_lo[l + 1];
+                for (uint32_t w = lo + lane; w < hi; w += 64) Yt[w] = star_fold(Xt, Yt, s_gtp, s_gto[w], l);
+                wave_sync_lds();
+              }
+#pragma unroll
+              for (int k = 0; k < W; ++k) key[k] = transpose64(Yt[64 * k + lane]);
+              wave_sync_lds();  // the tiles are rewritten by the next item
+            } else if (blk.op == OP_CHAR) {
               const int idx = valid ? d.char_index[e] : -1;
 #pragma unroll
               for (int k = 0; k < W; ++k) key[k] = (idx >= 0 && (idx >> 6) == k) ? (1ull << (idx & 63)) : 0ull;
@@ -455,15 +656,6 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
               dup = (key[0] & 1ull) != 0;
               key[0] |= 1ull;
             } else {
-              uint64_t i = 0, j = 0;
-              if (valid) {
-                if (blk.same) {
-                  tri_decode(e, lct, &i, &j);
-                } else {
-                  i = e / rct;
-                  j = e - i * rct;
-                }
-              }
               const uint64_t* x = d.rows + (lst + i) * W;
               const uint64_t* y = d.rows + (rst + j) * W;
               bool eqx = true, eqy = true;
@@ -481,14 +673,13 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
           }
           uint64_t* T = s_tile[wave];
           uint64_t* U = s_uni[wave];
-          const uint64_t nL = lct, nR = rct;
-          if (nR >= 64 || nR >= nL) {
-            // right operands across the lanes: tile f = i * nT + jt holds
-            // candidates i * nR + 64 * jt + lane; the block's items are the
-            // tiles from the one holding e0 to the one holding e1 - 1
-            const uint64_t nT = (nR + 63) / 64;
-            const uint64_t f = (e0 / nR) * nT + (e0 % nR) / 64 + li;
-            const uint64_t i = f / nT, jt = f - i * nT;
+          const uint32_t nL = (uint32_t)lct, nR = (uint32_t)rct;
+          if (right_lanes(nL, nR)) {
+            // right operands across the lanes: the block's tiles, row by kept
+            // left row, from the one at (sp.a, sp.b)
+            const uint32_t nT = (nR + 63) / 64, f = sp.b + li;
+            const uint64_t i = kl.row(sp.a + f / nT);
+            const uint32_t jt = f % nT;
             const uint64_t jr = 64 * jt + lane;
 #pragma unroll
             for (int k = 0; k < W; ++k)
@@ -502,11 +693,11 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
             wave_sync_lds();
           } else {
             // left operands across the lanes (the right level is small):
-            // item li is (left tile xt, right operand j)
-            const uint64_t xt = (e0 / nR) / 64 + li / nR, j = li % nR;
-            const uint64_t ef = (64 * xt) * nR + j, el = (64 * xt + 63) * nR + j;
-            if (el < e0 || ef >= e1) continue;
-            const uint64_t ir = 64 * xt + lane;
+            // item li is (tile of kept left rows, right operand j)
+            const uint32_t kk = 64 * (sp.a + li / nR) + lane, j = li % nR;
+            const uint64_t ir = kk < kl.count() ? kl.row(kk) : nL;
+            const uint64_t ec = ir * nR + j;
+            if (!__any(ir < nL && ec >= e0 && ec < e1)) continue;
 #pragma unroll
             for (int k = 0; k < W; ++k)
               T[64 * k + lane] = transpose64(ir < nL ? d.rows[(lst + ir) * W + k] : 0ull);
@@ -522,30 +713,30 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
       }
       phase_barrier();
 
-        // ---- insert survivors
+        // ---- insert survivors; winners' bits end up set (a survivor that
+        // takes its slot toggles its bit on, one that is displaced has its
+        // bit toggled off)
         const uint32_t ns = s_nsurv;
         for (uint32_t sid = tid; sid < ns; sid += kT) {
           uint64_t key[W];
 #pragma unroll
           for (int k = 0; k < W; ++k) key[k] = d.skey[(uint64_t)sid * W + k];
           const uint64_t h = d.spos[sid];
+          const uint32_t e = d.se[sid];
+          const uint64_t mine = kInl ? chunk_ref(ref_gen, e) : new_ref(e, sid);
           uint64_t old;
-          const uint64_t pos = table_insert<W, kInl>(d.slots, tmask, d.rows, d.skey, key, h,
-                                                     new_ref(d.se[sid], sid), &old);
-          d.spos[sid] = spos_pack(pos, h);
+          const uint64_t pos = table_insert<W, kInl>(d.slots, tmask, d.rows, d.skey, key, h, mine, &old);
+          if constexpr (!kInl) d.spos[sid] = spos_pack(pos, h);
+          if (mine < old) {
+            atomicXor(&s_bm[e >> 5], 1u << (e & 31));
+            uint32_t oe;
+            if (displaced_survivor<kInl>(old, ref_gen, &oe)) atomicXor(&s_bm[oe >> 5], 1u << (oe & 31));
+          }
         }
         phase_barrier();
 
-        // ---- winners, ranks, ordered append, accounting
+        // ---- ranks, ordered append, accounting
         const uint32_t words = (len + 31) / 32;
-        for (uint32_t i = tid; i < words; i += kT) s_bm[i] = 0;
-        __syncthreads();
-        for (uint32_t sid = tid; sid < ns; sid += kT) {
-          const uint32_t e = d.se[sid];
-          if (table_is_winner<kInl>(d.slots, d.spos[sid], new_ref(e, sid)))
-            atomicOr(&s_bm[e >> 5], 1u << (e & 31));
-        }
-        __syncthreads();
         if (wave == 0) {
           const uint32_t t = wave_popc_scan<kWords / 64>(s_bm, s_pre, words);
           if (lane == 0) s_winners = t;
@@ -556,6 +747,11 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
         const uint64_t room = d.row_cap > total ? d.row_cap - total : 0;
         const uint64_t alloc_room = d.rows_alloc > total ? d.rows_alloc - total : 0;
         const uint32_t ans = s_ans;
+        // constructor boundaries of the level that lie in this chunk
+        if (tid < 4 && s_thr[tid] >= E0 && s_thr[tid] < E1) {
+          const uint32_t r = (uint32_t)(s_thr[tid] - E0);
+          (&s_mk[c].q)[tid] = (uint32_t)s_lcount[c] + s_pre[r >> 5] + (uint32_t)__popc(s_bm[r >> 5] & ((1u << (r & 31)) - 1));
+        }
         // each survivor's rank among the stored rows (kNotStored: not stored)
         constexpr uint32_t kNotStored = 0xFFFFu;  // ranks are below kBatchChunk
         auto place = [&](uint32_t sid, uint32_t e) -> uint32_t {
@@ -578,7 +774,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
 #pragma unroll
             for (int k = 0; k < W; ++k) d.rows[row * W + k] = d.skey[(uint64_t)sid * W + k];
             d.aux[row] = E0 + e;
-            table_publish<kInl>(d.slots, d.spos[sid], row);
+            if constexpr (!kInl) table_publish(d.slots, d.spos[sid], row);
           }
         } else {
           // wide rows: ranks into LDS (over the tiles, idle in this phase),
@@ -595,7 +791,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
             d.rows[row * W + k] = d.skey[(uint64_t)q * W + k];
             if (k == 0) {
               d.aux[row] = E0 + d.se[q];
-              table_publish<kInl>(d.slots, d.spos[q], row);
+              table_publish(d.slots, d.spos[q], row);
             }
           }
         }
@@ -639,6 +835,9 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
         }
         phase_barrier();
     }
+    // boundaries at the level's end
+    if (tid < 4 && (&s_mk[c].q)[tid] == ~0u) (&s_mk[c].q)[tid] = (uint32_t)s_lcount[c];
+    __syncthreads();  // every wave is done with this level's blocks
   }
 
   // ---- results, written straight to the instance's host-visible buffers

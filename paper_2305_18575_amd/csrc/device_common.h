@@ -278,22 +278,30 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask,
 constexpr uint64_t kPosMask = (1ull << 40) - 1;
 __device__ __forceinline__ uint64_t spos_pack(uint64_t pos, uint64_t h) { return pos | (fingerprint(h) << 40); }
 
-// After all inserts of the chunk: does `mine` own its key's slot?  rec is
-// the survivor's slot record.
-template <bool kInl>
-__device__ __forceinline__ bool table_is_winner(const uint64_t* slots, uint64_t rec, uint64_t mine) {
-  const uint64_t pos = rec & kPosMask;
-  return kInl ? slots[2 * pos + 1] == mine : slots[pos] == mine;
+// The winner (slot record rec) is now stored as `row` (fingerprint form; inline
+// keys are in their slots already).
+__device__ __forceinline__ void table_publish(uint64_t* slots, uint64_t rec, uint64_t row) {
+  slots[rec & kPosMask] = ((rec >> 40) << kRowBits) | row;
 }
 
-// The winner (slot record rec) is now stored as `row`.
+// References of the inline form (no survivor id needed): those of later chunks
+// are smaller than any of earlier ones (gen counts down above bit 28), so they
+// need no reset once the chunk is over.
+constexpr int kRefBits = 28;
+static_assert(kMaxChunk <= (1ull << kRefBits), "chunk-relative indices fit a reference");
+__device__ __forceinline__ uint64_t chunk_ref(uint64_t gen, uint32_t e) { return (gen << kRefBits) | e; }
+
+// Whether the reference a survivor took its slot from (table_insert's old)
+// belongs to another survivor of the chunk, and that one's index.
 template <bool kInl>
-__device__ __forceinline__ void table_publish(uint64_t* slots, uint64_t rec, uint64_t row) {
-  const uint64_t pos = rec & kPosMask;
-  if constexpr (kInl)
-    slots[2 * pos + 1] = kEmpty;  // the key is in the slot already
-  else
-    slots[pos] = ((rec >> 40) << kRowBits) | row;
+__device__ __forceinline__ bool displaced_survivor(uint64_t old, uint64_t gen, uint32_t* e) {
+  if constexpr (kInl) {
+    *e = (uint32_t)(old & ((1ull << kRefBits) - 1));
+    return (old >> kRefBits) == gen;  // (not EMPTY nor an earlier chunk's)
+  } else {
+    *e = (uint32_t)(old >> 32) & 0x7FFFFFFFu;
+    return old != kEmpty;
+  }
 }
 
 // Stores a row's key during a rebuild (all keys distinct).

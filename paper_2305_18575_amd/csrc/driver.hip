@@ -182,8 +182,8 @@ struct rei_instance {
   // levels, indexed by cost
   std::vector<uint64_t> lstart, lcount;
   // constructor boundaries of the stored levels, as far as they were asked
-  // for, and the pinned buffer the device writes them to (kMaxMarks, then the
-  // number of the last launch that is done)
+  // for, and where the device writes them (kMaxMarks, then the number of the
+  // last launch that is done; pinned, after the answer tree)
   std::vector<LevelMarks> marks;
   uint64_t* h_marks = nullptr;
   uint64_t* v_marks = nullptr;
@@ -581,13 +581,6 @@ rei_status marks_launch(rei_instance* in, hipStream_t s, const std::vector<uint3
                         std::vector<LevelMarks>* plan, uint32_t* n_out) {
   MarksArgs a{};
   *n_out = 0;
-  if (!in->h_marks) {
-    HIP_OK(in, hipHostMalloc((void**)&in->h_marks, (kMaxMarks + 1) * 8,
-                             hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent));
-    HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_marks, in->h_marks, 0));
-    in->h_marks[kMaxMarks] = 0;
-    in->marks_seq = 0;
-  }
   std::vector<Block> blocks;
   plan->clear();
   for (uint32_t c : levels) {
@@ -1963,7 +1956,6 @@ void free_device(rei_instance* in) {
   if (in->h_state) (void)hipHostFree(in->h_state);
   if (in->h_levels) (void)hipHostFree(in->h_levels);
   if (in->h_tree) (void)hipHostFree(in->h_tree);
-  if (in->h_marks) (void)hipHostFree(in->h_marks);
   in->h_state = nullptr;
   in->h_levels = nullptr;
   in->h_tree = nullptr;
@@ -2005,11 +1997,14 @@ rei_status create_device(rei_instance* in) {
   const unsigned fl = hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent;
   HIP_OK(in, hipHostMalloc((void**)&in->h_state, sizeof(DevState), fl));
   HIP_OK(in, hipHostMalloc((void**)&in->h_levels, 3 * L * 8, fl));
-  HIP_OK(in, hipHostMalloc((void**)&in->h_tree, (1 + 4 * kBatchTreeNodes) * 8, fl));
+  HIP_OK(in, hipHostMalloc((void**)&in->h_tree, (1 + 4 * kBatchTreeNodes + kMaxMarks + 1) * 8, fl));
   in->h_tree[0] = 0;
+  in->h_marks = in->h_tree + 1 + 4 * kBatchTreeNodes;
+  in->h_marks[kMaxMarks] = 0;
   HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_state, in->h_state, 0));
   HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_levels, in->h_levels, 0));
   HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_tree, in->h_tree, 0));
+  in->v_marks = in->v_tree + 1 + 4 * kBatchTreeNodes;
   return REI_OK;
 }
 

@@ -579,15 +579,22 @@ __device__ __forceinline__ void concat_fold(const GenArgs& a, const PieceD& p, u
     for (int q = 0; q < W; ++q) {
       if (q < q_lo || q >= q_hi) continue;
       const uint32_t w = 64u * q + lane;
+      const uint32_t c0 = w < a.n ? a.gt_off[w] : 0u, c1 = w < a.n ? a.gt_off[w + 1] : 0u;
       uint64_t acc = 0;
-      if (w < a.n) {
-        const uint32_t q1 = a.gt_off[w + 1];
-        for (uint32_t c = a.gt_off[w]; c < q1; ++c) {
-          const uint32_t pr = a.gt_pair[c];
-          const uint32_t uu = p.left_lanes ? (pr & 0xFFFFu) : (pr >> 16);   // index into the uniform row
-          const uint32_t tt = p.left_lanes ? (pr >> 16) : (pr & 0xFFFFu);   // index into the tile
-          if ((U[uu >> 6] >> (uu & 63)) & 1ull) acc |= X[tt];
+      // four cuts at a time: their reads overlap
+      for (uint32_t c = c0; c < c1; c += 4) {
+        uint32_t pr[4];
+        uint64_t xv[4], uv[4];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) pr[z] = a.gt_pair[min(c + z, c1 - 1)];
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+          const uint32_t uu = p.left_lanes ? (pr[z] & 0xFFFFu) : (pr[z] >> 16);  // index into the uniform row
+          xv[z] = X[p.left_lanes ? (pr[z] >> 16) : (pr[z] & 0xFFFFu)];           // of the tile
+          uv[z] = U[uu >> 6] >> (uu & 63);
         }
+#pragma unroll
+        for (int z = 0; z < 4; ++z) acc |= (uv[z] & 1ull) ? xv[z] : 0ull;  // (the last cut again is harmless)
       }
       key[q] = transpose64(acc);
     }
@@ -792,17 +799,6 @@ __device__ __forceinline__ void toggle_bits(uint32_t* bitmap, uint32_t e, bool o
   if (head && on) atomicXor(&bitmap[w], m);
 }
 
-// A survivor's reference in this chunk: the smaller wins its key's slot.
-// With keys inline (no survivor id needed) references of later chunks are
-// smaller than any of earlier ones (ref_gen counts down above bit 28), so
-// they need no reset once the chunk is over.
-constexpr int kRefBits = 28;
-static_assert(kMaxChunk <= (1ull << kRefBits), "chunk-relative indices fit a reference");
-template <bool kInl>
-__device__ __forceinline__ uint64_t chunk_ref(const ChunkArgs& a, uint32_t e, uint32_t sid) {
-  return kInl ? (a.ref_gen << kRefBits) | e : new_ref(e, sid);
-}
-
 // Insertion, and the winners' bits: a survivor that takes its slot toggles
 // its bit on, one that is displaced has its bit toggled off by the displacing
 // survivor.  Toggles commute, so each winner's bit ends up set and every
@@ -825,23 +821,13 @@ __global__ __launch_bounds__(256) void insert_survivors(ChunkArgs a) {
       load_row<W>(a.skey, sid, true, key);
       const uint64_t h = a.spos[sid];
       e = a.se[sid];
-      const uint64_t mine = chunk_ref<kInl>(a, e, sid);
+      const uint64_t mine = kInl ? chunk_ref(a.ref_gen, e) : new_ref(e, sid);
       uint64_t old;
       const uint64_t pos = table_insert<W, kInl>(a.slots, a.slot_mask, a.rows, a.skey, key, h, mine, &old);
       if constexpr (!kInl) a.spos[sid] = spos_pack(pos, h);
       won = mine < old;  // else an earlier candidate has it
-      // displaced: another survivor of this chunk (EMPTY and, inline, earlier
-      // chunks' references are not)
       uint32_t oe;
-      bool displaced;
-      if constexpr (kInl) {
-        displaced = won && (old >> kRefBits) == a.ref_gen;
-        oe = (uint32_t)(old & ((1ull << kRefBits) - 1));
-      } else {
-        displaced = won && old != kEmpty;
-        oe = (uint32_t)(old >> 32) & 0x7FFFFFFFu;
-      }
-      if (displaced) atomicXor(&a.bitmap[oe >> 5], 1u << (oe & 31));
+      if (won && displaced_survivor<kInl>(old, a.ref_gen, &oe)) atomicXor(&a.bitmap[oe >> 5], 1u << (oe & 31));
     }
     toggle_bits(a.bitmap, e, won);
   });
@@ -936,7 +922,7 @@ __device__ __forceinline__ void store_winner(const ChunkArgs& a, uint32_t sid, u
 #pragma unroll
   for (int k = 0; k < W; ++k) a.rows_w[row * W + k] = key[k];
   a.aux[row] = a.chunk_e0 + e;
-  if constexpr (!kInl) table_publish<kInl>(a.slots, rec, row);
+  if constexpr (!kInl) table_publish(a.slots, rec, row);
 }
 
 constexpr uint32_t kSmallWords = (uint32_t)(kSmallChunk / 32);
@@ -1021,7 +1007,7 @@ __global__ __launch_bounds__(1024) void finalize_small(ChunkArgs a) {
       a.rows_w[row * W + k] = a.skey[(uint64_t)q * W + k];
       if (k == 0) {
         a.aux[row] = a.chunk_e0 + a.se[q];
-        table_publish<kInl>(a.slots, a.spos[q], row);
+        table_publish(a.slots, a.spos[q], row);
       }
     }
   }
