@@ -207,63 +207,77 @@ __device__ __forceinline__ void concat_tile(const uint64_t* T, const uint64_t* u
   }
 }
 
+// Constructor block k of level c, blocks in enumeration order: the characters
+// at c1; else r?, r*, r.s by left cost, r+s by left cost (blocks may be
+// empty).  The counts of the levels below c are final.
+struct BlockList {
+  const BatchDesc& d;
+  const uint64_t* lcount;
+  uint32_t c;
+  int32_t n_cat, n_uni;
+  __device__ BlockList(const BatchDesc& d_, const uint64_t* lcount_, uint32_t c_) : d(d_), lcount(lcount_), c(c_) {
+    const int64_t cc = c, c1 = d.c1;
+    n_cat = c == d.c1 ? 0 : (int32_t)max((int64_t)0, cc - (int64_t)d.c4 - 2 * c1 + 1);
+    n_uni = c == d.c1 ? 0 : (int32_t)max((int64_t)0, (cc >= (int64_t)d.c5 ? (cc - (int64_t)d.c5) / 2 : -1) - c1 + 1);
+  }
+  __device__ int32_t count() const { return c == d.c1 ? 1 : 2 + n_cat + n_uni; }
+  __device__ BlockD get(int32_t k) const {
+    const int64_t cc = c, c1 = d.c1;
+    auto lc = [&](int64_t q) -> uint64_t { return (q >= c1 && q < cc) ? lcount[q] : 0ull; };
+    if (k >= count()) return BlockD{0, 0, 0, 0, 0};
+    if (c == d.c1) return BlockD{OP_CHAR, 0, 0, 0, (uint64_t)d.nsigma};
+    if (k == 0) return BlockD{OP_QUESTION, (uint32_t)(cc - d.c2), 0, 0, lc(cc - d.c2)};
+    if (k == 1) return BlockD{OP_STAR, (uint32_t)(cc - d.c3), 0, 0, lc(cc - d.c3)};
+    if (k < 2 + n_cat) {
+      const int64_t L = c1 + (k - 2), R = cc - d.c4 - L;
+      return BlockD{OP_CONCAT, (uint32_t)L, (uint32_t)R, 0, lc(L) * lc(R)};
+    }
+    const int64_t L = c1 + (k - 2 - n_cat), R = cc - d.c5 - L;
+    const uint64_t x = lc(L), y = lc(R);
+    return BlockD{OP_UNION, (uint32_t)L, (uint32_t)R, L == R ? 1u : 0u, L < R ? x * y : (x ? x * (x - 1) / 2 : 0)};
+  }
+};
+
+// The inclusive prefix sum of v over the wave's lanes.
+__device__ __forceinline__ uint64_t wave_scan(uint64_t v) {
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const uint64_t o = __shfl_up((unsigned long long)v, off, kWave);
+    if ((int)lane_id() >= off) v += o;
+  }
+  return v;
+}
+
 // Decodes level index e of level c into its constructor and operands (rows),
-// walking the level's blocks in enumeration order (Q, S, C by left cost, U by
-// left cost); the counts of levels below c are final.  lstart and lcount are
-// the workgroup's level tables in LDS.
+// the level's blocks a lane each.  Called by a whole wave, every lane gets the
+// answer.  lstart and lcount are the workgroup's level tables in LDS.
 __device__ __forceinline__ bool decode_index(const BatchDesc& d, const uint64_t* lstart, const uint64_t* lcount,
                                              uint32_t c, uint64_t e, uint32_t* op, uint64_t* a, uint64_t* b) {
-  const int64_t c1 = d.c1, cc = c;
-  auto lc = [&](int64_t k) -> uint64_t { return (k >= c1 && k < cc) ? lcount[k] : 0ull; };
-  *b = 0;
-  if (cc == c1) {
-    *op = OP_CHAR;
-    *a = e;
-    return e < d.nsigma;
-  }
-  uint64_t n = lc(cc - d.c2);
-  if (e < n) {
-    *op = OP_QUESTION;
-    *a = lstart[cc - d.c2] + e;
-    return true;
-  }
-  e -= n;
-  n = lc(cc - d.c3);
-  if (e < n) {
-    *op = OP_STAR;
-    *a = lstart[cc - d.c3] + e;
-    return true;
-  }
-  e -= n;
-  for (int64_t L = c1; cc - (int64_t)d.c4 - L >= c1; ++L) {
-    const int64_t R = cc - d.c4 - L;
-    n = lc(L) * lc(R);
-    if (e < n) {
-      *op = OP_CONCAT;
-      *a = lstart[L] + e / lc(R);
-      *b = lstart[R] + e % lc(R);
-      return true;
-    }
-    e -= n;
-  }
-  for (int64_t L = c1; L <= cc - (int64_t)d.c5 - L; ++L) {
-    const int64_t R = cc - d.c5 - L;
-    const uint64_t x = lc(L), y = lc(R);
-    n = (L < R) ? x * y : (x ? x * (x - 1) / 2 : 0);
-    if (e < n) {
-      *op = OP_UNION;
-      if (L == R) {
-        uint64_t i = 0, j = 0;
-        tri_decode(e, x, &i, &j);
-        *a = lstart[L] + i;
-        *b = lstart[L] + j;
-      } else {
-        *a = lstart[L] + e / y;
-        *b = lstart[R] + e % y;
+  const BlockList bl(d, lcount, c);
+  const int32_t n = bl.count();
+  uint64_t run = 0;
+  for (int32_t k0 = 0; k0 < n; k0 += 64) {
+    const BlockD blk = bl.get(k0 + (int32_t)lane_id());
+    const uint64_t end = run + wave_scan(blk.count), first = end - blk.count;
+    const uint64_t hit = __ballot(e >= first && e < end);
+    if (hit) {
+      const int at = __ffsll((unsigned long long)hit) - 1;
+      const uint64_t r = e - __shfl((unsigned long long)first, at, kWave);
+      const uint32_t L = (uint32_t)__shfl((int)blk.L, at, kWave), R = (uint32_t)__shfl((int)blk.R, at, kWave);
+      *op = (uint32_t)__shfl((int)blk.op, at, kWave);
+      const uint64_t rc = lcount[R];
+      uint64_t i = r, j = 0;
+      if (*op == OP_UNION && L == R)
+        tri_decode(r, lcount[L], &i, &j);
+      else if (*op == OP_CONCAT || *op == OP_UNION) {
+        i = r / rc;
+        j = r - i * rc;
       }
+      *a = *op == OP_CHAR ? r : lstart[L] + i;
+      *b = *op == OP_CONCAT || *op == OP_UNION ? lstart[R] + j : 0;
       return true;
     }
-    e -= n;
+    run = __shfl((unsigned long long)end, kWave - 1, kWave);
   }
   return false;
 }
@@ -387,38 +401,14 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
   const long long t_start = wall_clock64();
   for (uint32_t c = d.c1; c <= d.max_cost && s_stop == STOP_NONE; ++c) {
     if (wave == 0) {
-      // constructor blocks of level c, in enumeration order, one per lane:
-      // characters, or r?, r*, r.s by left cost, r+s by left cost
-      auto lc = [&](int64_t k) -> uint64_t { return (k >= (int64_t)d.c1 && k < (int64_t)c) ? s_lcount[k] : 0ull; };
-      const int64_t cc = c, c1 = d.c1;
-      const int32_t n_cat = c == d.c1 ? 0 : (int32_t)max((int64_t)0, cc - (int64_t)d.c4 - 2 * c1 + 1);
-      const int32_t n_uni = c == d.c1 ? 0 : (int32_t)max((int64_t)0, (cc - (int64_t)d.c5 >= 0 ? (cc - (int64_t)d.c5) / 2 : -1) - c1 + 1);
-      const int32_t n_all = 2 + n_cat + n_uni;  // (at c1: the characters and nothing)
+      // constructor blocks of level c, in enumeration order, one per lane
+      const BlockList bl(d, s_lcount, c);
+      const int32_t n_all = bl.count();
       uint32_t nb = 0;
       uint64_t run = 0, thr[4] = {0, 0, 0, 0};
       for (int32_t k0 = 0; k0 < n_all; k0 += 64) {
-        const int32_t k = k0 + (int32_t)lane;
-        BlockD b{0, 0, 0, 0, 0};
-        if (c == d.c1) {
-          if (k == 0) b = BlockD{OP_CHAR, 0, 0, 0, (uint64_t)d.nsigma};
-        } else if (k == 0) {
-          b = BlockD{OP_QUESTION, (uint32_t)(cc - d.c2), 0, 0, lc(cc - d.c2)};
-        } else if (k == 1) {
-          b = BlockD{OP_STAR, (uint32_t)(cc - d.c3), 0, 0, lc(cc - d.c3)};
-        } else if (k < 2 + n_cat) {
-          const int64_t L = c1 + (k - 2), R = cc - d.c4 - L;
-          b = BlockD{OP_CONCAT, (uint32_t)L, (uint32_t)R, 0, lc(L) * lc(R)};
-        } else if (k < n_all) {
-          const int64_t L = c1 + (k - 2 - n_cat), R = cc - d.c5 - L;
-          const uint64_t x = lc(L), y = lc(R);
-          b = BlockD{OP_UNION, (uint32_t)L, (uint32_t)R, L == R ? 1u : 0u, L < R ? x * y : (x ? x * (x - 1) / 2 : 0)};
-        }
-        uint64_t incl = b.count;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-          const uint64_t v = __shfl_up((unsigned long long)incl, off, kWave);
-          if ((int)lane >= off) incl += v;
-        }
+        const BlockD b = bl.get(k0 + (int32_t)lane);
+        const uint64_t incl = wave_scan(b.count);
         const uint64_t some = __ballot(b.count != 0);
         if (b.count) {
           const uint32_t at = nb + (uint32_t)__popcll(some & ((1ull << lane) - 1));
@@ -841,12 +831,12 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
   }
 
   // ---- results, written straight to the instance's host-visible buffers
-  if (tid == 0) {
+  if (wave == 0) {
     // The answer's expression tree (A12): the answer candidate, then every
     // stored row below it, each decoded from its back-pointer (level index)
-    // with the block structure of its level.  Trees have at most one node
-    // per unit of cost; a count of 0 tells the host to decode from the
-    // back-pointers itself.
+    // with the block structure of its level, by one wave.  Trees have at most
+    // one node per unit of cost; a count of 0 tells the host to decode from
+    // the back-pointers itself.
     uint32_t k = 0;
     if (s_stop == STOP_ANSWER) {
       uint64_t* stk = s_tile[0];  // free after the search
@@ -859,35 +849,43 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
           ok = false;
           return;
         }
-        uint64_t* o = d.htree + 1 + 4 * k++;
-        o[0] = row;
-        o[1] = op;
-        o[2] = a;
-        o[3] = b;
-        if (op != OP_CHAR) stk[sp++] = a;
-        if (op == OP_CONCAT || op == OP_UNION) stk[sp++] = b;
+        if (lane == 0) {
+          uint64_t* o = d.htree + 1 + 4 * k;
+          o[0] = row;
+          o[1] = op;
+          o[2] = a;
+          o[3] = b;
+          if (op != OP_CHAR) stk[sp] = a;
+          if (op == OP_CONCAT || op == OP_UNION) stk[sp + 1] = b;
+        }
+        ++k;
+        if (op != OP_CHAR) ++sp;
+        if (op == OP_CONCAT || op == OP_UNION) ++sp;
+        wave_sync_lds();
       };
-      node(~0ull, ans_cost, ans_e);
+      node(~0ull, (uint32_t)__shfl((int)ans_cost, 0, kWave), __shfl((unsigned long long)ans_e, 0, kWave));
       while (ok && sp) {
         const uint64_t row = stk[--sp];
-        uint32_t rc = 0;
-        for (uint32_t c = d.c1; c <= d.max_cost; ++c)
-          if (row >= s_lstart[c] && row < s_lstart[c] + s_lcount[c]) rc = c;
-        if (!rc) {
+        const bool mine = lane >= d.c1 && lane <= d.max_cost && row >= s_lstart[lane] &&
+                          row < s_lstart[lane] + s_lcount[lane];
+        const uint64_t at = __ballot(mine);
+        if (!at) {
           ok = false;
           break;
         }
-        node(row, rc, d.aux[row]);
+        node(row, (uint32_t)__ffsll((unsigned long long)at) - 1, d.aux[row]);
       }
       if (!ok) k = 0;
     }
-    d.htree[0] = k;
-    d.hst->total_rows = s_total;
-    d.hst->row_cap = d.row_cap;
-    d.hst->stop = s_stop;
-    d.hst->answer_cost = ans_cost;
-    d.hst->answer_e = ans_e;
-    d.hst->resume_level = s_resume;
+    if (lane == 0) {
+      d.htree[0] = k;
+      d.hst->total_rows = s_total;
+      d.hst->row_cap = d.row_cap;
+      d.hst->stop = s_stop;
+      d.hst->answer_cost = ans_cost;
+      d.hst->answer_e = ans_e;
+      d.hst->resume_level = s_resume;
+    }
   }
   const uint32_t L = d.max_cost + 2;
   for (uint32_t i = tid; i < L; i += kT) {

@@ -1280,12 +1280,22 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     hs->answer_cost = 0;
     hs->answer_e = 0;
     hs->resume_level = 0;
+    hs->otf_on = in->otf_on ? 1u : 0u;
+    hs->otf = 0;
     hs->chunks = 0;
-    LAUNCH(in, s, REI_K_OTHER, 1, launch_search_reset(ra, s));
-    HIP_OK(in, hipMemcpyAsync(in->d_state, hs, sizeof(DevState), hipMemcpyHostToDevice, s));
-    HIP_OK(in, hipMemcpyAsync(in->d_levels, in->h_levels, 3 * L * 8, hipMemcpyHostToDevice, s));
     // the batched solver used a prefix of the table: rebuild it at full size
-    if ((r = ensure_table(in, in->known_rows + 1024, s, true)) != REI_OK) return r;
+    if (in->slots_cap < 2 * (in->known_rows + 1024) &&
+        (r = table_alloc(in, pow2_at_least(4 * (in->known_rows + 1024)))) != REI_OK)
+      return r;
+    ra.total_rows = in->known_rows;
+    ra.levels = in->d_levels;
+    ra.levels_src = in->v_levels;
+    ra.n_levels = 3 * L;
+    ra.slots = in->d_slots;
+    ra.n_slot_words = in->slots_cap * (slot_bytes(in) / 8);
+    LAUNCH(in, s, REI_K_OTHER, ra.n_slot_words, launch_search_reset(ra, s));
+    LAUNCH(in, s, REI_K_OTHER, in->known_rows,
+           launch_rehash(in->st.W, in->inl, in->d_rows, in->known_rows, in->d_slots, in->slots_cap - 1, s));
   } else {
     // a fresh search: nothing stored yet (also when a batched attempt ran out
     // of its preallocated rows and left some behind)
@@ -1387,12 +1397,16 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
   return REI_OK;
 }
 
+rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete);
+
 rei_status solve_impl(rei_instance* in, hipStream_t s, rei_result* out) {
   const double t0 = now_s();
   HIP_OK(in, hipSetDevice(in->device));
   rei_status r;
   if (!begin_solve(in, t0)) {
-    if ((r = search_levels(in, s)) != REI_OK) return r;
+    bool complete = false;
+    if ((r = first_levels(in, s, &complete)) != REI_OK) return r;
+    if (!complete && (r = search_levels(in, s)) != REI_OK) return r;
     if ((r = finish_solve(in, t0)) != REI_OK) return r;
   }
   *out = in->res;
@@ -1759,6 +1773,80 @@ bool batch_take_state(rei_instance* in) {
     return true;
   }
   return false;
+}
+
+// The first levels of a search by rei_solve on one workgroup: a level of a
+// few hundred candidates takes it 10-15 us, where the per-chunk path's chain
+// of three launches and a wait at the level's end takes 30 us.  A level of
+// more than kFirstLevelMax candidates, wider languages, and what the
+// one-workgroup solver cannot do go to the per-chunk path, which continues
+// from the rows stored.  *complete: the search ended here.
+#ifndef REI_FIRST_LEVEL_MAX
+#define REI_FIRST_LEVEL_MAX 4096
+#endif
+constexpr uint64_t kFirstLevelMax = REI_FIRST_LEVEL_MAX;
+constexpr int kFirstLevelsMaxW = 4;
+constexpr uint64_t kFirstRows = 1ull << 15;
+rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
+  *complete = false;
+  const uint32_t cap = std::min(in->max_cost, kBatchMaxCost);
+  bool same_char_cost = true;
+  for (uint32_t ca : in->char_cost) same_char_cost = same_char_cost && ca == in->costs.c_char;
+  // (a chunk size set by the caller, and profiling, ask for the per-chunk path)
+  if (in->st.W > kFirstLevelsMaxW || in->st.gt_pair.size() > batch_max_pairs(in->st.W) || !same_char_cost ||
+      in->costs.c_char > cap || in->prof || in->chunk_max != kDefaultChunk)
+    return REI_OK;
+  rei_status r;
+  const uint64_t R = std::max<uint64_t>(1024, std::min(in->row_cap, kFirstRows));
+  if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, s)) != REI_OK) return r;
+  if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
+  // (the solver clears the part of the table it uses)
+  const uint64_t entries = 2 * (kFirstRows + kBatchChunk);
+  if (in->slots_cap < entries && (r = table_alloc(in, pow2_at_least(entries))) != REI_OK) return r;
+  DescBuf db;
+  if ((r = desc_acquire(in, 1, &db)) != REI_OK) return r;
+  BatchDesc d = make_desc(in);
+  d.max_cost = cap;
+  d.level_max = kFirstLevelMax;
+  d.time_ticks = 0;
+  // rows beyond these would not fit the table's share
+  d.rows_alloc = std::min<uint64_t>(in->rows_alloc, std::max<uint64_t>(kFirstRows, R));
+  *db.h = d;
+  __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
+  const hipError_t e =
+      launch_solve_batch(in->st.W, in->inl, batch_max_threads(in->st.W), db.d, 1, s);
+  hipError_t w = hipSuccess;
+  if (e == hipSuccess) {
+    // the flag is the launch's last store
+    const double t0 = now_s();
+    while (!__atomic_load_n(&in->h_state->done, __ATOMIC_ACQUIRE))
+      if ((now_s() - t0) * 1e6 > kSpinUs) {
+        w = hipStreamSynchronize(s);
+        break;
+      }
+  }
+  {
+    std::lock_guard<std::mutex> g(g_pool_mu);
+    g_desc_free.push_back(db);
+  }
+  HIP_OK(in, e);
+  HIP_OK(in, w);
+  const uint64_t L = in->max_cost + 2, l = cap + 2;
+  if (L != l) {  // the solver's counters have its own bound's stride
+    uint64_t* h = in->h_levels;
+    for (int k = 2; k >= 0; --k) {
+      std::memmove(h + k * L, h + k * l, l * 8);
+      std::memset(h + k * L + l, 0, (L - l) * 8);
+    }
+  }
+  DevState* hs = in->h_state;
+  if (hs->stop == STOP_NONE && cap < in->max_cost) {  // higher levels than the solver has
+    hs->stop = STOP_HANDOFF;
+    hs->resume_level = cap + 1;
+  }
+  if (hs->stop == STOP_OOM && in->otf_on) hs->stop = STOP_CAPACITY;  // goes on without storing: from the start
+  *complete = !batch_take_state(in);
+  return REI_OK;
 }
 
 // The batched launches' event pairs go into the statistics of insts[0];

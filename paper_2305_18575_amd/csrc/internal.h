@@ -231,15 +231,17 @@ struct TreeArgs {
   uint32_t ccost[kTreeMaxChars];  // character costs in enumeration order
 };
 hipError_t launch_decode_tree(const TreeArgs& t, hipStream_t s);
-// Start of a per-chunk search, one launch: state and control block reset,
-// level counters to zero, the table's words to EMPTY, both winner bitmaps'
-// used words to zero (any count may be 0).
+// Start of a per-chunk search, one launch: state and control block reset
+// (total_rows rows stored), level counters to zero or to levels_src (host-
+// visible), the table's words to EMPTY, both winner bitmaps' used words to
+// zero (any count may be 0).
 struct ResetArgs {
   Ctrl* ctrl;
   DevState* st;
-  uint64_t row_cap;
+  uint64_t row_cap, total_rows;
   uint32_t otf_on;
   uint64_t* levels;
+  const uint64_t* levels_src;
   uint64_t n_levels;
   uint64_t* slots;
   uint64_t n_slot_words;

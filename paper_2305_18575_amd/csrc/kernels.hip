@@ -734,7 +734,7 @@ __global__ __launch_bounds__(256) void search_reset(ResetArgs a) {
   if (t == 0) {
     ctrl_clear(a.ctrl);
     DevState* st = a.st;
-    st->total_rows = 0;
+    st->total_rows = a.total_rows;
     st->row_cap = a.row_cap;
     st->stop = STOP_NONE;
     st->answer_cost = 0;
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(256) void search_reset(ResetArgs a) {
     st->otf = 0;
     st->chunks = 0;
   }
-  for (uint64_t i = t; i < a.n_levels; i += n) a.levels[i] = 0;
+  for (uint64_t i = t; i < a.n_levels; i += n) a.levels[i] = a.levels_src ? a.levels_src[i] : 0;
   for (uint64_t i = t; i < a.n_slot_words; i += n) a.slots[i] = kEmpty;
   for (int b = 0; b < 2; ++b)
     for (uint64_t i = t; i < a.bitmap_words[b]; i += n) a.bitmap[b][i] = 0;
