@@ -339,7 +339,10 @@ rei_status rei_trim(rei_instance *inst);
 rei_status rei_set_allocator(void *(*alloc)(size_t bytes, void *ctx),
                              void (*free_)(void *ptr, void *ctx), void *ctx);
 
-/* Free the instance and its device memory.  NULL is ignored. */
+/* Free the instance and its device memory (up to 64 MB of small device blocks
+ * and 4 MB of pinned host memory stay with the process for the next
+ * instances; rei_trim gives idle ones back).  Waits for the device.  NULL is
+ * ignored. */
 void rei_destroy(rei_instance *inst);
 
 const char *rei_status_str(rei_status s);

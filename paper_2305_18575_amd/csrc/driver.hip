@@ -112,7 +112,9 @@ struct rei_instance {
   double t_seen = -1;  // seconds into a batched call when its completion flag showed
   double seconds_stage = 0;
 
-  // staged tables on the device
+  // staged tables on the device, all in the block d_tables with d_ctrl,
+  // d_state and d_levels
+  char* d_tables = nullptr;
   uint32_t* d_gt_off = nullptr;
   uint32_t* d_gt_pair = nullptr;
   uint32_t* d_len_off = nullptr;
@@ -224,6 +226,101 @@ namespace {
     }                                                                                  \
   } while (0)
 
+// Idle blocks of destroyed instances, kept for new ones: a solve that is asked
+// once (created, solved, destroyed) otherwise spends most of its time
+// allocating.  Pinned host blocks above all (34-120 us to allocate, 60-160 us
+// to free, three per instance before; 64 KB at most each, 4 MB kept), and
+// device blocks of up to 4 MB (16 us, 7 us to free; 64 MB kept per process).
+// A block comes here only when no work that uses it is left (rei_destroy
+// waits for the device as a free would), so any stream may take it.
+// Beyond the bounds blocks are freed; rei_trim gives all idle ones back.
+// Thread-safe; never destroyed (the process's end frees it).
+class BlockPool {
+ public:
+  static BlockPool& get() {
+    static BlockPool* p = new BlockPool();
+    return *p;
+  }
+  hipError_t take(int device, bool host, size_t bytes, void** out) {
+    const size_t cls = size_class_of(bytes);
+    if (cls <= most(host)) {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto it = idle_.find({device, host, cls});
+      if (it != idle_.end() && !it->second.empty()) {
+        *out = it->second.back();
+        it->second.pop_back();
+        kept_[host] -= cls;
+        lent_[*out] = cls;
+        return hipSuccess;
+      }
+    }
+    const size_t n = cls <= most(host) ? cls : bytes;
+    hipError_t e = fresh(host, n, out);
+    if (e != hipSuccess) {  // idle blocks may be what is missing
+      (void)hipGetLastError();
+      give_back();
+      e = fresh(host, n, out);
+    }
+    if (e == hipSuccess && cls <= most(host)) {
+      std::lock_guard<std::mutex> lk(mu_);
+      lent_[*out] = cls;
+    }
+    return e;
+  }
+  void put(int device, bool host, void* p) {
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      auto it = lent_.find(p);
+      if (it != lent_.end()) {
+        const size_t cls = it->second;
+        lent_.erase(it);
+        if (kept_[host] + cls <= bound(host)) {
+          idle_[{device, host, cls}].push_back(p);
+          kept_[host] += cls;
+          return;
+        }
+      }
+    }
+    release(host, p);
+  }
+  // Frees every idle block.
+  void give_back() {
+    std::map<std::tuple<int, bool, size_t>, std::vector<void*>> all;
+    {
+      std::lock_guard<std::mutex> lk(mu_);
+      all.swap(idle_);
+      kept_[0] = kept_[1] = 0;
+    }
+    for (auto& x : all)
+      for (void* p : x.second) release(std::get<1>(x.first), p);
+  }
+
+ private:
+  static size_t most(bool host) { return host ? 64u << 10 : 4u << 20; }
+  static size_t bound(bool host) { return host ? 4u << 20 : 64u << 20; }
+  static size_t size_class_of(size_t bytes) {
+    size_t c = 4096;
+    while (c < bytes) c <<= 1;
+    return c;
+  }
+  static hipError_t fresh(bool host, size_t n, void** out) {
+    // host: coherent (fine-grained), as the host reads flags and counters
+    // in it while launches that write them still run
+    return host ? hipHostMalloc(out, n, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent)
+                : hipMalloc(out, n);
+  }
+  static void release(bool host, void* p) {
+    if (host)
+      (void)hipHostFree(p);
+    else
+      (void)hipFree(p);
+  }
+  std::mutex mu_;
+  std::map<std::tuple<int, bool, size_t>, std::vector<void*>> idle_;
+  std::unordered_map<void*, size_t> lent_;  // size class of each block of a class that is in use
+  size_t kept_[2] = {0, 0};
+};
+
 // A caller's allocator may order its reuse of memory by some stream of its
 // own, which the library's streams do not follow: the device is drained after
 // taking memory from it and before handing memory back, as hipMalloc and
@@ -235,9 +332,10 @@ hipError_t dev_alloc(const rei_instance* in, T** p, size_t bytes) {
     if (!*p) return hipErrorOutOfMemory;
     return hipDeviceSynchronize();
   }
-  return hipMalloc(p, bytes);
+  return BlockPool::get().take(in->device, false, bytes, (void**)p);
 }
 
+// (no work that uses the block may be left)
 template <class T>
 void dfree(const rei_instance* in, T*& p) {
   if (p) {
@@ -245,11 +343,14 @@ void dfree(const rei_instance* in, T*& p) {
       (void)hipDeviceSynchronize();
       in->alloc.free_((void*)p, in->alloc.ctx);
     } else {
-      (void)hipFree(p);
+      BlockPool::get().put(in->device, false, (void*)p);
     }
   }
   p = nullptr;
 }
+
+// Bytes rounded up, so that what follows in a shared block is aligned.
+uint64_t aligned(uint64_t bytes) { return (bytes + 255) & ~255ull; }
 
 // Grid-path launch parameters by word width, from rei_tune_grid or a tuning
 // file; widths without an entry use GridTune's defaults.
@@ -344,21 +445,16 @@ rei_status ensure_rows(rei_instance* in, uint64_t need, hipStream_t s) {
   if (need <= in->rows_alloc) return REI_OK;
   uint64_t cap = std::max<uint64_t>({need, 2 * in->rows_alloc, 1024});
   const int W = in->st.W;
+  // one block: rows, then back-pointers
   uint64_t* nr = nullptr;
-  uint64_t* na = nullptr;
-  HIP_OK(in, dev_alloc(in, &nr, cap * W * 8));
-  if (dev_alloc(in, &na, cap * 8) != hipSuccess) {
-    dfree(in, nr);
-    in->err = "hipMalloc of the back-pointer array failed";
-    return REI_ERR_DEVICE;
-  }
+  HIP_OK(in, dev_alloc(in, &nr, aligned(cap * W * 8) + cap * 8));
+  uint64_t* na = nr + aligned(cap * W * 8) / 8;
   if (in->known_rows) {
     HIP_OK(in, hipMemcpyAsync(nr, in->d_rows, in->known_rows * W * 8, hipMemcpyDeviceToDevice, s));
     HIP_OK(in, hipMemcpyAsync(na, in->d_aux, in->known_rows * 8, hipMemcpyDeviceToDevice, s));
   }
   HIP_OK(in, hipStreamSynchronize(s));
   dfree(in, in->d_rows);
-  dfree(in, in->d_aux);
   in->d_rows = nr;
   in->d_aux = na;
   in->rows_alloc = cap;
@@ -390,18 +486,29 @@ rei_status ensure_table(rei_instance* in, uint64_t entries, hipStream_t s, bool 
   return REI_OK;
 }
 
-// slots: survivor slots; len: candidates (bitmap bits); regions: survivor ranges.
-rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, uint64_t regions, hipStream_t s) {
+// slots: survivor slots; len: candidates (bitmap bits); regions: survivor
+// ranges.  ahead: buffers that have to grow become this many times larger
+// than asked for (the chunks of a level double in size; each growth waits for
+// the stream, and blocks of 16 MB and more take 0.1 ms to allocate and 0.3 ms
+// to free), if that much memory is there.
+rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, uint64_t regions, hipStream_t s,
+                                uint64_t ahead = 1) {
   const int W = in->st.W;
   if (slots > in->surv_cap) {
     dfree(in, in->d_skey);
-    dfree(in, in->d_se);
-    dfree(in, in->d_spos);
     in->surv_cap = 0;
-    HIP_OK(in, dev_alloc(in, &in->d_skey, slots * W * 8));
-    HIP_OK(in, dev_alloc(in, &in->d_se, slots * 4));
-    HIP_OK(in, dev_alloc(in, &in->d_spos, slots * 8));
-    in->surv_cap = slots;
+    uint64_t n = std::max(slots * ahead, ahead > 1 || slots > kBatchChunk ? slots + slots / 8 : slots);
+    // one block: keys, slot records, indices
+    auto bytes = [&](uint64_t k) { return aligned(k * W * 8) + aligned(k * 8) + k * 4; };
+    if (n > slots && dev_alloc(in, &in->d_skey, bytes(n)) != hipSuccess) {
+      (void)hipGetLastError();
+      in->d_skey = nullptr;
+      n = slots;
+    }
+    if (!in->d_skey) HIP_OK(in, dev_alloc(in, &in->d_skey, bytes(n)));
+    in->d_spos = in->d_skey + aligned(n * W * 8) / 8;
+    in->d_se = (uint32_t*)(in->d_spos + aligned(n * 8) / 8);
+    in->surv_cap = n;
   }
   if (regions > in->reg_cap) {
     dfree(in, in->d_reg);
@@ -410,16 +517,15 @@ rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, 
     HIP_OK(in, dev_alloc(in, &in->d_reg, cap * sizeof(uint2)));
     in->reg_cap = cap;
   }
-  const uint64_t words = (len + 31) / 32;
-  if (words > in->bitmap_cap) {
+  if ((len + 31) / 32 > in->bitmap_cap) {
+    const uint64_t words = (len + 31) / 32 * ahead;
     dfree(in, in->d_bitmap);
-    dfree(in, in->d_prefix);
-    dfree(in, in->d_bsums);
     in->bitmap_cap = 0;
     in->bm_dirty[0] = in->bm_dirty[1] = in->bm_high = 0;
-    HIP_OK(in, dev_alloc(in, &in->d_bitmap, words * 8));  // both
-    HIP_OK(in, dev_alloc(in, &in->d_prefix, words * 4));
-    HIP_OK(in, dev_alloc(in, &in->d_bsums, ((words + 1023) / 1024 + 1) * 4));
+    // one block: both bitmaps, prefix counts, block sums
+    HIP_OK(in, dev_alloc(in, &in->d_bitmap, words * 8 + words * 4 + ((words + 1023) / 1024 + 1) * 4));
+    in->d_prefix = in->d_bitmap + 2 * words;
+    in->d_bsums = in->d_prefix + words;
     in->bitmap_cap = words;
     LAUNCH(in, s, REI_K_OTHER, words, launch_fill((uint64_t*)in->d_bitmap, words, 0, s));
   }
@@ -862,7 +968,9 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
     if (otf_level) {
       if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions, s)) != REI_OK) return r;
     } else {
-      if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s)) != REI_OK) return r;
+      const uint64_t most = std::max(len, std::min(in->chunk_max, grid_params(in).chunk_max));
+      const uint64_t ahead = std::min<uint64_t>(4, std::max<uint64_t>(1, most / len));
+      if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s, ahead)) != REI_OK) return r;
       if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + generated), s)) != REI_OK) return r;
       if ((r = ensure_table(in, in->known_rows + generated, s, false)) != REI_OK) return r;
     }
@@ -2001,15 +2109,15 @@ class GridPool {
 void free_search_buffers(rei_instance* in) {
   (void)hipSetDevice(in->device);
   dfree(in, in->d_rows);
-  dfree(in, in->d_aux);
   dfree(in, in->d_slots);
   dfree(in, in->d_skey);
-  dfree(in, in->d_se);
-  dfree(in, in->d_spos);
   dfree(in, in->d_reg);
   dfree(in, in->d_bitmap);
-  dfree(in, in->d_prefix);
-  dfree(in, in->d_bsums);
+  in->d_aux = nullptr;
+  in->d_se = nullptr;
+  in->d_spos = nullptr;
+  in->d_prefix = nullptr;
+  in->d_bsums = nullptr;
   in->rows_alloc = 0;
   in->slots_cap = 0;
   in->surv_cap = 0;
@@ -2022,28 +2130,10 @@ void free_search_buffers(rei_instance* in) {
 
 void free_device(rei_instance* in) {
   (void)hipSetDevice(in->device);
-  dfree(in, in->d_gt_off);
-  dfree(in, in->d_gt_pair);
-  dfree(in, in->d_len_off);
-  dfree(in, in->d_pmask);
-  dfree(in, in->d_nmask);
-  dfree(in, in->d_char_index);
-  dfree(in, in->d_rows);
-  dfree(in, in->d_aux);
-  dfree(in, in->d_slots);
-  dfree(in, in->d_skey);
-  dfree(in, in->d_se);
-  dfree(in, in->d_spos);
-  dfree(in, in->d_reg);
-  dfree(in, in->d_bitmap);
-  dfree(in, in->d_prefix);
-  dfree(in, in->d_bsums);
-  dfree(in, in->d_ctrl);
-  dfree(in, in->d_state);
-  dfree(in, in->d_levels);
-  if (in->h_state) (void)hipHostFree(in->h_state);
-  if (in->h_levels) (void)hipHostFree(in->h_levels);
-  if (in->h_tree) (void)hipHostFree(in->h_tree);
+  (void)hipDeviceSynchronize();  // blocks may be lent again at once
+  free_search_buffers(in);
+  dfree(in, in->d_tables);
+  if (in->h_state) BlockPool::get().put(in->device, true, in->h_state);
   in->h_state = nullptr;
   in->h_levels = nullptr;
   in->h_tree = nullptr;
@@ -2057,41 +2147,65 @@ void free_device(rei_instance* in) {
   in->pool.clear();
 }
 
-template <class T>
-rei_status upload(rei_instance* in, T** dst, const std::vector<T>& src) {
-  const size_t bytes = std::max<size_t>(1, src.size()) * sizeof(T);
-  HIP_OK(in, dev_alloc(in, dst, bytes));
-  if (!src.empty()) HIP_OK(in, hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
-  return REI_OK;
-}
-
+// The staged tables in one device block (copied from one pinned block), with
+// the control block, the state and the level counters behind them; the host
+// mirrors in one pinned block.
 rei_status create_device(rei_instance* in) {
   HIP_OK(in, hipGetDevice(&in->device));
-  rei_status r;
-  if ((r = upload(in, &in->d_gt_off, in->st.gt_off)) != REI_OK) return r;
-  if ((r = upload(in, &in->d_gt_pair, in->st.gt_pair)) != REI_OK) return r;
-  if ((r = upload(in, &in->d_len_off, in->st.len_off)) != REI_OK) return r;
-  if ((r = upload(in, &in->d_pmask, in->st.pmask)) != REI_OK) return r;
-  if ((r = upload(in, &in->d_nmask, in->st.nmask)) != REI_OK) return r;
   in->char_order.resize(in->st.sigma.size());
   for (uint32_t a = 0; a < in->char_order.size(); ++a) in->char_order[a] = a;
-  if ((r = upload(in, &in->d_char_index, in->st.char_index)) != REI_OK) return r;
-  HIP_OK(in, dev_alloc(in, &in->d_ctrl, sizeof(Ctrl)));
-  HIP_OK(in, dev_alloc(in, &in->d_state, sizeof(DevState)));
   const uint64_t L = in->max_cost + 2;
-  HIP_OK(in, dev_alloc(in, &in->d_levels, 3 * L * 8));
-  // coherent (fine-grained): the batched solver's completion flag is read
-  // by the host while the launch still runs
-  const unsigned fl = hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent;
-  HIP_OK(in, hipHostMalloc((void**)&in->h_state, sizeof(DevState), fl));
-  HIP_OK(in, hipHostMalloc((void**)&in->h_levels, 3 * L * 8, fl));
-  HIP_OK(in, hipHostMalloc((void**)&in->h_tree, (1 + 4 * kBatchTreeNodes + kMaxMarks + 1) * 8, fl));
-  in->h_tree[0] = 0;
+  uint64_t at = 0;
+  auto place = [&](uint64_t bytes) {
+    const uint64_t here = at;
+    at += aligned(std::max<uint64_t>(bytes, 1));
+    return here;
+  };
+  const Staged& st = in->st;
+  struct Part {
+    const void* src;
+    uint64_t bytes, off;
+  } parts[] = {{st.gt_off.data(), st.gt_off.size() * 4, 0},   {st.gt_pair.data(), st.gt_pair.size() * 4, 0},
+               {st.len_off.data(), st.len_off.size() * 4, 0}, {st.pmask.data(), st.pmask.size() * 8, 0},
+               {st.nmask.data(), st.nmask.size() * 8, 0},     {st.char_index.data(), st.char_index.size() * 4, 0}};
+  for (Part& p : parts) p.off = place(p.bytes);
+  const uint64_t copied = at;
+  const uint64_t o_ctrl = place(sizeof(Ctrl)), o_state = place(sizeof(DevState)), o_levels = place(3 * L * 8);
+  HIP_OK(in, dev_alloc(in, &in->d_tables, at));
+  char* base = in->d_tables;
+  in->d_gt_off = (uint32_t*)(base + parts[0].off);
+  in->d_gt_pair = (uint32_t*)(base + parts[1].off);
+  in->d_len_off = (uint32_t*)(base + parts[2].off);
+  in->d_pmask = (uint64_t*)(base + parts[3].off);
+  in->d_nmask = (uint64_t*)(base + parts[4].off);
+  in->d_char_index = (int32_t*)(base + parts[5].off);
+  in->d_ctrl = (Ctrl*)(base + o_ctrl);
+  in->d_state = (DevState*)(base + o_state);
+  in->d_levels = (uint64_t*)(base + o_levels);
+  {
+    void* stage = nullptr;
+    HIP_OK(in, BlockPool::get().take(in->device, true, copied, &stage));
+    for (const Part& p : parts)
+      if (p.bytes) std::memcpy((char*)stage + p.off, p.src, p.bytes);
+    const hipError_t e = hipMemcpy(base, stage, copied, hipMemcpyHostToDevice);
+    BlockPool::get().put(in->device, true, stage);
+    HIP_OK(in, e);
+  }
+  const uint64_t h_levels = aligned(sizeof(DevState)), h_tree = h_levels + aligned(3 * L * 8);
+  void* h = nullptr;
+  HIP_OK(in, BlockPool::get().take(in->device, true, h_tree + (1 + 4 * kBatchTreeNodes + kMaxMarks + 1) * 8, &h));
+  in->h_state = (DevState*)h;
+  in->h_levels = (uint64_t*)((char*)h + h_levels);
+  in->h_tree = (uint64_t*)((char*)h + h_tree);
   in->h_marks = in->h_tree + 1 + 4 * kBatchTreeNodes;
+  std::memset(h, 0, sizeof(DevState));
+  in->h_tree[0] = 0;
   in->h_marks[kMaxMarks] = 0;
-  HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_state, in->h_state, 0));
-  HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_levels, in->h_levels, 0));
-  HIP_OK(in, hipHostGetDevicePointer((void**)&in->v_tree, in->h_tree, 0));
+  void* v = nullptr;
+  HIP_OK(in, hipHostGetDevicePointer(&v, h, 0));
+  in->v_state = (DevState*)v;
+  in->v_levels = (uint64_t*)((char*)v + h_levels);
+  in->v_tree = (uint64_t*)((char*)v + h_tree);
   in->v_marks = in->v_tree + 1 + 4 * kBatchTreeNodes;
   return REI_OK;
 }
@@ -2831,6 +2945,7 @@ rei_status rei_trim(rei_instance* inst) {
   HIP_OK(inst, hipSetDevice(inst->device));
   HIP_OK(inst, hipDeviceSynchronize());
   free_search_buffers(inst);
+  BlockPool::get().give_back();
   // no rows left to inspect (the result's counts live in uniq / cand)
   std::fill(inst->lstart.begin(), inst->lstart.end(), 0);
   std::fill(inst->lcount.begin(), inst->lcount.end(), 0);
