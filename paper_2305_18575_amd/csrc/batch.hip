@@ -282,6 +282,8 @@ __device__ __forceinline__ bool decode_index(const BatchDesc& d, const uint64_t*
   return false;
 }
 
+constexpr int solver_waves(int W, uint32_t threads) { return W > 4 ? 1 : threads == 256 && W > 1 ? 3 : 4; }
+
 // kT threads per instance (256, 512 or 1024; at most batch_max_threads(W),
 // so that the per-wave operand tiles and the guide table fit the LDS):
 // many waves shorten one instance's search, few let more instances share a
@@ -299,8 +301,12 @@ __device__ __forceinline__ bool decode_index(const BatchDesc& d, const uint64_t*
 // leaves once it has waited qc->idle_ticks without finding a slot, or when
 // the host sets qc->closing; slots published after the last one left are
 // found unsolved by the host and published again in its next launch.
+// Registers: up to four words per language at most 128 (168 for 256 threads
+// beside a full guide table, where the LDS holds three workgroups), so that
+// two workgroups of 512 threads or three to four of 256 fit a compute unit
+// (left alone the compiler takes 180-220, and one or two fit).
 template <int W, bool kInl, uint32_t kT>
-__global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32_t n_inst, const uint32_t* order,
+__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves(W, kT)))) void solve_batch(const BatchDesc* descs, uint32_t n_inst, const uint32_t* order,
                                                   uint32_t* next, const QueueCtl* qc) {
   static_assert(kT >= kBatchChunk / 32 && kT <= batch_max_threads(W) && kT % 64 == 0, "one scan value per thread");
   constexpr uint32_t kIc = batch_max_ic(W), kPairs = batch_max_pairs(W);
@@ -328,6 +334,7 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
   __shared__ uint64_t s_uni[kWaves][W];
   __shared__ uint32_t s_gto[kIc + 1], s_gtp[kPairs], s_lo[kIc + 2];
   __shared__ uint32_t s_item;
+  __shared__ uint32_t s_desc[sizeof(BatchDesc) / 4];
 
   for (uint32_t pass = 0;; ++pass) {
   uint32_t item;
@@ -366,7 +373,22 @@ __global__ __launch_bounds__(kT) void solve_batch(const BatchDesc* descs, uint32
     if (item >= n_inst) return;
     if (order) item = order[item];
   }
-  const BatchDesc d = descs[item];
+  // The descriptor goes through LDS into scalar registers: its 90-odd words
+  // are the same for every lane, but loaded as a struct by an index the
+  // compiler cannot prove uniform they took that many vector registers (200 in
+  // all, 100 of them spilled in the 1024-thread forms: one workgroup per
+  // compute unit).
+  static_assert(sizeof(BatchDesc) % 4 == 0 && sizeof(BatchDesc) / 4 <= kT, "one word per thread");
+  if (threadIdx.x < sizeof(BatchDesc) / 4)
+    s_desc[threadIdx.x] = reinterpret_cast<const uint32_t*>(descs + item)[threadIdx.x];
+  __syncthreads();
+  BatchDesc d;
+  {
+    uint32_t w[sizeof(BatchDesc) / 4];
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(BatchDesc) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_desc[i]);
+    __builtin_memcpy(&d, w, sizeof(d));
+  }
   const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // The dedup table starts small and grows (cleared and rebuilt from the
   // stored rows) while rows accumulate, up to the arena's slot_mask: a

@@ -453,7 +453,7 @@ rei_status ensure_rows(rei_instance* in, uint64_t need, hipStream_t s) {
     HIP_OK(in, hipMemcpyAsync(nr, in->d_rows, in->known_rows * W * 8, hipMemcpyDeviceToDevice, s));
     HIP_OK(in, hipMemcpyAsync(na, in->d_aux, in->known_rows * 8, hipMemcpyDeviceToDevice, s));
   }
-  HIP_OK(in, hipStreamSynchronize(s));
+  if (in->known_rows) HIP_OK(in, hipStreamSynchronize(s));  // (else nothing uses the old rows)
   dfree(in, in->d_rows);
   in->d_rows = nr;
   in->d_aux = na;
@@ -474,10 +474,9 @@ rei_status table_alloc(rei_instance* in, uint64_t cap) {
 }
 
 // The table keeps its load at most 1/2: entries = stored rows + possible new ones.
-rei_status ensure_table(rei_instance* in, uint64_t entries, hipStream_t s, bool force) {
-  if (!force && in->slots_cap >= 2 * entries) return REI_OK;
+rei_status ensure_table(rei_instance* in, uint64_t entries, hipStream_t s) {
+  if (in->slots_cap >= 2 * entries) return REI_OK;
   uint64_t cap = std::max<uint64_t>(4096, pow2_at_least(4 * entries));
-  if (force && in->slots_cap >= cap) cap = in->slots_cap;
   rei_status r;
   if (cap != in->slots_cap && (r = table_alloc(in, cap)) != REI_OK) return r;
   LAUNCH(in, s, REI_K_OTHER, cap, launch_fill(in->d_slots, cap * (slot_bytes(in) / 8), kEmpty, s));
@@ -972,7 +971,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       const uint64_t ahead = std::min<uint64_t>(4, std::max<uint64_t>(1, most / len));
       if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s, ahead)) != REI_OK) return r;
       if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + generated), s)) != REI_OK) return r;
-      if ((r = ensure_table(in, in->known_rows + generated, s, false)) != REI_OK) return r;
+      if ((r = ensure_table(in, in->known_rows + generated, s)) != REI_OK) return r;
     }
   }
 
@@ -1628,8 +1627,9 @@ struct BatchRun {
 
 // ---- launch shape of the batched solver ---------------------------------
 // Threads per instance for a group of n instances of word width W: the
-// tuner's choice for this size class when there is one, else enough waves
-// per instance to fill the device's wave slots (32 per CU) with n instances.
+// tuner's choice for this size class when there is one, else the waves of
+// an instance's share of the device when `total` instances run at once (a
+// group at a time they would queue for compute units behind each other).
 std::mutex g_tune_mu;
 std::map<std::pair<int, int>, uint32_t> g_tuned;  // (group, size class) -> threads
 int g_cus = 0;
@@ -1642,6 +1642,9 @@ constexpr int kSlots = 7;
 std::atomic<uint64_t> g_level_max[kSlots];
 // Threads per instance forced on every group while the tuner times a shape.
 std::atomic<uint32_t> g_force_threads{0};
+
+// Groups (word widths, 0: one word with keys inline) in launch order.
+constexpr int kWidestFirst[] = {32, 16, 8, 4, 2, 1, 0};
 
 int width_slot(int g) { return g == 0 ? 0 : 1 + __builtin_ctz((unsigned)g); }
 int group_of(const rei_instance* in) { return in->inl ? 0 : in->st.W; }
@@ -1668,7 +1671,7 @@ int size_class(size_t n) {
 
 uint32_t max_threads(int g) { return batch_max_threads(g ? g : 1); }
 
-uint32_t choose_threads(int g, size_t n) {
+uint32_t choose_threads(int g, size_t n, size_t total) {
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find({g, size_class(n)});
@@ -1682,7 +1685,8 @@ uint32_t choose_threads(int g, size_t n) {
         g_cus = 256;
     }
   }
-  const uint64_t waves = (uint64_t)g_cus * 32 / std::max<size_t>(1, n);
+  // the call's workgroups share the device: 16 waves fit a compute unit
+  const uint64_t waves = (uint64_t)g_cus * 16 / std::max<size_t>(1, total);
   uint32_t t = waves >= 16 ? 1024u : waves >= 8 ? 512u : 256u;
   return std::min(t, max_threads(g));
 }
@@ -1754,6 +1758,20 @@ BatchDesc make_desc(const rei_instance* in) {
   return d;
 }
 
+// Buffers of the one-workgroup solver for R rows: survivors of one chunk, rows
+// and a table of load at most 1/2 for the rows the solver may store, all that
+// the buffers hold (make_desc) or, with only_r, R of them.  Nothing is filled:
+// the solver clears the part of the table that it uses, the per-chunk path
+// resets what it takes over.
+rei_status solver_buffers(rei_instance* in, uint64_t R, bool only_r, hipStream_t s) {
+  rei_status r;
+  if ((r = ensure_chunk_buffers(in, kBatchChunk, 0, 0, s)) != REI_OK) return r;
+  if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
+  const uint64_t entries = 2 * ((only_r ? R : in->rows_alloc) + kBatchChunk);
+  if (in->slots_cap < entries) return table_alloc(in, pow2_at_least(entries));
+  return REI_OK;
+}
+
 // Device bytes a batched instance uses (rows, back-pointers, table, survivors).
 uint64_t batch_reserve(const rei_instance* in, uint64_t arena_bytes) {
   const uint64_t R = batch_rows(in, arena_bytes);
@@ -1768,7 +1786,7 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
                         BatchRun* run) {
   run->s = s;
   run->t0 = now_s();
-  std::vector<BatchDesc> groups[kBatchMaxW + 1];
+  size_t batched = 0;
   rei_status r;
   for (size_t i = 0; i < n; ++i) {
     rei_instance* in = insts[i];
@@ -1782,32 +1800,24 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
       run->grid.push_back(in);
       continue;
     }
-    const uint64_t R = batch_rows(in, arena_bytes);
-    if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, s)) != REI_OK) return r;
-    if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
-    if ((r = ensure_table(in, in->rows_alloc + kBatchChunk, s, false)) != REI_OK) return r;
-    const int g = in->inl ? 0 : in->st.W;
-    groups[g].push_back(make_desc(in));
-    run->members[g].push_back(in);
-    __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
+    run->members[group_of(in)].push_back(in);
+    ++batched;
   }
   run->pin = n ? insts[0] : nullptr;
   // Hand-off on time moves deep searches onto compute units the batch leaves
   // idle; a batch with a workgroup for every compute unit leaves none.
-  size_t batched = 0;
-  for (int g = 0; g <= kBatchMaxW; g = g ? 2 * g : 1) batched += groups[g].size();
-  if (n && batched >= device_cus(insts[0]->device))
-    for (int g = 0; g <= kBatchMaxW; g = g ? 2 * g : 1)
-      for (BatchDesc& d : groups[g]) d.time_ticks = 0;
-  // One launch per word width; the first on s, the others on side streams
+  const bool full = n && batched >= device_cus(insts[0]->device);
+  // One launch per word width, the widest first (its searches take longest;
+  // behind the others they would start when those make room), each as soon as
+  // its instances are prepared.  The first is on s, the others on side streams
   // that start after s's earlier work and that s waits for, so the groups
   // run side by side.  The fork is recorded before the first launch: after
   // it, the side streams would wait for the first group to finish.
   {
     rei_instance* lead = nullptr;
     int n_groups = 0;
-    for (int g = 0; g <= kBatchMaxW; g = g ? 2 * g : 1)
-      if (!groups[g].empty()) {
+    for (int g : kWidestFirst)
+      if (!run->members[g].empty()) {
         if (!lead) lead = run->members[g][0];
         ++n_groups;
       }
@@ -1817,13 +1827,10 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
     }
   }
   bool first = true;
-  for (int g = 0; g <= kBatchMaxW; g = g ? 2 * g : 1) {
-    if (groups[g].empty()) continue;
+  for (int g : kWidestFirst) {
+    if (run->members[g].empty()) continue;
     rei_instance* in0 = run->members[g][0];
-    DescBuf db;
-    if ((r = desc_acquire(in0, groups[g].size(), &db)) != REI_OK) return r;
-    run->descs.push_back(db);
-    std::memcpy(db.h, groups[g].data(), groups[g].size() * sizeof(BatchDesc));
+    const size_t gn = run->members[g].size();
     hipStream_t gs = s;
     if (!first) {
       SideStream ss;
@@ -1832,12 +1839,23 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
       HIP_OK(in0, hipStreamWaitEvent(ss.s, run->fork, 0));
       gs = ss.s;
     }
+    DescBuf db;
+    if ((r = desc_acquire(in0, gn, &db)) != REI_OK) return r;
+    run->descs.push_back(db);
+    for (size_t k = 0; k < gn; ++k) {
+      rei_instance* in = run->members[g][k];
+      const uint64_t R = batch_rows(in, arena_bytes);
+      if ((r = solver_buffers(in, R, false, gs)) != REI_OK) return r;
+      db.h[k] = make_desc(in);
+      if (full) db.h[k].time_ticks = 0;
+      __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
+    }
     const uint32_t forced = g_force_threads.load();
-    const uint32_t th = forced ? std::min(forced, max_threads(g)) : choose_threads(g, groups[g].size());
+    const uint32_t th = forced ? std::min(forced, max_threads(g)) : choose_threads(g, gn, batched);
     run->threads[g] = th;
     hipEvent_t ev = nullptr, ev2 = nullptr;
     if ((r = prof_begin(run->pin, gs, REI_K_BATCH, &ev, &ev2)) != REI_OK) return r;
-    HIP_OK(in0, launch_solve_batch(g ? g : 1, g == 0, th, db.d, (uint32_t)groups[g].size(), gs));
+    HIP_OK(in0, launch_solve_batch(g ? g : 1, g == 0, th, db.d, (uint32_t)gn, gs));
     if ((r = prof_end(run->pin, gs, REI_K_BATCH, ev, ev2, 0)) != REI_OK) return r;
     if (profiled(run->pin, REI_K_BATCH)) {
       // kept apart from the instance's own records until the launch is
@@ -1906,19 +1924,14 @@ rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
     return REI_OK;
   rei_status r;
   const uint64_t R = std::max<uint64_t>(1024, std::min(in->row_cap, kFirstRows));
-  if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, s)) != REI_OK) return r;
-  if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
-  // (the solver clears the part of the table it uses)
-  const uint64_t entries = 2 * (kFirstRows + kBatchChunk);
-  if (in->slots_cap < entries && (r = table_alloc(in, pow2_at_least(entries))) != REI_OK) return r;
+  if ((r = solver_buffers(in, R, true, s)) != REI_OK) return r;
   DescBuf db;
   if ((r = desc_acquire(in, 1, &db)) != REI_OK) return r;
   BatchDesc d = make_desc(in);
   d.max_cost = cap;
   d.level_max = kFirstLevelMax;
   d.time_ticks = 0;
-  // rows beyond these would not fit the table's share
-  d.rows_alloc = std::min<uint64_t>(in->rows_alloc, std::max<uint64_t>(kFirstRows, R));
+  d.rows_alloc = R;  // (buffers of an earlier search may be larger; the table was checked for these)
   *db.h = d;
   __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
   const hipError_t e =
@@ -2559,7 +2572,7 @@ rei_status rei_solve_batch_noalloc(rei_instance* const* insts, size_t n, void* h
       const int g = group(idx[k]);
       uint32_t e = k;
       while (e < m && group(idx[e]) == g) ++e;
-      HIP_OK(in0, launch_solve_batch(g ? g : 1, g == 0, choose_threads(g, e - k), d_desc + k, e - k, s));
+      HIP_OK(in0, launch_solve_batch(g ? g : 1, g == 0, choose_threads(g, e - k, e - k), d_desc + k, e - k, s));
       k = e;
     }
     HIP_OK(insts[0], hipStreamSynchronize(s));
@@ -3384,9 +3397,7 @@ void server_sched_queue(rei_server* sv) {
             continue;
           }
           const uint64_t R = batch_rows(in, sv->arena);
-          if ((a.r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, sv->setup)) != REI_OK) continue;
-          if ((a.r = ensure_rows(in, R, sv->setup)) != REI_OK) continue;
-          if ((a.r = ensure_table(in, in->rows_alloc + kBatchChunk, sv->setup, false)) != REI_OK) continue;
+          if ((a.r = solver_buffers(in, R, false, sv->setup)) != REI_OK) continue;
           setup_used = true;
           __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
         } catch (const std::bad_alloc&) {
@@ -3784,11 +3795,7 @@ BatchDesc graph_desc(const rei_instance* in) {
 // Arena of a graph's instance: rows, chunk buffers, and a table that holds
 // every row plus a chunk at load at most 1/2.
 rei_status graph_arena(rei_instance* in, uint64_t arena_bytes, hipStream_t s) {
-  rei_status r;
-  const uint64_t R = batch_rows(in, arena_bytes);
-  if ((r = ensure_chunk_buffers(in, kBatchChunk, kBatchChunk, 0, s)) != REI_OK) return r;
-  if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
-  return ensure_table(in, in->rows_alloc + kBatchChunk, s, false);
+  return solver_buffers(in, batch_rows(in, arena_bytes), false, s);
 }
 
 // Results of one run of the launches (they have finished): every batched
@@ -3879,13 +3886,15 @@ rei_status rei_batch_graph_create(rei_instance* const* insts, size_t n, uint64_t
       descs.clear();
       g->groups.clear();
       g->batched.clear();
-      for (int w = 0; w <= kBatchMaxW; w = w ? 2 * w : 1) {
+      size_t total = 0;
+      for (const auto& m : members) total += m.size();
+      for (int w : kWidestFirst) {
         if (members[w].empty()) continue;
         rei_batch_graph::Group q;
         q.g = w;
         q.off = (uint32_t)descs.size();
         q.n = (uint32_t)members[w].size();
-        q.threads = choose_threads(w, members[w].size());
+        q.threads = choose_threads(w, members[w].size(), total);
         for (rei_instance* in : members[w]) {
           descs.push_back(graph_desc(in));  // no hand-off: the whole search stays in the graph
           g->batched.push_back(in);

@@ -353,12 +353,12 @@ hipError_t launch_level_marks(const MarksArgs& a, hipStream_t s);
 constexpr uint32_t kBatchChunk = 8192;   // candidates per chunk
 constexpr uint32_t kBatchMaxCost = 63;   // largest max_cost handled in a batch
 constexpr int kBatchMaxW = 32;           // largest words per language
-// The guide table sits in the workgroup's LDS: up to 512 infixes and 6144
-// cuts for languages of at most 8 words, up to 64 W infixes and 12288 cuts
-// for 16 and 32 words (the wider solvers run fewer threads, so their
-// operand tiles leave room for it).
-constexpr uint32_t batch_max_ic(int W) { return W <= 8 ? 512u : 64u * (uint32_t)W; }
-constexpr uint32_t batch_max_pairs(int W) { return W <= 8 ? 6144u : 12288u; }
+// The guide table sits in the workgroup's LDS: every infix of W words per
+// language, and up to 6144 cuts for languages of at most 8 words (one word:
+// 64 infixes never have more than 2080), 12288 cuts for 16 and 32 words (the
+// wider solvers run fewer threads, so their operand tiles leave room for it).
+constexpr uint32_t batch_max_ic(int W) { return 64u * (uint32_t)W; }
+constexpr uint32_t batch_max_pairs(int W) { return W == 1 ? 2112u : W <= 8 ? 6144u : 12288u; }
 // Most threads per instance for W words: each wave holds a 64 x W-word
 // operand tile in LDS.
 constexpr uint32_t batch_max_threads(int W) { return W >= 32 ? 256u : W >= 8 ? 512u : 1024u; }
