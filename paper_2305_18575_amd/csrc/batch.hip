@@ -133,9 +133,9 @@ __device__ __forceinline__ void phase_barrier() { __syncthreads(); }
 
 // Concatenation of 64 candidates that share one operand ("uniform") while the
 // other operand varies over the 64 bit positions of the transposed tile T.
-// kLeft = false: tile = right rows, out_t(w) = OR over cuts (u, v) of w with
+// left = false: tile = right rows, out_t(w) = OR over cuts (u, v) of w with
 //                uniform(u) of T[v];
-// kLeft = true:  tile = left rows,  out_t(w) = OR over cuts (u, v) with
+// left = true:  tile = left rows,  out_t(w) = OR over cuts (u, v) with
 //                uniform(v) of T[u].
 // Lane t receives the W words of candidate t.
 // The guide table (gto, gtp) is the workgroup's LDS copy.
@@ -145,9 +145,9 @@ __device__ __forceinline__ void phase_barrier() { __syncthreads(); }
 // independent LDS reads are in flight per round of eight words instead of a
 // chain of three per cut; below that the per-word loop keeps the register
 // count of the 1024-thread instantiations down.
-template <int W, bool kLeft>
+template <int W>
 __device__ __forceinline__ void concat_tile(const uint64_t* T, const uint64_t* uni, const uint32_t* gto,
-                                            const uint32_t* gtp, uint32_t n, uint32_t qn, uint64_t (&key)[W]) {
+                                            const uint32_t* gtp, uint32_t n, uint32_t qn, bool left, uint64_t (&key)[W]) {
   const uint32_t lane = lane_id();
   if constexpr (W >= 8) {
     // eight words at a time keeps the registers of the 16- and 32-word
@@ -170,8 +170,8 @@ __device__ __forceinline__ void concat_tile(const uint64_t* T, const uint64_t* u
         for (int k = 0; k < 8; ++k) p[k] = gtp[min(first[k] + q, last[k])];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          const uint32_t ui = kLeft ? (p[k] & 0xFFFFu) : (p[k] >> 16);
-          const uint32_t si = kLeft ? (p[k] >> 16) : (p[k] & 0xFFFFu);
+          const uint32_t ui = left ? (p[k] & 0xFFFFu) : (p[k] >> 16);
+          const uint32_t si = left ? (p[k] >> 16) : (p[k] & 0xFFFFu);
           const uint64_t t = T[si];
           const bool on = q < cnt[k] && ((uni[ui >> 6] >> (ui & 63)) & 1ull);
           acc[k] |= on ? t : 0ull;
@@ -195,8 +195,8 @@ __device__ __forceinline__ void concat_tile(const uint64_t* T, const uint64_t* u
         for (int z = 0; z < 4; ++z) p[z] = gtp[min(q + z, q1 - 1)];
 #pragma unroll
         for (int z = 0; z < 4; ++z) {
-          const uint32_t ui = kLeft ? (p[z] & 0xFFFFu) : (p[z] >> 16);
-          t[z] = T[kLeft ? (p[z] >> 16) : (p[z] & 0xFFFFu)];
+          const uint32_t ui = left ? (p[z] & 0xFFFFu) : (p[z] >> 16);
+          t[z] = T[left ? (p[z] >> 16) : (p[z] & 0xFFFFu)];
           u[z] = uni[ui >> 6] >> (ui & 63);  // (the last cut again is harmless)
         }
 #pragma unroll
@@ -205,6 +205,51 @@ __device__ __forceinline__ void concat_tile(const uint64_t* T, const uint64_t* u
       key[k] = transpose64(acc);
     }
   }
+}
+
+// The same for output words k0 .. k0 + kN - 1 only, left in the tile out (word
+// k of lane t at 64 k + t): a wave's share of a tile that several build.
+template <int kN>
+__device__ __forceinline__ void concat_words(const uint64_t* T, const uint64_t* uni, const uint32_t* gto,
+                                             const uint32_t* gtp, uint32_t n, uint32_t qn, bool left, uint32_t k0,
+                                             uint64_t* out) {
+  const uint32_t lane = lane_id();
+  uint32_t first[kN], last[kN], cnt[kN];
+  uint64_t acc[kN];
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+    const uint32_t w = 64u * (k0 + k) + lane;
+    first[k] = w < n ? gto[w] : 0u;
+    cnt[k] = w < n ? gto[w + 1] - first[k] : 0u;
+    last[k] = first[k] + (cnt[k] ? cnt[k] - 1 : 0u);
+    acc[k] = 0;
+  }
+  for (uint32_t q = 0; q < qn; ++q) {
+    uint32_t p[kN];
+#pragma unroll
+    for (int k = 0; k < kN; ++k) p[k] = gtp[min(first[k] + q, last[k])];
+#pragma unroll
+    for (int k = 0; k < kN; ++k) {
+      const uint32_t ui = left ? (p[k] & 0xFFFFu) : (p[k] >> 16);
+      const uint64_t t = T[left ? (p[k] >> 16) : (p[k] & 0xFFFFu)];
+      const bool on = q < cnt[k] && ((uni[ui >> 6] >> (ui & 63)) & 1ull);
+      acc[k] |= on ? t : 0ull;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kN; ++k) out[64 * (k0 + k) + lane] = transpose64(acc[k]);
+}
+
+// Words k0 .. k0 + kN - 1 of each lane's row (zeros when !have), transposed
+// into the tile T.
+template <int W, int kN>
+__device__ __forceinline__ void stage_words(uint64_t* T, const uint64_t* rows, uint64_t row, bool have, uint32_t k0) {
+  const uint32_t lane = lane_id();
+  uint64_t v[kN];
+#pragma unroll
+  for (int k = 0; k < kN; ++k) v[k] = have ? rows[row * W + k0 + k] : 0ull;
+#pragma unroll
+  for (int k = 0; k < kN; ++k) T[64 * (k0 + k) + lane] = transpose64(v[k]);
 }
 
 // Constructor block k of level c, blocks in enumeration order: the characters
@@ -333,6 +378,10 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
   static_assert(kBatchChunk <= 0xFFFFu, "ranks of a chunk fit 16 bits");
   __shared__ uint64_t s_uni[kWaves][W];
   __shared__ uint32_t s_gto[kIc + 1], s_gtp[kPairs], s_lo[kIc + 2];
+  // From eight words on concatenation tiles are dealt apart from the other
+  // items: a tile keeps its wave 20-30 us, and a small level has few.
+  constexpr bool kSplitItems = W >= 8;
+  __shared__ uint32_t s_cat0[kSplitItems ? kMaxBlocks + 1 : 1];  // each block's first tile in the chunk
   __shared__ uint32_t s_item;
   __shared__ uint32_t s_desc[sizeof(BatchDesc) / 4];
 
@@ -511,7 +560,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
           s_over = ~0u;
         }
         // each block's work in this chunk, a block per lane
-        uint32_t run = 0;
+        uint32_t run = 0, run_cat = 0;
         for (uint32_t b0 = 0; b0 < nblk; b0 += 64) {
           const uint32_t bi = b0 + lane;
           Span sp{0, 0, 0, 0};
@@ -526,17 +575,24 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
             }
             s_span[bi] = sp;
           }
-          const uint32_t dealt = bi < nblk && (kStarItems || s_blk[bi].op != OP_STAR) ? sp.items : 0u;
-          uint32_t incl = dealt;
-#pragma unroll
-          for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t v = (uint32_t)__shfl_up((int)incl, off, kWave);
-            if ((int)lane >= off) incl += v;
+          const bool apart = bi < nblk && ((!kStarItems && s_blk[bi].op == OP_STAR) ||
+                                           (kSplitItems && s_blk[bi].op == OP_CONCAT));
+          // (both prefixes in one scan: items in the low half, tiles above;
+          // a chunk has fewer than 2^31 of either)
+          const uint64_t dealt = apart ? (s_blk[bi].op == OP_CONCAT ? (uint64_t)sp.items << 32 : 0ull) : sp.items;
+          const uint64_t incl = wave_scan(dealt);
+          if (bi < nblk) {
+            s_item0[bi] = run + (uint32_t)(incl - dealt);
+            if constexpr (kSplitItems) s_cat0[bi] = run_cat + (uint32_t)((incl - dealt) >> 32);
           }
-          if (bi < nblk) s_item0[bi] = run + incl - dealt;
-          run += (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+          const uint64_t all = __shfl((unsigned long long)incl, kWave - 1, kWave);
+          run += (uint32_t)all;
+          run_cat += (uint32_t)(all >> 32);
         }
-        if (lane == 0) s_item0[nblk] = run;
+        if (lane == 0) {
+          s_item0[nblk] = run;
+          if constexpr (kSplitItems) s_cat0[nblk] = run_cat;
+        }
       }
       __syncthreads();
       // Star blocks first, one at a time, where they pair the waves: they
@@ -559,6 +615,51 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
         // The workgroup barriers around the block keep the partner's tile
         // out of the neighbouring blocks' per-wave use.
         __syncthreads();
+        if constexpr (kSplitItems) {
+          // few groups: four waves share each, every wave staging its words
+          // and taking its share of the words of each length
+          constexpr uint32_t kGroups = kWaves / 4;
+          const Span sp = s_span[bi];
+          if (sp.items <= kGroups) {
+            constexpr int kPart = W / 4;
+            const uint32_t slot = wave / 4, part = wave % 4;
+            const uint32_t k_lo = part * kPart;
+            uint64_t* Xt = s_tile[4 * slot];
+            uint64_t* Yt = s_tile[4 * slot + 1];
+            uint64_t* K = s_tile[4 * slot + 2];
+            const Kept kl = left_kept(OP_STAR, s_mk[blk.L], (uint32_t)s_lcount[blk.L]);
+            const bool have = slot < sp.items;
+            const uint32_t kk = (uint32_t)sp.k + 64 * slot + lane;
+            const uint64_t e = have && kk < kl.count() ? kl.row(kk) : e1;
+            if (have) {
+              stage_words<W, kPart>(Xt, d.rows, lst + e, e < e1, k_lo);
+#pragma unroll
+              for (int k = 0; k < kPart; ++k) Yt[64 * (k_lo + k) + lane] = (k_lo + k == 0 && lane == 0) ? ~0ull : 0ull;
+            }
+            __syncthreads();
+            for (uint32_t l = 1; l <= d.max_len; ++l) {
+              if (have) {
+                const uint32_t lo = s_lo[l], hi = s_lo[l + 1];
+                for (uint32_t w = lo + lane + 64 * part; w < hi; w += 256)
+                  Yt[w] = star_fold(Xt, Yt, s_gtp, s_gto[w], l);
+              }
+              __syncthreads();
+            }
+            if (have) {
+#pragma unroll
+              for (int k = 0; k < kPart; ++k) K[64 * (k_lo + k) + lane] = transpose64(Yt[64 * (k_lo + k) + lane]);
+            }
+            __syncthreads();
+            if (have && part == 0) {
+              uint64_t key[W];
+#pragma unroll
+              for (int k = 0; k < W; ++k) key[k] = K[64 * k + lane];
+              filter_emit<W, kInl>(probe, sink, e >= e0 && e < e1, false, key, (uint32_t)(rel0 + e));
+            }
+            __syncthreads();
+            continue;
+          }
+        }
         if ((wave & 1u) == 0) {
           uint64_t* Xt = s_tile[wave];
           uint64_t* Yt = s_tile[wave + 1];
@@ -597,6 +698,79 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
       // Every other block's work items (64 consecutive candidates, or one
       // concatenation tile) are dealt to the waves together, so a chunk that
       // spans many small blocks keeps every wave busy.
+      if constexpr (kSplitItems) {
+        constexpr uint32_t kGroups = kWaves / 4;
+        const uint32_t n_cat = s_cat0[nblk];
+        // four waves share a tile where that takes less time: a shared round
+        // is about a third of a wave's own (16 words: 9 against 28 us)
+        const bool shared = (n_cat + kGroups - 1) / kGroups < 3 * ((n_cat + kWaves - 1) / kWaves);
+        const uint32_t step = shared ? kGroups : kWaves, slot = shared ? wave / 4 : wave, part = shared ? wave % 4 : 0;
+        constexpr int kPart = W / 4;
+        uint64_t* T = s_tile[shared ? 4 * slot : wave];
+        uint64_t* K = s_tile[shared ? 4 * slot + 1 : wave];  // the tile's candidates, word by word
+        uint64_t* U = s_uni[shared ? 4 * slot : wave];
+        uint32_t bi = 0;
+        // (every wave takes every round: workgroup barriers inside when shared)
+        for (uint32_t base = 0; base < n_cat; base += step) {
+          const uint32_t it = base + slot;
+          const bool have = it < n_cat;
+          uint64_t e = 0;
+          bool valid = false, left = false;
+          uint32_t rel = 0;
+          if (have) {
+            while (s_cat0[bi + 1] <= it) ++bi;
+            const uint32_t li = it - s_cat0[bi];
+            const uint64_t bs = s_bstart[bi], be = s_bstart[bi + 1];
+            const BlockD blk = s_blk[bi];
+            const uint64_t lst = s_lstart[blk.L], rst = s_lstart[blk.R];
+            const uint32_t nL = (uint32_t)s_lcount[blk.L], nR = (uint32_t)s_lcount[blk.R];
+            const uint64_t e0 = max(E0, bs) - bs, e1 = min(E1, be) - bs;
+            const Span sp = s_span[bi];
+            const Kept kl = left_kept(OP_CONCAT, s_mk[blk.L], nL);
+            uint64_t row, urow;  // this lane's row of the tile, the uniform row
+            if (right_lanes(nL, nR)) {
+              const uint32_t nT = (nR + 63) / 64, f = sp.b + li;
+              const uint64_t i = kl.row(sp.a + f / nT), j = 64 * (f % nT) + lane;
+              valid = j < nR;
+              row = rst + j;
+              urow = lst + i;
+              e = i * nR + j;
+            } else {
+              left = true;
+              const uint32_t kk = 64 * (sp.a + li / nR) + lane, j = li % nR;
+              valid = kk < kl.count();
+              const uint64_t i = valid ? kl.row(kk) : 0ull;
+              row = lst + i;
+              urow = rst + j;
+              e = i * nR + j;
+            }
+            for (uint32_t k0 = shared ? part * kPart : 0; k0 < (shared ? (part + 1) * kPart : (uint32_t)W); k0 += kPart)
+              stage_words<W, kPart>(T, d.rows, row, valid, k0);
+            if (part == 0 && lane < (uint32_t)W) U[lane] = d.rows[urow * W + lane];
+            valid = valid && e >= e0 && e < e1;
+            rel = (uint32_t)(bs - E0 + e);
+          }
+          if (shared)
+            __syncthreads();
+          else
+            wave_sync_lds();
+          if (shared) {
+            if (have) concat_words<kPart>(T, U, s_gto, s_gtp, d.n, d.max_len + 1, left, part * kPart, K);
+            __syncthreads();
+          }
+          if (have && part == 0) {
+            uint64_t key[W];
+            if (shared) {
+#pragma unroll
+              for (int k = 0; k < W; ++k) key[k] = K[64 * k + lane];
+            } else {
+              concat_tile<W>(T, U, s_gto, s_gtp, d.n, d.max_len + 1, left, key);
+            }
+            filter_emit<W, kInl>(probe, sink, valid, false, key, rel);
+          }
+          if (!shared) wave_sync_lds();  // the tile is rewritten in the next round
+        }
+      }
       {
         const uint32_t n_items = s_item0[nblk];
         uint32_t bi = 0;
@@ -683,6 +857,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
             filter_emit<W, kInl>(probe, sink, valid, dup, key, (uint32_t)(rel0 + e));
             continue;
           }
+          if constexpr (!kSplitItems) {
           uint64_t* T = s_tile[wave];
           uint64_t* U = s_uni[wave];
           const uint32_t nL = (uint32_t)lct, nR = (uint32_t)rct;
@@ -699,7 +874,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
             if (lane < (uint32_t)W) U[lane] = d.rows[(lst + i) * W + lane];
             wave_sync_lds();
             uint64_t key[W];
-            concat_tile<W, false>(T, U, s_gto, s_gtp, d.n, d.max_len + 1, key);
+            concat_tile<W>(T, U, s_gto, s_gtp, d.n, d.max_len + 1, false, key);
             const uint64_t e = i * nR + jr;
             filter_emit<W, kInl>(probe, sink, jr < nR && e >= e0 && e < e1, false, key, (uint32_t)(rel0 + e));
             wave_sync_lds();
@@ -716,10 +891,11 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
             if (lane < (uint32_t)W) U[lane] = d.rows[(rst + j) * W + lane];
             wave_sync_lds();
             uint64_t key[W];
-            concat_tile<W, true>(T, U, s_gto, s_gtp, d.n, d.max_len + 1, key);
+            concat_tile<W>(T, U, s_gto, s_gtp, d.n, d.max_len + 1, true, key);
             const uint64_t e = ir * nR + j;
             filter_emit<W, kInl>(probe, sink, ir < nL && e >= e0 && e < e1, false, key, (uint32_t)(rel0 + e));
             wave_sync_lds();
+          }
           }
         }
       }

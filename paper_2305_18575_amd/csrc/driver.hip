@@ -1643,6 +1643,8 @@ std::atomic<uint64_t> g_level_max[kSlots];
 // Threads per instance forced on every group while the tuner times a shape.
 std::atomic<uint32_t> g_force_threads{0};
 
+constexpr int kGridWorkers = 8;  // instances on the per-chunk path at once
+
 // Groups (word widths, 0: one word with keys inline) in launch order.
 constexpr int kWidestFirst[] = {32, 16, 8, 4, 2, 1, 0};
 
@@ -1786,7 +1788,7 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
                         BatchRun* run) {
   run->s = s;
   run->t0 = now_s();
-  size_t batched = 0;
+  size_t batched = 0, wide = 0;
   rei_status r;
   for (size_t i = 0; i < n; ++i) {
     rei_instance* in = insts[i];
@@ -1802,6 +1804,7 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
     }
     run->members[group_of(in)].push_back(in);
     ++batched;
+    wide += in->st.W >= 8;
   }
   run->pin = n ? insts[0] : nullptr;
   // Hand-off on time moves deep searches onto compute units the batch leaves
@@ -1831,6 +1834,8 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
     if (run->members[g].empty()) continue;
     rei_instance* in0 = run->members[g][0];
     const size_t gn = run->members[g].size();
+    // (a hand-off size set by the caller or the tuner stands)
+    const bool few_wide = g >= 8 && wide <= (size_t)kGridWorkers;
     hipStream_t gs = s;
     if (!first) {
       SideStream ss;
@@ -1848,6 +1853,8 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
       if ((r = solver_buffers(in, R, false, gs)) != REI_OK) return r;
       db.h[k] = make_desc(in);
       if (full) db.h[k].time_ticks = 0;
+      if (few_wide && !in->batch_level_max && !g_level_max[width_slot(g)].load())
+        db.h[k].level_max = std::min(db.h[k].level_max, kWideLevelMax);
       __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
     }
     const uint32_t forced = g_force_threads.load();
@@ -2013,8 +2020,6 @@ rei_status batch_collect(BatchRun* run, const std::vector<rei_instance*>* taken 
   if (fold_prof && (r = batch_fold_prof(run)) != REI_OK) return r;
   return REI_OK;
 }
-
-constexpr int kGridWorkers = 8;
 
 // Worker threads that run the per-chunk path for instances handed to them
 // while a batched launch still runs: 8 threads for the whole process, each

@@ -365,6 +365,11 @@ constexpr uint32_t batch_max_threads(int W) { return W >= 32 ? 256u : W >= 8 ? 5
 constexpr uint64_t kBatchTimeMinLevel = 4096;  // smaller levels stay on the workgroup whatever the time
 constexpr uint32_t kBatchTimeUs = 500;         // default workgroup time before larger levels move
 constexpr uint64_t kBatchLevelMax = 1ull << 16;  // default: candidates of one level a workgroup takes on
+// ... of eight words or more per language, when no more instances are that wide
+// than the worker threads run at once: a 64-candidate tile of 16 words keeps a
+// wave 20-30 us, and the device beside it is idle (four instances of 8-16
+// words: 1.10 ms at 2^11, 1.45 ms at 2^16)
+constexpr uint64_t kWideLevelMax = 1ull << 11;
 constexpr uint32_t kBatchTreeNodes = 64; // answer-tree nodes written back (cost <= 63 needs <= 63)
 
 struct BatchDesc {
