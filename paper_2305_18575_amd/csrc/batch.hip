@@ -906,14 +906,11 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(solver_waves
         // bit toggled off)
         const uint32_t ns = s_nsurv;
         for (uint32_t sid = tid; sid < ns; sid += kT) {
-          uint64_t key[W];
-#pragma unroll
-          for (int k = 0; k < W; ++k) key[k] = d.skey[(uint64_t)sid * W + k];
           const uint64_t h = d.spos[sid];
           const uint32_t e = d.se[sid];
           const uint64_t mine = kInl ? chunk_ref(ref_gen, e) : new_ref(e, sid);
           uint64_t old;
-          const uint64_t pos = table_insert<W, kInl>(d.slots, tmask, d.rows, d.skey, key, h, mine, &old);
+          const uint64_t pos = table_insert<W, kInl>(d.slots, tmask, d.rows, d.skey, sid, h, mine, &old);
           if constexpr (!kInl) d.spos[sid] = spos_pack(pos, h);
           if (mine < old) {
             atomicXor(&s_bm[e >> 5], 1u << (e & 31));

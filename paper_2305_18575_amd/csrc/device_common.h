@@ -195,6 +195,20 @@ __device__ __forceinline__ bool key_eq(const uint64_t* p, const uint64_t (&key)[
   return eq;
 }
 
+// Whether two stored keys are equal, up to 16 words at a time (their reads
+// overlap; most pairs that differ do so in the first 16).
+template <int W>
+__device__ __forceinline__ bool keys_equal(const uint64_t* p, const uint64_t* q) {
+  constexpr int kStep = W < 16 ? W : 16;
+  for (int k = 0; k < W; k += kStep) {
+    bool eq = true;
+#pragma unroll
+    for (int z = 0; z < kStep; ++z) eq = eq && p[k + z] == q[k + z];
+    if (!eq) return false;
+  }
+  return true;
+}
+
 __device__ __forceinline__ uint64_t new_ref(uint32_t e, uint32_t sid) {
   return kNewFlag | ((uint64_t)e << 32) | sid;
 }
@@ -223,22 +237,26 @@ __device__ __forceinline__ bool table_find(const uint64_t* slots, uint64_t mask,
 }
 
 // Inserts a survivor (reference `mine` = 1 | e | sid); equal keys meet in one
-// slot and keep the smallest reference.  Returns the slot.
+// slot and keep the smallest reference.  Returns the slot.  The survivor's key
+// (at skey + sid * W) is read only where a slot is taken already: most
+// survivors claim an empty one (inline keys are the slots' contents).
 // old: the reference the slot held for this key before (EMPTY: none).
 template <int W, bool kInl>
 __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask, const uint64_t* rows,
-                                                 const uint64_t* skey, const uint64_t (&key)[W], uint64_t h,
-                                                 uint64_t mine, uint64_t* old) {
+                                                 const uint64_t* skey, uint32_t sid, uint64_t h, uint64_t mine,
+                                                 uint64_t* old) {
   uint64_t pos = h & mask;
+  const uint64_t* key = skey + (uint64_t)sid * W;
   if constexpr (kInl) {
+    const uint64_t own = key[0];
     for (;;) {
       uint64_t v = slots[2 * pos];
       if (v == kEmpty) {
         v = atomicCAS((unsigned long long*)&slots[2 * pos], (unsigned long long)kEmpty,
-                      (unsigned long long)key[0]);
-        if (v == kEmpty) v = key[0];  // claimed
+                      (unsigned long long)own);
+        if (v == kEmpty) v = own;  // claimed
       }
-      if (v == key[0]) {
+      if (v == own) {
         *old = atomicMin((unsigned long long*)&slots[2 * pos + 1], (unsigned long long)mine);
         return pos;
       }
@@ -258,11 +276,11 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask,
       }
       if (v & kNewFlag) {
         // another survivor owns the slot; its key never changes
-        if (key_eq<W>(skey + (uint64_t)(uint32_t)v * W, key)) {
+        if (keys_equal<W>(skey + (uint64_t)(uint32_t)v * W, key)) {
           *old = atomicMin((unsigned long long*)&slots[pos], (unsigned long long)mine);
           return pos;
         }
-      } else if (((v >> kRowBits) & 0xFFFFFFull) == fp && key_eq<W>(rows + (v & kRowMask) * W, key)) {
+      } else if (((v >> kRowBits) & 0xFFFFFFull) == fp && keys_equal<W>(rows + (v & kRowMask) * W, key)) {
         *old = 0;  // stored already (the generators filter these; kept for safety): below any survivor
         return pos;
       }

@@ -1911,14 +1911,15 @@ bool batch_take_state(rei_instance* in) {
 // The first levels of a search by rei_solve on one workgroup: a level of a
 // few hundred candidates takes it 10-15 us, where the per-chunk path's chain
 // of three launches and a wait at the level's end takes 30 us.  A level of
-// more than kFirstLevelMax candidates, wider languages, and what the
+// more than first_level_max candidates, languages of 32 words, and what the
 // one-workgroup solver cannot do go to the per-chunk path, which continues
 // from the rows stored.  *complete: the search ended here.
-#ifndef REI_FIRST_LEVEL_MAX
-#define REI_FIRST_LEVEL_MAX 4096
-#endif
-constexpr uint64_t kFirstLevelMax = REI_FIRST_LEVEL_MAX;
-constexpr int kFirstLevelsMaxW = 4;
+// Eight solves of one and two words: 1.76 / 1.75 / 1.72 / 1.75 / 1.83 ms at
+// 1024 / 2048 / 4096 / 8192 / 16384; four of 8-16 words: 1.29 / 1.24 / 1.33 /
+// 1.44 ms at 0 / 128 / 512 / 2048; one of 32 words: 0.98 / 1.03 / 1.17 ms at
+// 0 / 128 / 512.
+constexpr uint64_t first_level_max(int W) { return W <= 4 ? 4096 : 128; }
+constexpr int kFirstLevelsMaxW = 16;
 constexpr uint64_t kFirstRows = 1ull << 15;
 rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
   *complete = false;
@@ -1936,7 +1937,7 @@ rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
   if ((r = desc_acquire(in, 1, &db)) != REI_OK) return r;
   BatchDesc d = make_desc(in);
   d.max_cost = cap;
-  d.level_max = kFirstLevelMax;
+  d.level_max = first_level_max(in->st.W);
   d.time_ticks = 0;
   d.rows_alloc = R;  // (buffers of an earlier search may be larger; the table was checked for these)
   *db.h = d;

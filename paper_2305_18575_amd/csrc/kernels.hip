@@ -817,13 +817,11 @@ __global__ __launch_bounds__(256) void insert_survivors(ChunkArgs a) {
     uint32_t e = 0;
     bool won = false;
     if (have) {
-      uint64_t key[W];
-      load_row<W>(a.skey, sid, true, key);
       const uint64_t h = a.spos[sid];
       e = a.se[sid];
       const uint64_t mine = kInl ? chunk_ref(a.ref_gen, e) : new_ref(e, sid);
       uint64_t old;
-      const uint64_t pos = table_insert<W, kInl>(a.slots, a.slot_mask, a.rows, a.skey, key, h, mine, &old);
+      const uint64_t pos = table_insert<W, kInl>(a.slots, a.slot_mask, a.rows, a.skey, sid, h, mine, &old);
       if constexpr (!kInl) a.spos[sid] = spos_pack(pos, h);
       won = mine < old;  // else an earlier candidate has it
       uint32_t oe;
