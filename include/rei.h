@@ -123,7 +123,9 @@ rei_status rei_solve(rei_instance *inst, void *hip_stream, rei_result *out);
  * by side), one workgroup per instance executing the whole level loop on the
  * device (no host round trip per level or chunk; the answer's expression
  * tree is decoded there too).  An instance whose next level has more
- * candidates than the hand-off size (rei_set_batch_level; 2^16 by default),
+ * candidates than the hand-off size (rei_set_batch_level; 2^16 by default, 2^11
+ * for languages of 8 words or more when at most 8 such instances are in the
+ * call),
  * or more than 4096 after its workgroup has run for the hand-off time
  * (rei_set_batch_time; 500 us by default),
  * continues from that level on rei_solve's path with its lower levels kept;
@@ -370,7 +372,7 @@ rei_status rei_row_regex(rei_instance *inst, uint32_t cost, uint64_t i, char *bu
 rei_status rei_set_chunk(rei_instance *inst, uint64_t max_candidates);
 /* Largest level, in candidates, that rei_solve_batch searches inside its
  * one-workgroup solver (0 = the process default for the instance's word
- * width: 2^16, or what rei_tune_batch chose, where 0 means rei_solve's path
+ * width: 2^16 (2^11 for few wide languages), or what rei_tune_batch chose, where 0 means rei_solve's path
  * from the start).  At a larger level the instance,
  * with every lower level kept, continues on rei_solve's path.  Results do not
  * depend on it. */

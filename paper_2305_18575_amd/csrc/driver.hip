@@ -1661,6 +1661,11 @@ uint64_t level_max_of(const rei_instance* in) {
   return in->batch_level_max ? in->batch_level_max : tuned_level_max(width_slot(group_of(in)));
 }
 
+// Whether neither the caller nor the tuner has set the instance's size.
+bool default_level_max(const rei_instance* in) {
+  return !in->batch_level_max && !g_level_max[width_slot(group_of(in))].load();
+}
+
 // Whether rei_solve_batch (and the server) start the instance in the
 // one-workgroup solver: it fits there, and its hand-off size is not 0.
 bool batch_path(const rei_instance* in) { return batchable(in) && level_max_of(in) > 0; }
@@ -1853,8 +1858,7 @@ rei_status batch_launch(rei_instance* const* insts, size_t n, hipStream_t s, uin
       if ((r = solver_buffers(in, R, false, gs)) != REI_OK) return r;
       db.h[k] = make_desc(in);
       if (full) db.h[k].time_ticks = 0;
-      if (few_wide && !in->batch_level_max && !g_level_max[width_slot(g)].load())
-        db.h[k].level_max = std::min(db.h[k].level_max, kWideLevelMax);
+      if (few_wide && default_level_max(in)) db.h[k].level_max = std::min(db.h[k].level_max, kWideLevelMax);
       __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
     }
     const uint32_t forced = g_force_threads.load();
@@ -3296,7 +3300,12 @@ uint64_t request_reserve(const rei_server* sv, const rei_instance* in) {
 // mid-sized ones after the workgroup's time, as for rei_solve_batch (the
 // per-chunk path runs beside the persistent launches, which hold a quarter
 // of the compute units per group).
-BatchDesc queue_desc(const rei_instance* in) { return make_desc(in); }
+BatchDesc queue_desc(const rei_instance* in) {
+  BatchDesc d = make_desc(in);
+  // (a queue launch has few workgroups, the workers take what leaves them)
+  if (in->st.W >= 8 && default_level_max(in)) d.level_max = std::min(d.level_max, kWideLevelMax);
+  return d;
+}
 
 void server_sched_queue(rei_server* sv) {
   (void)hipSetDevice(sv->device);
