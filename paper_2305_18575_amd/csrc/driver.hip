@@ -178,6 +178,7 @@ struct rei_instance {
   uint32_t otf_level = 0;
   bool otf_blocked = false;
   uint64_t pending = 0;
+  int ctrl_turn = 0;        // the control block of the next chunk
   ChunkLaunches launches;   // of the chunk being enqueued
   uint32_t chunks_enq = 0;  // chunks enqueued on the per-chunk path since the state was reset
 
@@ -984,7 +985,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
     q.se = in->d_se;
     q.spos = in->d_spos;
     q.reg = in->d_reg;
-    q.ctrl = in->d_ctrl;
+    q.ctrl = in->d_ctrl + in->ctrl_turn;
     q.pmask = in->d_pmask;
     q.nmask = in->d_nmask;
     q.gt_off = in->d_gt_off;
@@ -1037,7 +1038,10 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
   ca.word_prefix = in->d_prefix;
   ca.block_sums = in->d_bsums;
   ca.n_bitmap_words = (uint32_t)words;
-  ca.ctrl = in->d_ctrl;
+  ca.ctrl = in->d_ctrl + in->ctrl_turn;
+  ca.ctrl_next = in->d_ctrl + (1 - in->ctrl_turn);
+  ca.chunk_id = in->chunks_enq + 1;
+  in->ctrl_turn = 1 - in->ctrl_turn;
   ca.st = in->d_state;
   const uint64_t L = in->max_cost + 2;
   ca.lcount = in->d_levels;
@@ -1364,6 +1368,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
   }
   in->bm_high = 0;
   in->bm_turn = 0;
+  in->ctrl_turn = 0;
   in->chunks_enq = 0;
   if (c_from > c1) {
     // The batched solver stored every level below c_from (rows and
@@ -2193,7 +2198,7 @@ rei_status create_device(rei_instance* in) {
                {st.nmask.data(), st.nmask.size() * 8, 0},     {st.char_index.data(), st.char_index.size() * 4, 0}};
   for (Part& p : parts) p.off = place(p.bytes);
   const uint64_t copied = at;
-  const uint64_t o_ctrl = place(sizeof(Ctrl)), o_state = place(sizeof(DevState)), o_levels = place(3 * L * 8);
+  const uint64_t o_ctrl = place(2 * sizeof(Ctrl)), o_state = place(sizeof(DevState)), o_levels = place(3 * L * 8);
   HIP_OK(in, dev_alloc(in, &in->d_tables, at));
   char* base = in->d_tables;
   in->d_gt_off = (uint32_t*)(base + parts[0].off);

@@ -48,15 +48,15 @@ constexpr uint64_t kRowMask = (1ull << kRowBits) - 1;
 constexpr uint64_t kNewFlag = 1ull << 63;
 constexpr uint64_t kMaxChunk = (1ull << 28);  // chunk-relative indices stay far below 2^31 - 1
 
-// Per-chunk control block in device memory.  The generator starts from
-// n_surv = 0, answer_e = ~0; the chunk's last kernel puts them back.
+// Per-chunk control block in device memory, two of them taken in turn: the
+// accounting of a chunk clears the next chunk's (n_surv = 0, answer_e = ~0) and
+// leaves its own for the ordered append that follows it.
 struct Ctrl {
   uint32_t n_surv;          // survivors appended by the generator
   uint32_t answer_e;        // chunk-relative index of the first precise survivor (or ~0)
-  uint32_t answer_rank;     // rank of the answer among the chunk's winners
-  uint32_t winners;         // winners in the chunk
-  uint32_t overflow_e;      // chunk-relative index of the winner that does not fit
-  uint32_t pad[3];
+  uint32_t append;          // number of the chunk accounted here, whose winners are to be stored (0: none)
+  uint32_t pad;
+  uint64_t row_base, room;  // rows stored before the chunk, rows that still fit
 };
 
 // Search state in device memory, advanced by the last kernel of each chunk,
@@ -150,6 +150,8 @@ struct ChunkArgs {
   uint32_t* block_sums;
   uint32_t n_bitmap_words;
   Ctrl* ctrl;
+  Ctrl* ctrl_next;            // the next chunk's
+  uint32_t chunk_id;          // number of the chunk in its search, from 1
   DevState* st;
   uint64_t* uniq;             // per cost level: new languages
   uint64_t* cand;             // per cost level: candidates
@@ -236,7 +238,7 @@ hipError_t launch_decode_tree(const TreeArgs& t, hipStream_t s);
 // visible), the table's words to EMPTY, both winner bitmaps' used words to
 // zero (any count may be 0).
 struct ResetArgs {
-  Ctrl* ctrl;
+  Ctrl* ctrl;                 // both
   DevState* st;
   uint64_t row_cap, total_rows;
   uint32_t otf_on;

@@ -724,15 +724,14 @@ __global__ void fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
 __device__ __forceinline__ void ctrl_clear(Ctrl* c) {
   c->n_surv = 0;
   c->answer_e = ~0u;
-  c->answer_rank = ~0u;
-  c->winners = 0;
-  c->overflow_e = ~0u;
+  c->append = 0;
 }
 
 __global__ __launch_bounds__(256) void search_reset(ResetArgs a) {
   const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (uint64_t)gridDim.x * blockDim.x;
   if (t == 0) {
     ctrl_clear(a.ctrl);
+    ctrl_clear(a.ctrl + 1);
     DevState* st = a.st;
     st->total_rows = a.total_rows;
     st->row_cap = a.row_cap;
@@ -842,6 +841,9 @@ __device__ void account_chunk(const ChunkArgs& a, uint32_t ans, uint32_t answer_
   DevState* st = a.st;
   const uint64_t room = st->row_cap > st->total_rows ? st->row_cap - st->total_rows : 0;
   const uint32_t c = a.cost;
+  a.ctrl->append = a.chunk_id;
+  a.ctrl->row_base = st->total_rows;
+  a.ctrl->room = room;
   uint64_t stored;
   if (st->otf) {
     stored = 0;
@@ -892,7 +894,7 @@ __device__ void account_chunk(const ChunkArgs& a, uint32_t ans, uint32_t answer_
   }
   st->total_rows += stored;
   a.lcount[c] += stored;
-  ctrl_clear(a.ctrl);
+  ctrl_clear(a.ctrl_next);
   // the host reads these at level boundaries without a copy
   DevState* h = a.hst;
   h->total_rows = st->total_rows;
@@ -1035,11 +1037,37 @@ __global__ __launch_bounds__(256) void scan_reduce(ChunkArgs a) {
   if (t == 0) a.block_sums[b] = red[0];
 }
 
+// The chunk's accounting by the workgroup that knows the total: before[w] is
+// the number of winners below bitmap word w.  Called by one thread.
+template <typename Before>
+__device__ void account_scanned(const ChunkArgs& a, uint32_t winners, Before before) {
+  const uint32_t ans = a.ctrl->answer_e;
+  const uint64_t total = a.st->total_rows;
+  const uint64_t room = a.st->row_cap > total ? a.st->row_cap - total : 0;
+  uint32_t answer_rank = ~0u, overflow_e = ~0u;
+  if (ans != ~0u) answer_rank = before(ans >> 5) + (uint32_t)__popc(a.bitmap[ans >> 5] & ((1u << (ans & 31)) - 1));
+  if (winners > room) {
+    // the first winner that does not fit: bisect the words, then the bits
+    uint32_t lo = 0, hi = a.n_bitmap_words;
+    while (hi - lo > 1) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      if (before(mid) <= room)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    uint32_t m = a.bitmap[lo];
+    for (uint32_t k = (uint32_t)room - before(lo); k; --k) m &= m - 1;
+    overflow_e = 32 * lo + (uint32_t)__ffs(m) - 1;
+  }
+  account_chunk(a, ans, answer_rank, winners, overflow_e);
+}
+
 // Chunks whose bitmap has at most kScanSingleWords words (2^18 candidates,
 // eight words per thread): the whole exclusive scan of the winner bitmap in
-// one workgroup (each thread a contiguous run of words), total ->
-// ctrl->winners.  Replaces the three launches below for the mid-sized
-// chunks a level starts with; larger bitmaps scan faster spread out.
+// one workgroup (each thread a contiguous run of words), and the accounting.
+// Replaces the two launches below for the mid-sized chunks a level starts
+// with; larger bitmaps scan faster spread out.
 constexpr uint32_t kScanSingleWords = 8192;
 __global__ __launch_bounds__(1024) void scan_single(ChunkArgs a) {
   __shared__ uint32_t part[1024];
@@ -1063,39 +1091,30 @@ __global__ __launch_bounds__(1024) void scan_single(ChunkArgs a) {
     a.word_prefix[w] = run;
     run += __popc(a.bitmap[w]);
   }
-  if (t == 1023) a.ctrl->winners = part[1023];
-}
-
-// single workgroup: exclusive scan of the block sums, total -> ctrl->winners
-__global__ __launch_bounds__(1024) void scan_top(ChunkArgs a, uint32_t nb) {
-  __shared__ uint32_t part[1024];
-  if (a.st->stop) return;
-  const uint32_t t = threadIdx.x;
-  const uint32_t per = (nb + 1023) / 1024;
-  const uint32_t lo = min(nb, t * per), hi = min(nb, lo + per);
-  uint32_t s = 0;
-  for (uint32_t i = lo; i < hi; ++i) s += a.block_sums[i];
-  part[t] = s;
   __syncthreads();
-  for (uint32_t st = 1; st < 1024; st <<= 1) {
-    const uint32_t v = (t >= st) ? part[t - st] : 0u;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  uint32_t run = part[t] - s;  // exclusive
-  for (uint32_t i = lo; i < hi; ++i) {
-    const uint32_t v = a.block_sums[i];
-    a.block_sums[i] = run;
-    run += v;
-  }
-  if (t == 1023) a.ctrl->winners = part[1023];
+  if (t == 0) account_scanned(a, part[1023], [&](uint32_t w) { return a.word_prefix[w]; });
 }
 
-__global__ __launch_bounds__(256) void scan_down(ChunkArgs a) {
+// Each block adds the sums of the blocks before it by itself (a launch of one
+// workgroup in between cost 4.4 us and its gap per chunk); the last one also
+// accounts the chunk (a launch of its own at the end cost 4 us).
+__global__ __launch_bounds__(256) void scan_down(ChunkArgs a, uint32_t nb) {
   __shared__ uint32_t part[256];
-  if (a.st->stop) return;
+  __shared__ uint32_t s_base;
+  // (no look at the stop code before the last block's accounting, which may
+  // set it while others have not started: a chunk after a stop writes prefixes
+  // that nobody reads)
   const uint32_t b = blockIdx.x, t = threadIdx.x;
+  uint32_t before = 0;
+  for (uint32_t i = t; i < b; i += 256) before += a.block_sums[i];
+  part[t] = before;
+  __syncthreads();
+  for (uint32_t st = 128; st > 0; st >>= 1) {
+    if (t < st) part[t] += part[t + st];
+    __syncthreads();
+  }
+  if (t == 0) s_base = part[0];
+  __syncthreads();
   uint32_t c[4], s = 0;
   for (uint32_t q = 0; q < 4; ++q) {
     const uint32_t w = b * kScanBlock + t * 4 + q;
@@ -1110,20 +1129,63 @@ __global__ __launch_bounds__(256) void scan_down(ChunkArgs a) {
     part[t] += v;
     __syncthreads();
   }
-  uint32_t run = a.block_sums[b] + part[t] - s;
+  uint32_t run = s_base + part[t] - s;
   for (uint32_t q = 0; q < 4; ++q) {
     const uint32_t w = b * kScanBlock + t * 4 + q;
     if (w < a.n_bitmap_words) a.word_prefix[w] = run;
     run += c[q];
   }
+  if (b + 1 == nb && !a.st->stop) {
+    const uint32_t winners = s_base + part[255];
+    // winners below a word: the other blocks' prefixes may not be written
+    // yet, so the sums and the words of its block are added up (one word for
+    // the answer; some twenty more when the cache overflows)
+    auto sum_below = [&](uint32_t w) -> uint32_t {  // by the whole block
+      uint32_t v = 0;
+      const uint32_t wb = w / kScanBlock;
+      for (uint32_t i = t; i < wb; i += 256) v += a.block_sums[i];
+      for (uint32_t i = wb * kScanBlock + t; i < w; i += 256) v += __popc(a.bitmap[i]);
+      __syncthreads();
+      part[t] = v;
+      __syncthreads();
+      for (uint32_t st = 128; st > 0; st >>= 1) {
+        if (t < st) part[t] += part[t + st];
+        __syncthreads();
+      }
+      return part[0];
+    };
+    const uint32_t ans = a.ctrl->answer_e;
+    const uint64_t total = a.st->total_rows;
+    const uint64_t room = a.st->row_cap > total ? a.st->row_cap - total : 0;
+    uint32_t answer_rank = ~0u, overflow_e = ~0u;
+    if (ans != ~0u)
+      answer_rank = sum_below(ans >> 5) + (uint32_t)__popc(a.bitmap[ans >> 5] & ((1u << (ans & 31)) - 1));
+    if (winners > room) {
+      uint32_t lo = 0, hi = a.n_bitmap_words;
+      while (hi - lo > 1) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (sum_below(mid) <= room)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      const uint32_t first = sum_below(lo);
+      uint32_t m = a.bitmap[lo];
+      for (uint32_t k = (uint32_t)room - first; k; --k) m &= m - 1;
+      overflow_e = 32 * lo + (uint32_t)__ffs(m) - 1;
+    }
+    if (t == 0) account_chunk(a, ans, answer_rank, winners, overflow_e);
+  }
 }
 
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void compact_winners(ChunkArgs a) {
-  if (a.st->stop) return;
+  // (the chunk is accounted already, the stop code may be its own; a block left
+  // by an earlier chunk, when a stop kept this one from being accounted, has
+  // that chunk's number)
+  if (a.ctrl->append != a.chunk_id) return;
   const uint32_t ans = a.ctrl->answer_e;
-  const uint64_t row_base = a.st->total_rows;
-  const uint64_t room = a.st->row_cap > row_base ? a.st->row_cap - row_base : 0;
+  const uint64_t row_base = a.ctrl->row_base, room = a.ctrl->room;
   for_survivors(a, [&](uint32_t sid, bool have) {
     if (!have) return;
     const uint32_t e = a.se[sid];
@@ -1131,18 +1193,14 @@ __global__ __launch_bounds__(256) void compact_winners(ChunkArgs a) {
     const uint32_t bit = 1u << (e & 31);
     if (!(word & bit)) return;
     const uint32_t rank = a.word_prefix[e >> 5] + (uint32_t)__popc(word & (bit - 1));
-    if (e == ans) a.ctrl->answer_rank = rank;
     if (ans != ~0u && e >= ans) return;
-    if (rank < room)
-      store_winner<W, kInl>(a, sid, e, row_base + rank);
-    else if (rank == room)
-      a.ctrl->overflow_e = e;
+    if (rank < room) store_winner<W, kInl>(a, sid, e, row_base + rank);
   });
 }
 
 __global__ void account_large(ChunkArgs a) {
   if (a.st->stop) return;
-  account_chunk(a, a.ctrl->answer_e, a.ctrl->answer_rank, a.ctrl->winners, a.ctrl->overflow_e);
+  account_chunk(a, a.ctrl->answer_e, ~0u, 0, ~0u);  // (no winners: nothing is stored)
 }
 
 inline uint32_t grid_for(uint64_t n, uint64_t block, uint32_t cap = 0x7fffffffu) {
@@ -1470,11 +1528,9 @@ hipError_t launch_finalize(int W, const ChunkArgs& a, hipStream_t s) {
   } else {
     const uint32_t nb = (a.n_bitmap_words + kScanBlock - 1) / kScanBlock;
     hipLaunchKernelGGL(scan_reduce, dim3(nb), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(scan_top, dim3(1), dim3(1024), 0, s, a, nb);
-    hipLaunchKernelGGL(scan_down, dim3(nb), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(scan_down, dim3(nb), dim3(256), 0, s, a, nb);
   }
   REI_DISPATCH_WI(W, a.inl, hipLaunchKernelGGL((compact_winners<kW, kI>), dim3(g), dim3(256), 0, s, a));
-  hipLaunchKernelGGL(account_large, dim3(1), dim3(1), 0, s, a);
   return hipGetLastError();
 }
 
