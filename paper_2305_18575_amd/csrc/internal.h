@@ -124,7 +124,7 @@ struct GenArgs {
 };
 
 // Tunable launch parameters of the per-chunk grid path (per word width):
-// the first chunk of a level (each next one doubles), the largest chunk,
+// the first chunk of a level (each next one is eight times larger), the largest chunk,
 // and the concatenation kernel's grid target and left rows per workgroup.
 // Results do not depend on them.
 struct GridTune {
