@@ -241,6 +241,10 @@ __device__ __forceinline__ bool table_find(const uint64_t* slots, uint64_t mask,
 // (at skey + sid * W) is read only where a slot is taken already: most
 // survivors claim an empty one (inline keys are the slots' contents).
 // old: the reference the slot held for this key before (EMPTY: none).
+// A plain read that already shows a smaller reference ends the insertion
+// without an atomic: references of a slot only fall while a chunk is
+// inserted, so a stale value can only be too large (one-word search 36.6 ->
+// 36.4 ms, two-word 13.47 -> 13.38 ms).
 template <int W, bool kInl>
 __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask, const uint64_t* rows,
                                                  const uint64_t* skey, uint32_t sid, uint64_t h, uint64_t mine,
@@ -250,11 +254,15 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask,
   if constexpr (kInl) {
     const uint64_t own = key[0];
     for (;;) {
-      uint64_t v = slots[2 * pos];
+      const ulonglong2 pair = *reinterpret_cast<const ulonglong2*>(slots + 2 * pos);
+      uint64_t v = pair.x;
       if (v == kEmpty) {
         v = atomicCAS((unsigned long long*)&slots[2 * pos], (unsigned long long)kEmpty,
                       (unsigned long long)own);
         if (v == kEmpty) v = own;  // claimed
+      } else if (v == own && pair.y < mine) {
+        *old = pair.y;
+        return pos;
       }
       if (v == own) {
         *old = atomicMin((unsigned long long*)&slots[2 * pos + 1], (unsigned long long)mine);
@@ -277,6 +285,10 @@ __device__ __forceinline__ uint64_t table_insert(uint64_t* slots, uint64_t mask,
       if (v & kNewFlag) {
         // another survivor owns the slot; its key never changes
         if (keys_equal<W>(skey + (uint64_t)(uint32_t)v * W, key)) {
+          if (v < mine) {
+            *old = v;
+            return pos;
+          }
           *old = atomicMin((unsigned long long*)&slots[pos], (unsigned long long)mine);
           return pos;
         }
