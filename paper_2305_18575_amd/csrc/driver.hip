@@ -744,6 +744,18 @@ rei_status marks_take(rei_instance* in, hipStream_t s, const std::vector<uint32_
   return REI_OK;
 }
 
+// Marks that a level of cost c has: its four constructors' and one per union
+// block.  Costs far apart leave most levels empty: (20,20,20,5,30) has 3-6
+// marks where c / 2 + 5 would be the bound, so that one launch takes all
+// levels of a search (7 us and a wait each; a search to cost 196 made 19
+// launches by the bound and took 840 us, now 738).
+uint32_t marks_of(const rei_instance* in, uint32_t c, std::vector<Block>* blocks) {
+  if (!make_blocks(in, c, blocks)) return kMaxMarks + 1;
+  uint32_t n = 4;
+  for (const Block& b : *blocks) n += b.op == OP_UNION;
+  return n;
+}
+
 // Marks of every stored level below c that has none yet.
 rei_status marks_below(rei_instance* in, hipStream_t s, uint32_t c) {
   std::vector<uint32_t> todo;
@@ -759,9 +771,10 @@ rei_status marks_below(rei_instance* in, hipStream_t s, uint32_t c) {
   };
   rei_status r;
   uint32_t entries = 0;
+  std::vector<Block> blocks;
   for (uint32_t k = in->costs.c_char; k < c; ++k) {
     if (in->marks[k].have || in->lcount[k] == 0) continue;
-    const uint32_t most = 4 + k / 2 + 1;  // unions: one block per left cost, at most half the level's cost
+    const uint32_t most = marks_of(in, k, &blocks);
     if (most > kMaxMarks) continue;
     if (entries + most > kMaxMarks) {
       if ((r = flush()) != REI_OK) return r;
@@ -1493,7 +1506,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     std::vector<uint32_t> own(1, c);
     std::vector<LevelMarks> plan;
     uint32_t own_marks = 0;
-    if (prune && !stopped && 4 + c / 2 + 1 <= kMaxMarks && (r = marks_launch(in, s, own, &plan, &own_marks)) != REI_OK)
+    if (prune && !stopped && (r = marks_launch(in, s, own, &plan, &own_marks)) != REI_OK)
       return r;
     // level boundary: the next level's blocks depend on this level's size
     if ((r = sync_state(in, s, false)) != REI_OK) return r;
@@ -1935,6 +1948,25 @@ bool batch_take_state(rei_instance* in) {
 constexpr uint64_t first_level_max(int W) { return W <= 4 ? 4096 : 128; }
 constexpr int kFirstLevelsMaxW = 16;
 constexpr uint64_t kFirstRows = 1ull << 15;
+// Costs far apart leave few levels below the solver's largest cost: a search
+// that goes beyond it with fewer than kFirstLevelsMin possible level costs up
+// to it starts on the per-chunk path, as its launch (130 us for the four
+// levels that (20,20,20,5,30) has) would cost more than their chains.
+constexpr uint32_t kFirstLevelsMin = 8;
+// Costs up to cap that an expression can have.
+uint32_t possible_levels(const rei_costs& k, uint32_t cap) {
+  std::vector<char> has(cap + 1, 0);
+  uint32_t n = 0;
+  for (uint32_t c = k.c_char; c <= cap; ++c) {
+    bool h = c == k.c_char || (c > k.c_question && has[c - k.c_question]) || (c > k.c_star && has[c - k.c_star]);
+    for (uint32_t op : {k.c_concat, k.c_union})
+      for (uint32_t l = k.c_char; !h && (uint64_t)op + 2 * (uint64_t)l <= c; ++l) h = has[l] && has[c - op - l];
+    has[c] = h;
+    n += h;
+  }
+  return n;
+}
+
 rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
   *complete = false;
   const uint32_t cap = std::min(in->max_cost, kBatchMaxCost);
@@ -1944,6 +1976,7 @@ rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
   if (in->st.W > kFirstLevelsMaxW || in->st.gt_pair.size() > batch_max_pairs(in->st.W) || !same_char_cost ||
       in->costs.c_char > cap || in->prof || in->chunk_max != kDefaultChunk)
     return REI_OK;
+  if (cap < in->max_cost && possible_levels(in->costs, cap) < kFirstLevelsMin) return REI_OK;
   rei_status r;
   const uint64_t R = std::max<uint64_t>(1024, std::min(in->row_cap, kFirstRows));
   if ((r = solver_buffers(in, R, true, s)) != REI_OK) return r;
