@@ -262,7 +262,8 @@ rei_status rei_tune_batch(rei_instance *const *insts, size_t n, void *hip_stream
 rei_status rei_tune_grid(rei_instance *const *insts, size_t n, void *hip_stream, uint64_t *params_out);
 /* The per-chunk path's launch parameters for one instance, overriding the
  * tuned table for its width (0 = keep the table's or the default value for
- * that field; defaults 2^16, 2^24, 2048, 16).  concat_xi at most 64.
+ * that field; defaults 2^16, 2^24, 2048, 16).  concat_xi at most 64.  Without
+ * a first_chunk set here, a level of at most four first chunks is one chunk.
  * Results do not depend on them; tests vary them to check that. */
 rei_status rei_set_grid_tuning(rei_instance *inst, uint64_t first_chunk, uint64_t chunk_max,
                                uint32_t concat_wg, uint32_t concat_xi);
