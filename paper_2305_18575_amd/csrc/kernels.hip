@@ -1100,7 +1100,8 @@ __global__ __launch_bounds__(1024) void scan_single(ChunkArgs a) {
 // accounts the chunk (a launch of its own at the end cost 4 us).
 __global__ __launch_bounds__(256) void scan_down(ChunkArgs a, uint32_t nb) {
   __shared__ uint32_t part[256];
-  __shared__ uint32_t s_base;
+  __shared__ uint32_t s_base, s_ans, s_stopped;
+  __shared__ uint64_t s_room;
   // (no look at the stop code before the last block's accounting, which may
   // set it while others have not started: a chunk after a stop writes prefixes
   // that nobody reads)
@@ -1113,7 +1114,17 @@ __global__ __launch_bounds__(256) void scan_down(ChunkArgs a, uint32_t nb) {
     if (t < st) part[t] += part[t + st];
     __syncthreads();
   }
-  if (t == 0) s_base = part[0];
+  if (t == 0) {
+    s_base = part[0];
+    if (b + 1 == nb) {
+      // what the accounting starts from, read once: thread 0 changes the state
+      // below while the other waves still decide by these
+      const uint64_t total = a.st->total_rows;
+      s_room = a.st->row_cap > total ? a.st->row_cap - total : 0;
+      s_ans = a.ctrl->answer_e;
+      s_stopped = a.st->stop;
+    }
+  }
   __syncthreads();
   uint32_t c[4], s = 0;
   for (uint32_t q = 0; q < 4; ++q) {
@@ -1135,7 +1146,7 @@ __global__ __launch_bounds__(256) void scan_down(ChunkArgs a, uint32_t nb) {
     if (w < a.n_bitmap_words) a.word_prefix[w] = run;
     run += c[q];
   }
-  if (b + 1 == nb && !a.st->stop) {
+  if (b + 1 == nb && !s_stopped) {
     const uint32_t winners = s_base + part[255];
     // winners below a word: the other blocks' prefixes may not be written
     // yet, so the sums and the words of its block are added up (one word for
@@ -1154,9 +1165,8 @@ __global__ __launch_bounds__(256) void scan_down(ChunkArgs a, uint32_t nb) {
       }
       return part[0];
     };
-    const uint32_t ans = a.ctrl->answer_e;
-    const uint64_t total = a.st->total_rows;
-    const uint64_t room = a.st->row_cap > total ? a.st->row_cap - total : 0;
+    const uint32_t ans = s_ans;
+    const uint64_t room = s_room;
     uint32_t answer_rank = ~0u, overflow_e = ~0u;
     if (ans != ~0u)
       answer_rank = sum_below(ans >> 5) + (uint32_t)__popc(a.bitmap[ans >> 5] & ((1u << (ans & 31)) - 1));
@@ -1170,9 +1180,11 @@ __global__ __launch_bounds__(256) void scan_down(ChunkArgs a, uint32_t nb) {
           hi = mid;
       }
       const uint32_t first = sum_below(lo);
-      uint32_t m = a.bitmap[lo];
-      for (uint32_t k = (uint32_t)room - first; k; --k) m &= m - 1;
-      overflow_e = 32 * lo + (uint32_t)__ffs(m) - 1;
+      if (t == 0) {
+        uint32_t m = a.bitmap[lo];
+        for (uint32_t k = (uint32_t)room - first; k; --k) m &= m - 1;
+        overflow_e = 32 * lo + (uint32_t)__ffs(m) - 1;
+      }
     }
     if (t == 0) account_chunk(a, ans, answer_rank, winners, overflow_e);
   }
