@@ -11,6 +11,7 @@
 #include <memory>
 #include <mutex>
 #include <thread>
+#include <tuple>
 #include <unordered_map>
 #include <cstdio>
 #include <cstdlib>
@@ -105,6 +106,7 @@ struct rei_instance {
   // grid-path launch parameters set for this instance (0: the process table
   // for its word width, else the defaults)
   GridTune grid_set{0, 0, 0, 0};
+  bool own_first_chunk = false;  // a first chunk was asked for: no level is one chunk beyond it
   uint64_t batch_level_max = 0;  // 0: the tuned value, else kBatchLevelMax
   int64_t batch_time_us = -1;    // -1: kBatchTimeUs; 0: no hand-off on time
   int device = 0;
@@ -1471,7 +1473,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     const GridTune gt = grid_params(in);
     const uint64_t cmax = std::max<uint64_t>(1, std::min(in->chunk_max, gt.chunk_max));
     uint64_t cur = std::min(cmax, gt.first_chunk);
-    if (!in->grid_set.first_chunk && level_total <= 4 * gt.first_chunk)
+    if (!in->own_first_chunk && level_total <= 4 * gt.first_chunk)
       cur = std::min(cmax, std::max<uint64_t>(level_total, 1));
     std::vector<Piece> pieces;
     std::vector<std::pair<uint64_t, uint64_t>> left;
@@ -2764,6 +2766,7 @@ rei_status rei_set_grid_tuning(rei_instance* inst, uint64_t first_chunk, uint64_
                                uint32_t concat_xi) {
   if (!inst || concat_xi > 64) return REI_ERR_INVALID_ARG;
   inst->grid_set = GridTune{first_chunk, chunk_max, concat_wg, concat_xi};
+  inst->own_first_chunk = first_chunk != 0;
   return REI_OK;
 }
 
@@ -2777,8 +2780,13 @@ rei_status rei_tune_grid(rei_instance* const* insts, size_t n, void* hip_stream,
     if (params_out) std::fill(params_out, params_out + 24, 0ull);
     for (auto& kv : by_w) {
       std::vector<rei_instance*>& grp = kv.second;
-      std::vector<GridTune> saved;
-      for (rei_instance* in : grp) saved.push_back(in->grid_set);
+      // the instances' own parameters, put back in the end; until then each
+      // chunks its levels as an instance that uses the table does
+      std::vector<std::pair<GridTune, bool>> saved;
+      for (rei_instance* in : grp) saved.push_back({in->grid_set, in->own_first_chunk});
+      auto put_back = [&] {
+        for (size_t k = 0; k < grp.size(); ++k) std::tie(grp[k]->grid_set, grp[k]->own_first_chunk) = saved[k];
+      };
       GridTune base;
       {
         std::lock_guard<std::mutex> lk(g_grid_mu);
@@ -2789,7 +2797,10 @@ rei_status rei_tune_grid(rei_instance* const* insts, size_t n, void* hip_stream,
       rei_status r = REI_OK;
       // the group's rei_solve calls one after another, best of three
       auto time_group = [&](const GridTune& t, double* out) -> rei_status {
-        for (rei_instance* in : grp) in->grid_set = t;
+        for (rei_instance* in : grp) {
+          in->grid_set = t;
+          in->own_first_chunk = false;
+        }
         double best = 1e300;
         for (int rep = 0; rep < 3; ++rep) {
           const double t0 = now_s();
@@ -2805,7 +2816,7 @@ rei_status rei_tune_grid(rei_instance* const* insts, size_t n, void* hip_stream,
       };
       double cur = 1e300;
       if ((r = time_group(base, &cur)) != REI_OK) {
-        for (size_t k = 0; k < grp.size(); ++k) grp[k]->grid_set = saved[k];
+        put_back();
         return r;
       }
       // one parameter at a time, each over a few values around the defaults
@@ -2833,7 +2844,7 @@ rei_status rei_tune_grid(rei_instance* const* insts, size_t n, void* hip_stream,
           (r = sweep(maxes, [](GridTune& t, uint64_t v) { t.chunk_max = v; })) == REI_OK &&
           (r = sweep(wgs, [](GridTune& t, uint32_t v) { t.concat_wg = v; })) == REI_OK)
         r = sweep(xis, [](GridTune& t, uint32_t v) { t.concat_xi = v; });
-      for (size_t k = 0; k < grp.size(); ++k) grp[k]->grid_set = saved[k];
+      put_back();
       if (r != REI_OK) return r;
       {
         std::lock_guard<std::mutex> lk(g_grid_mu);
