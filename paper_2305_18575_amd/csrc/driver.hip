@@ -3803,6 +3803,7 @@ struct rei_batch_graph {
   bool in_flight = false;
   double t0 = 0;
   std::unique_ptr<GridPool> pool;     // the replay's instances on the worker threads
+  std::vector<size_t> stale;          // of batched: buffers may have moved since the descriptor was written
   std::string err;
 };
 
@@ -3867,16 +3868,34 @@ rei_status graph_arena(rei_instance* in, uint64_t arena_bytes, hipStream_t s) {
   return solver_buffers(in, batch_rows(in, arena_bytes), false, s);
 }
 
+// Gives the instances that were solved outside the launches since an arena
+// that holds their rows, and has their descriptors follow the buffers they now
+// have: a replay must read no freed memory, so none starts before this is done
+// for all of them (the first that fails, and those after it, stay listed).
+rei_status graph_refresh(rei_batch_graph* g, hipStream_t s) {
+  while (!g->stale.empty()) {
+    const size_t i = g->stale.back();
+    rei_instance* in = g->batched[i];
+    rei_status r;
+    if ((r = graph_arena(in, g->arena, s)) != REI_OK) return r;
+    HIP_OK(in, hipStreamSynchronize(s));
+    g->h_desc[i] = graph_desc(in);
+    g->stale.pop_back();
+  }
+  return REI_OK;
+}
+
 // Results of one run of the launches (they have finished): every batched
 // instance's state from its pinned buffers.  Instances that ran out of
 // their preallocated rows, and those that are not batchable, run
-// rei_solve's path on the worker threads; the former then get an arena that
-// holds their rows, and their descriptors follow the buffers they now have,
-// so the next replay reads no freed memory.
+// rei_solve's path on the worker threads; the former are then made ready for
+// the next replay (also when one of them failed).
 rei_status graph_collect(rei_batch_graph* g, hipStream_t s) {
-  rei_status r;
+  rei_status first = REI_OK;
+  auto keep = [&](rei_status r) {
+    if (first == REI_OK) first = r;
+  };
   GridPool& pool = *g->pool;  // holds the other instances since the launch
-  std::vector<size_t> refresh;
   for (size_t i = 0; i < g->batched.size(); ++i) {
     rei_instance* in = g->batched[i];
     in->err.clear();
@@ -3884,27 +3903,18 @@ rei_status graph_collect(rei_batch_graph* g, hipStream_t s) {
     (void)begin_solve(in, g->t0);  // batchable instances are never trivial
     if (batch_take_state(in)) {
       in->resume_level = 0;  // a fresh search: the arena was not enough
-      refresh.push_back(i);
+      g->stale.push_back(i);
       pool.submit(in);
       continue;
     }
-    if ((r = finish_solve(in, g->t0)) != REI_OK) {
-      (void)pool.join();
-      return r;
-    }
+    keep(finish_solve(in, g->t0));
     if (seen >= 0) in->res.seconds_solve = seen;
     in->t_seen = -1;
   }
-  r = pool.join();
+  keep(pool.join());
   g->pool.reset();
-  if (r != REI_OK) return r;
-  for (size_t i : refresh) {
-    rei_instance* in = g->batched[i];
-    if ((r = graph_arena(in, g->arena, s)) != REI_OK) return r;
-    HIP_OK(in, hipStreamSynchronize(s));
-    g->h_desc[i] = graph_desc(in);
-  }
-  return REI_OK;
+  keep(graph_refresh(g, s));
+  return first;
 }
 
 }  // namespace
@@ -4114,6 +4124,13 @@ rei_status rei_batch_graph_launch(rei_batch_graph* g, void* hip_stream) {
     return REI_ERR_INVALID_ARG;
   }
   G_OK(g, hipSetDevice(g->device));
+  if (!g->stale.empty()) {  // an earlier replay's results ended in an error
+    const rei_status r = graph_refresh(g, (hipStream_t)hip_stream);
+    if (r != REI_OK) {
+      g->err = g->batched[g->stale.back()]->err;
+      return r;
+    }
+  }
   for (rei_instance* in : g->batched) {
     __atomic_store_n(&in->h_state->done, 0u, __ATOMIC_RELEASE);
     in->t_seen = -1;
