@@ -180,6 +180,8 @@ struct rei_instance {
   uint32_t otf_level = 0;
   bool otf_blocked = false;
   uint64_t pending = 0;
+  mutable bool no_memory = false;  // a device allocation of the running search was refused
+  uint64_t lean_chunk = 0;         // largest chunk of a search that is run again for that (0: the first try)
   int ctrl_turn = 0;        // the control block of the next chunk
   ChunkLaunches launches;   // of the chunk being enqueued
   uint32_t chunks_enq = 0;  // chunks enqueued on the per-chunk path since the state was reset
@@ -260,7 +262,6 @@ class BlockPool {
     const size_t n = cls <= most(host) ? cls : bytes;
     hipError_t e = fresh(host, n, out);
     if (e != hipSuccess) {  // idle blocks may be what is missing
-      (void)hipGetLastError();
       give_back();
       e = fresh(host, n, out);
     }
@@ -309,8 +310,14 @@ class BlockPool {
   static hipError_t fresh(bool host, size_t n, void** out) {
     // host: coherent (fine-grained), as the host reads flags and counters
     // in it while launches that write them still run
-    return host ? hipHostMalloc(out, n, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent)
-                : hipMalloc(out, n);
+    const hipError_t e =
+        host ? hipHostMalloc(out, n, hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent)
+             : hipMalloc(out, n);
+    if (e != hipSuccess) {
+      *out = nullptr;
+      (void)hipGetLastError();  // (the caller may go on without: no later launch reports it)
+    }
+    return e;
   }
   static void release(bool host, void* p) {
     if (host)
@@ -332,10 +339,27 @@ template <class T>
 hipError_t dev_alloc(const rei_instance* in, T** p, size_t bytes) {
   if (in->alloc.alloc) {
     *p = (T*)in->alloc.alloc(bytes, in->alloc.ctx);
-    if (!*p) return hipErrorOutOfMemory;
+    if (!*p) {
+      in->no_memory = true;
+      return hipErrorOutOfMemory;
+    }
     return hipDeviceSynchronize();
   }
-  return BlockPool::get().take(in->device, false, bytes, (void**)p);
+  const hipError_t e = BlockPool::get().take(in->device, false, bytes, (void**)p);
+  in->no_memory = in->no_memory || e == hipErrorOutOfMemory;
+  return e;
+}
+
+// The same for want bytes or, where these are refused, the need (<= want)
+// that the caller cannot do without.  *got: the one it became.
+template <class T>
+hipError_t dev_alloc_at_least(const rei_instance* in, T** p, size_t want, size_t need, size_t* got) {
+  *got = want;
+  const hipError_t e = dev_alloc(in, p, want);
+  if (e != hipErrorOutOfMemory || need >= want) return e;
+  in->no_memory = false;
+  *got = need;
+  return dev_alloc(in, p, need);
 }
 
 // (no work that uses the block may be left)
@@ -446,11 +470,14 @@ rei_status prof_collect(rei_instance* in) {
 
 rei_status ensure_rows(rei_instance* in, uint64_t need, hipStream_t s) {
   if (need <= in->rows_alloc) return REI_OK;
-  uint64_t cap = std::max<uint64_t>({need, 2 * in->rows_alloc, 1024});
+  uint64_t cap = std::max<uint64_t>({need, 2 * in->rows_alloc, in->lean_chunk ? 64u : 1024u});
   const int W = in->st.W;
   // one block: rows, then back-pointers
+  auto bytes = [&](uint64_t rows) { return aligned(rows * W * 8) + rows * 8; };
   uint64_t* nr = nullptr;
-  HIP_OK(in, dev_alloc(in, &nr, aligned(cap * W * 8) + cap * 8));
+  size_t got = 0;
+  HIP_OK(in, dev_alloc_at_least(in, &nr, bytes(cap), bytes(need), &got));
+  if (got < bytes(cap)) cap = need;
   uint64_t* na = nr + aligned(cap * W * 8) / 8;
   if (in->known_rows) {
     HIP_OK(in, hipMemcpyAsync(nr, in->d_rows, in->known_rows * W * 8, hipMemcpyDeviceToDevice, s));
@@ -467,21 +494,28 @@ rei_status ensure_rows(rei_instance* in, uint64_t need, hipStream_t s) {
 // Bytes per table slot: with inline keys a pair, the key and its reference.
 uint64_t slot_bytes(const rei_instance* in) { return in->inl ? 16 : 8; }
 
-// A table of cap slots (not filled) in place of the present one.
-rei_status table_alloc(rei_instance* in, uint64_t cap) {
+// Slots of the smallest table.
+uint64_t least_slots(const rei_instance* in) { return in->lean_chunk ? 256 : 4096; }
+
+// A table of cap slots (not filled) in place of the present one, or of `least`
+// where there is no memory for cap.
+rei_status table_alloc(rei_instance* in, uint64_t cap, uint64_t least) {
   dfree(in, in->d_slots);
   in->slots_cap = 0;
-  HIP_OK(in, dev_alloc(in, &in->d_slots, cap * slot_bytes(in)));
-  in->slots_cap = cap;
+  size_t got = 0;
+  HIP_OK(in, dev_alloc_at_least(in, &in->d_slots, cap * slot_bytes(in), least * slot_bytes(in), &got));
+  in->slots_cap = got / slot_bytes(in);
   return REI_OK;
 }
 
 // The table keeps its load at most 1/2: entries = stored rows + possible new ones.
 rei_status ensure_table(rei_instance* in, uint64_t entries, hipStream_t s) {
   if (in->slots_cap >= 2 * entries) return REI_OK;
-  uint64_t cap = std::max<uint64_t>(4096, pow2_at_least(4 * entries));
   rei_status r;
-  if (cap != in->slots_cap && (r = table_alloc(in, cap)) != REI_OK) return r;
+  if ((r = table_alloc(in, std::max(least_slots(in), pow2_at_least(4 * entries)),
+                       std::max(least_slots(in), pow2_at_least(2 * entries)))) != REI_OK)
+    return r;
+  const uint64_t cap = in->slots_cap;
   LAUNCH(in, s, REI_K_OTHER, cap, launch_fill(in->d_slots, cap * (slot_bytes(in) / 8), kEmpty, s));
   LAUNCH(in, s, REI_K_OTHER, in->known_rows,
          launch_rehash(in->st.W, in->inl, in->d_rows, in->known_rows, in->d_slots, cap - 1, s));
@@ -500,14 +534,12 @@ rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, 
     dfree(in, in->d_skey);
     in->surv_cap = 0;
     uint64_t n = std::max(slots * ahead, ahead > 1 || slots > kBatchChunk ? slots + slots / 8 : slots);
+    if (in->lean_chunk) n = slots;
     // one block: keys, slot records, indices
     auto bytes = [&](uint64_t k) { return aligned(k * W * 8) + aligned(k * 8) + k * 4; };
-    if (n > slots && dev_alloc(in, &in->d_skey, bytes(n)) != hipSuccess) {
-      (void)hipGetLastError();
-      in->d_skey = nullptr;
-      n = slots;
-    }
-    if (!in->d_skey) HIP_OK(in, dev_alloc(in, &in->d_skey, bytes(n)));
+    size_t got = 0;
+    HIP_OK(in, dev_alloc_at_least(in, &in->d_skey, bytes(n), bytes(slots), &got));
+    if (got < bytes(n)) n = slots;
     in->d_spos = in->d_skey + aligned(n * W * 8) / 8;
     in->d_se = (uint32_t*)(in->d_spos + aligned(n * 8) / 8);
     in->surv_cap = n;
@@ -515,7 +547,7 @@ rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, 
   if (regions > in->reg_cap) {
     dfree(in, in->d_reg);
     in->reg_cap = 0;
-    const uint64_t cap = std::max<uint64_t>(4096, pow2_at_least(regions));
+    const uint64_t cap = in->lean_chunk ? regions : std::max<uint64_t>(4096, pow2_at_least(regions));
     HIP_OK(in, dev_alloc(in, &in->d_reg, cap * sizeof(uint2)));
     in->reg_cap = cap;
   }
@@ -984,7 +1016,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions, s)) != REI_OK) return r;
     } else {
       const uint64_t most = std::max(len, std::min(in->chunk_max, grid_params(in).chunk_max));
-      const uint64_t ahead = std::min<uint64_t>(8, std::max<uint64_t>(1, most / len));
+      const uint64_t ahead = in->lean_chunk ? 1 : std::min<uint64_t>(8, std::max<uint64_t>(1, most / len));
       if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s, ahead)) != REI_OK) return r;
       if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + generated), s)) != REI_OK) return r;
       if ((r = ensure_table(in, in->known_rows + generated, s)) != REI_OK) return r;
@@ -1250,6 +1282,7 @@ bool begin_solve(rei_instance* in, double t0) {
   in->aux_view = nullptr;
   in->tree.clear();
   in->resume_level = 0;
+  in->lean_chunk = 0;
   in->otf_level = 0;
   in->otf_blocked = false;
   if (in->max_cost < c1) {
@@ -1358,7 +1391,7 @@ rei_status device_tree(rei_instance* in, hipStream_t s) {
 
 // The per-chunk search on the grid: chunks are enqueued without waiting,
 // with one wait per cost level.
-rei_status search_levels(rei_instance* in, hipStream_t s) {
+rei_status search_run(rei_instance* in, hipStream_t s) {
   const uint32_t c1 = in->costs.c_char;
   const uint64_t L = in->max_cost + 2;
   rei_status r;
@@ -1412,7 +1445,8 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     hs->chunks = 0;
     // the batched solver used a prefix of the table: rebuild it at full size
     if (in->slots_cap < 2 * (in->known_rows + 1024) &&
-        (r = table_alloc(in, pow2_at_least(4 * (in->known_rows + 1024)))) != REI_OK)
+        (r = table_alloc(in, pow2_at_least(4 * (in->known_rows + 1024)), pow2_at_least(2 * (in->known_rows + 1024)))) !=
+            REI_OK)
       return r;
     ra.total_rows = in->known_rows;
     ra.levels = in->d_levels;
@@ -1427,7 +1461,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     // a fresh search: nothing stored yet (also when a batched attempt ran out
     // of its preallocated rows and left some behind)
     in->known_rows = 0;
-    if (in->slots_cap == 0 && (r = table_alloc(in, 4096)) != REI_OK) return r;
+    if (in->slots_cap == 0 && (r = table_alloc(in, least_slots(in), least_slots(in))) != REI_OK) return r;
     ra.levels = in->d_levels;
     ra.n_levels = 3 * L;
     ra.slots = in->d_slots;
@@ -1471,9 +1505,10 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
     const bool prune = level_total >= kPruneMin && !in->otf_level;
     if (prune && (r = marks_below(in, s, c)) != REI_OK) return r;
     const GridTune gt = grid_params(in);
-    const uint64_t cmax = std::max<uint64_t>(1, std::min(in->chunk_max, gt.chunk_max));
+    const uint64_t cmax =
+        std::max<uint64_t>(1, std::min<uint64_t>({in->chunk_max, gt.chunk_max, in->lean_chunk ? in->lean_chunk : ~0ull}));
     uint64_t cur = std::min(cmax, gt.first_chunk);
-    if (!in->own_first_chunk && level_total <= 4 * gt.first_chunk)
+    if (!in->own_first_chunk && !in->lean_chunk && level_total <= 4 * gt.first_chunk)
       cur = std::min(cmax, std::max<uint64_t>(level_total, 1));
     std::vector<Piece> pieces;
     std::vector<std::pair<uint64_t, uint64_t>> left;
@@ -1496,7 +1531,7 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
           pieces.clear();
           chunk_e0 += acc;
           acc = 0;
-          cur = std::min(cmax, 8 * cur);
+          cur = std::min(cmax, (in->lean_chunk ? 2 : 8) * cur);
         }
       }
       if (stopped) break;
@@ -1527,6 +1562,34 @@ rei_status search_levels(rei_instance* in, hipStream_t s) {
   if (in->h_state->stop == STOP_ANSWER) return device_tree(in, s);
   if (!in->h_state->stop) HIP_OK(in, hipStreamSynchronize(s));
   return REI_OK;
+}
+
+// The search, from the level it is resumed at.  Where the device has no memory
+// for it, it is run again from the start with what it held given back and
+// nothing taken ahead: buffers as small as each chunk needs, chunks that only
+// double, up to 2^24, then 2^18, then 2^12 candidates.  (Few large chunks, a
+// one-workgroup start and joined buffers that grow ahead take 1.5 to 30 times
+// the memory of a small search and up to 4 times that of a mid-sized one; a
+// caller's allocator may have less.)  Nothing of the search is left on s when
+// it returns an error: its blocks may be lent to another instance next.
+void free_search_buffers(rei_instance* in);
+constexpr uint64_t kLeanChunks[] = {1ull << 24, 1ull << 18, 1ull << 12};
+rei_status search_levels(rei_instance* in, hipStream_t s) {
+  in->no_memory = false;
+  rei_status r = search_run(in, s);
+  if (r != REI_OK) (void)hipStreamSynchronize(s);
+  for (uint64_t chunk : kLeanChunks) {
+    if (r == REI_OK || !in->no_memory) break;
+    free_search_buffers(in);
+    in->err.clear();
+    in->no_memory = false;
+    in->resume_level = 0;
+    in->lean_chunk = chunk;
+    r = search_run(in, s);
+    in->lean_chunk = 0;
+    if (r != REI_OK) (void)hipStreamSynchronize(s);
+  }
+  return r;
 }
 
 rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete);
@@ -1800,7 +1863,7 @@ rei_status solver_buffers(rei_instance* in, uint64_t R, bool only_r, hipStream_t
   if ((r = ensure_chunk_buffers(in, kBatchChunk, 0, 0, s)) != REI_OK) return r;
   if ((r = ensure_rows(in, R, s)) != REI_OK) return r;
   const uint64_t entries = 2 * ((only_r ? R : in->rows_alloc) + kBatchChunk);
-  if (in->slots_cap < entries) return table_alloc(in, pow2_at_least(entries));
+  if (in->slots_cap < entries) return table_alloc(in, pow2_at_least(entries), pow2_at_least(entries));
   return REI_OK;
 }
 
@@ -1981,7 +2044,14 @@ rei_status first_levels(rei_instance* in, hipStream_t s, bool* complete) {
   if (cap < in->max_cost && possible_levels(in->costs, cap) < kFirstLevelsMin) return REI_OK;
   rei_status r;
   const uint64_t R = std::max<uint64_t>(1024, std::min(in->row_cap, kFirstRows));
-  if ((r = solver_buffers(in, R, true, s)) != REI_OK) return r;
+  in->no_memory = false;
+  if ((r = solver_buffers(in, R, true, s)) != REI_OK) {
+    // (the per-chunk path's buffers grow with the search and may do with less)
+    if (!in->no_memory) return r;
+    free_search_buffers(in);
+    in->err.clear();
+    return REI_OK;
+  }
   DescBuf db;
   if ((r = desc_acquire(in, 1, &db)) != REI_OK) return r;
   BatchDesc d = make_desc(in);

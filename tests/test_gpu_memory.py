@@ -60,6 +60,55 @@ def assert_equal(got, want, specs):
         assert mismatch(g, o, specs[k].max_cost) is None, (k, mismatch(g, o, specs[k].max_cost))
 
 
+def type1(seed, p, le, costs, max_cost):
+    return instances.type1_instance(seed, p, p, le, costs=costs, max_cost=max_cost)
+
+
+def capped(it, max_cost):
+    it.max_cost = min(it.max_cost, max_cost)
+    return it
+
+
+# (specification, cache bytes, device bytes): bytes that a search needs which
+# allocates for one chunk after the other, chunks of a level doubling from 2^16
+LIMITS = {
+    "plain": (lambda: capped(instances.plain_instance(3), 12), 64 << 20, 82860),
+    "single, 797 candidates": (lambda: instances.single_instance(8), 1 << 30, 263588),
+    "single, 7092 candidates": (lambda: instances.single_instance(6), 1 << 30, 2078372),
+    "single, 226958 candidates": (lambda: instances.single_instance(3, (1, 1, 5, 1, 2)), 1 << 30, 22029692),
+    "one word, 41656 candidates": (lambda: type1(1, 10, 5, (1, 1, 1, 1, 1), 11), 4 << 30, 4020012),
+    "one word, 1037685 candidates": (lambda: type1(13, 8, 6, (1, 1, 1, 1, 1), 14), 4 << 30, 66891192),
+    "two words, 1473413 candidates": (lambda: type1(7, 12, 7, (1, 1, 10, 1, 1), 16), 4 << 30, 97469536),
+    "16 words": (lambda: capped(instances.large_instance(0), 8), 1 << 30, 4677548),
+    "32 words": (lambda: instances.wide_instance(3, 8), 1 << 30, 8876324),
+}
+
+
+@pytest.mark.parametrize("name", list(LIMITS))
+def test_search_fits_the_memory_of_its_chunks(rei, name):
+    """Nothing that is taken for speed alone (the one-workgroup start, large
+    first chunks, buffers that grow ahead) turns a search away."""
+    make, cache, limit = LIMITS[name]
+    it = make()
+    want = oracle_of([it], cache)
+    with memory(rei) as m:
+        m.limit = limit
+        print(f"\n{name}: {limit} bytes", flush=True)
+        h = handles(rei, [it], cache)[0]
+        assert_equal([h.solve()], want, [it])
+        print(f"{m.refused} allocations refused", flush=True)
+        h.close()
+        assert not m.live
+        h = handles(rei, [it], cache)[0]
+        m.limit = m.bytes
+        with pytest.raises(rei.ReiError):  # with nothing at all it ends in an error
+            h.solve()
+        m.limit = 1 << 62
+        assert_equal([h.solve()], want, [it])
+        h.close()
+        assert not m.live
+
+
 @pytest.mark.parametrize("calls", [0, 1, 3, 8])
 def test_graph_replay_after_a_failed_one(rei, calls):
     """Instances that outgrow a replay's arenas are solved outside it, in
