@@ -182,6 +182,7 @@ struct rei_instance {
   uint64_t pending = 0;
   mutable bool no_memory = false;  // a device allocation of the running search was refused
   uint64_t lean_chunk = 0;         // largest chunk of a search that is run again for that (0: the first try)
+  bool served = false;             // by a server, which counts device bytes: nothing is taken ahead
   int ctrl_turn = 0;        // the control block of the next chunk
   ChunkLaunches launches;   // of the chunk being enqueued
   uint32_t chunks_enq = 0;  // chunks enqueued on the per-chunk path since the state was reset
@@ -259,17 +260,23 @@ class BlockPool {
         return hipSuccess;
       }
     }
-    const size_t n = cls <= most(host) ? cls : bytes;
+    const size_t n = held(host, bytes);
     hipError_t e = fresh(host, n, out);
     if (e != hipSuccess) {  // idle blocks may be what is missing
       give_back();
       e = fresh(host, n, out);
     }
+    if (e != hipSuccess && n > bytes) return fresh(host, bytes, out);  // (freed at its end, not kept)
     if (e == hipSuccess && cls <= most(host)) {
       std::lock_guard<std::mutex> lk(mu_);
       lent_[*out] = cls;
     }
     return e;
+  }
+  // Bytes that a block of this many takes.
+  static size_t held(bool host, size_t bytes) {
+    const size_t cls = size_class_of(bytes);
+    return cls <= most(host) ? cls : bytes;
   }
   void put(int device, bool host, void* p) {
     {
@@ -534,7 +541,7 @@ rei_status ensure_chunk_buffers(rei_instance* in, uint64_t slots, uint64_t len, 
     dfree(in, in->d_skey);
     in->surv_cap = 0;
     uint64_t n = std::max(slots * ahead, ahead > 1 || slots > kBatchChunk ? slots + slots / 8 : slots);
-    if (in->lean_chunk) n = slots;
+    if (in->lean_chunk || in->served) n = slots;
     // one block: keys, slot records, indices
     auto bytes = [&](uint64_t k) { return aligned(k * W * 8) + aligned(k * 8) + k * 4; };
     size_t got = 0;
@@ -1016,7 +1023,7 @@ rei_status enqueue_chunk(rei_instance* in, hipStream_t s, uint32_t c, const std:
       if ((r = ensure_chunk_buffers(in, 0, 0, sp.regions, s)) != REI_OK) return r;
     } else {
       const uint64_t most = std::max(len, std::min(in->chunk_max, grid_params(in).chunk_max));
-      const uint64_t ahead = in->lean_chunk ? 1 : std::min<uint64_t>(8, std::max<uint64_t>(1, most / len));
+      const uint64_t ahead = in->lean_chunk || in->served ? 1 : std::min<uint64_t>(8, std::max<uint64_t>(1, most / len));
       if ((r = ensure_chunk_buffers(in, sp.slots, len, sp.regions, s, ahead)) != REI_OK) return r;
       if ((r = ensure_rows(in, std::min(in->row_cap, in->known_rows + generated), s)) != REI_OK) return r;
       if ((r = ensure_table(in, in->known_rows + generated, s)) != REI_OK) return r;
@@ -1867,11 +1874,13 @@ rei_status solver_buffers(rei_instance* in, uint64_t R, bool only_r, hipStream_t
   return REI_OK;
 }
 
-// Device bytes a batched instance uses (rows, back-pointers, table, survivors).
+// Device bytes a batched instance uses (rows, back-pointers, table, survivors;
+// small blocks are rounded up to be kept for other instances later).
 uint64_t batch_reserve(const rei_instance* in, uint64_t arena_bytes) {
   const uint64_t R = batch_rows(in, arena_bytes);
   const uint64_t W = in->st.W;
-  return R * (8 * W + 8) + pow2_at_least(4 * (R + kBatchChunk)) * 8 + kBatchChunk * (8 * W + 12);
+  auto held = [&](uint64_t bytes) { return in->alloc.alloc ? bytes : BlockPool::held(false, bytes); };
+  return held(R * (8 * W + 8)) + held(pow2_at_least(4 * (R + kBatchChunk)) * 8) + held(kBatchChunk * (8 * W + 12));
 }
 
 // Trivial instances are finished at once, others that cannot be batched go to
@@ -3310,6 +3319,7 @@ void server_finish(rei_server* sv, uint64_t t, rei_status st) {
   q.res = q.in->res;
   q.t_done = now_s();
   q.res.seconds_solve = q.t_done - q.t_submit;
+  q.in->served = false;
   q.done = true;
   sv->in_use -= q.reserve;
   sv->cv_done.notify_all();
@@ -3768,6 +3778,7 @@ rei_status rei_server_submit(rei_server* sv, rei_instance* inst, uint64_t* ticke
   q.in = inst;
   q.t_submit = now_s();
   q.reserve = request_reserve(sv, inst);
+  inst->served = true;
   sv->reqs[t] = q;
   sv->queue.push_back(t);
   sv->cv_sched.notify_all();

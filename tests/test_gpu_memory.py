@@ -19,6 +19,7 @@ class Memory:
 
     def __init__(self):
         self.live, self.bytes, self.limit, self.calls, self.refused = {}, 0, 1 << 62, 1 << 62, 0
+        self.peak = 0
 
     def alloc(self, n):
         import torch
@@ -29,6 +30,7 @@ class Memory:
         p = torch.cuda.caching_allocator_alloc(n, 0)
         self.live[p] = n
         self.bytes += n
+        self.peak = max(self.peak, self.bytes)
         return p
 
     def free(self, p):
@@ -107,6 +109,27 @@ def test_search_fits_the_memory_of_its_chunks(rei, name):
         assert_equal([h.solve()], want, [it])
         h.close()
         assert not m.live
+
+
+@pytest.mark.parametrize("queue", [True, False])
+def test_served_request_takes_nothing_ahead(rei, queue):
+    """A server admits requests by the bytes they need.  One whose last level
+    leaves its workgroup holds its arena (16 MB of 24-byte rows, a table of load
+    at most 1/2) and the survivors of one chunk: 28 bytes a candidate."""
+    it = instances.single_instance(3, (1, 1, 5, 1, 2))
+    want = oracle_of([it], 1 << 30)
+    rows = (16 << 20) // 24
+    with memory(rei) as m:
+        h = handles(rei, [it], 1 << 30)[0]
+        srv = rei.Server(1 << 30, 64, 2, 2, queue=queue)
+        res = srv.wait(srv.submit(h))[0]
+        srv.close()
+        need = 24 * rows + 8 * (1 << 21) + 28 * max(res.candidates) + (1 << 20)
+        print(f"\npeak {m.peak}, need {need}", flush=True)
+        assert_equal([res], want, [it])
+        assert max(res.candidates) > 1 << 16 and 2 * (rows + 8192) <= 1 << 21 and sum(res.unique) < rows
+        assert m.peak <= need
+        h.close()
 
 
 @pytest.mark.parametrize("calls", [0, 1, 3, 8])
