@@ -20,6 +20,7 @@
 #include <string>
 #include <vector>
 
+#include "block_pool.h"
 #include "internal.h"
 
 using namespace rei;
@@ -232,89 +233,11 @@ namespace {
     }                                                                                  \
   } while (0)
 
-// Idle blocks of destroyed instances, kept for new ones: a solve that is asked
-// once (created, solved, destroyed) otherwise spends most of its time
-// allocating.  Pinned host blocks above all (34-120 us to allocate, 60-160 us
-// to free, three per instance before; 64 KB at most each, 4 MB kept), and
-// device blocks of up to 4 MB (16 us, 7 us to free; 64 MB kept per process).
-// A block comes here only when no work that uses it is left (rei_destroy
-// waits for the device as a free would), so any stream may take it.
-// Beyond the bounds blocks are freed; rei_trim gives all idle ones back.
-// Thread-safe; never destroyed (the process's end frees it).
-class BlockPool {
- public:
-  static BlockPool& get() {
-    static BlockPool* p = new BlockPool();
-    return *p;
-  }
-  hipError_t take(int device, bool host, size_t bytes, void** out) {
-    const size_t cls = size_class_of(bytes);
-    if (cls <= most(host)) {
-      std::lock_guard<std::mutex> lk(mu_);
-      auto it = idle_.find({device, host, cls});
-      if (it != idle_.end() && !it->second.empty()) {
-        *out = it->second.back();
-        it->second.pop_back();
-        kept_[host] -= cls;
-        lent_[*out] = cls;
-        return hipSuccess;
-      }
-    }
-    const size_t n = held(host, bytes);
-    hipError_t e = fresh(host, n, out);
-    if (e != hipSuccess) {  // idle blocks may be what is missing
-      give_back();
-      e = fresh(host, n, out);
-    }
-    if (e != hipSuccess && n > bytes) return fresh(host, bytes, out);  // (freed at its end, not kept)
-    if (e == hipSuccess && cls <= most(host)) {
-      std::lock_guard<std::mutex> lk(mu_);
-      lent_[*out] = cls;
-    }
-    return e;
-  }
-  // Bytes that a block of this many takes.
-  static size_t held(bool host, size_t bytes) {
-    const size_t cls = size_class_of(bytes);
-    return cls <= most(host) ? cls : bytes;
-  }
-  void put(int device, bool host, void* p) {
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      auto it = lent_.find(p);
-      if (it != lent_.end()) {
-        const size_t cls = it->second;
-        lent_.erase(it);
-        if (kept_[host] + cls <= bound(host)) {
-          idle_[{device, host, cls}].push_back(p);
-          kept_[host] += cls;
-          return;
-        }
-      }
-    }
-    release(host, p);
-  }
-  // Frees every idle block.
-  void give_back() {
-    std::map<std::tuple<int, bool, size_t>, std::vector<void*>> all;
-    {
-      std::lock_guard<std::mutex> lk(mu_);
-      all.swap(idle_);
-      kept_[0] = kept_[1] = 0;
-    }
-    for (auto& x : all)
-      for (void* p : x.second) release(std::get<1>(x.first), p);
-  }
-
- private:
-  static size_t most(bool host) { return host ? 64u << 10 : 4u << 20; }
-  static size_t bound(bool host) { return host ? 4u << 20 : 64u << 20; }
-  static size_t size_class_of(size_t bytes) {
-    size_t c = 4096;
-    while (c < bytes) c <<= 1;
-    return c;
-  }
-  static hipError_t fresh(bool host, size_t n, void** out) {
+// The device's memory and pinned host memory, as BlockPool takes them.
+struct HipMemory {
+  using Error = hipError_t;
+  static constexpr Error kOk = hipSuccess;
+  static Error take(bool host, size_t n, void** out) {
     // host: coherent (fine-grained), as the host reads flags and counters
     // in it while launches that write them still run
     const hipError_t e =
@@ -326,17 +249,14 @@ class BlockPool {
     }
     return e;
   }
-  static void release(bool host, void* p) {
+  static void give(bool host, void* p) {
     if (host)
       (void)hipHostFree(p);
     else
       (void)hipFree(p);
   }
-  std::mutex mu_;
-  std::map<std::tuple<int, bool, size_t>, std::vector<void*>> idle_;
-  std::unordered_map<void*, size_t> lent_;  // size class of each block of a class that is in use
-  size_t kept_[2] = {0, 0};
 };
+using Pool = BlockPool<HipMemory>;
 
 // A caller's allocator may order its reuse of memory by some stream of its
 // own, which the library's streams do not follow: the device is drained after
@@ -352,7 +272,7 @@ hipError_t dev_alloc(const rei_instance* in, T** p, size_t bytes) {
     }
     return hipDeviceSynchronize();
   }
-  const hipError_t e = BlockPool::get().take(in->device, false, bytes, (void**)p);
+  const hipError_t e = Pool::get().take(in->device, false, bytes, (void**)p);
   in->no_memory = in->no_memory || e == hipErrorOutOfMemory;
   return e;
 }
@@ -377,7 +297,7 @@ void dfree(const rei_instance* in, T*& p) {
       (void)hipDeviceSynchronize();
       in->alloc.free_((void*)p, in->alloc.ctx);
     } else {
-      BlockPool::get().put(in->device, false, (void*)p);
+      Pool::get().put(in->device, false, (void*)p);
     }
   }
   p = nullptr;
@@ -1879,7 +1799,7 @@ rei_status solver_buffers(rei_instance* in, uint64_t R, bool only_r, hipStream_t
 uint64_t batch_reserve(const rei_instance* in, uint64_t arena_bytes) {
   const uint64_t R = batch_rows(in, arena_bytes);
   const uint64_t W = in->st.W;
-  auto held = [&](uint64_t bytes) { return in->alloc.alloc ? bytes : BlockPool::held(false, bytes); };
+  auto held = [&](uint64_t bytes) { return in->alloc.alloc ? bytes : Pool::held(false, bytes); };
   return held(R * (8 * W + 8)) + held(pow2_at_least(4 * (R + kBatchChunk)) * 8) + held(kBatchChunk * (8 * W + 12));
 }
 
@@ -2280,7 +2200,7 @@ void free_device(rei_instance* in) {
   (void)hipDeviceSynchronize();  // blocks may be lent again at once
   free_search_buffers(in);
   dfree(in, in->d_tables);
-  if (in->h_state) BlockPool::get().put(in->device, true, in->h_state);
+  if (in->h_state) Pool::get().put(in->device, true, in->h_state);
   in->h_state = nullptr;
   in->h_levels = nullptr;
   in->h_tree = nullptr;
@@ -2331,16 +2251,16 @@ rei_status create_device(rei_instance* in) {
   in->d_levels = (uint64_t*)(base + o_levels);
   {
     void* stage = nullptr;
-    HIP_OK(in, BlockPool::get().take(in->device, true, copied, &stage));
+    HIP_OK(in, Pool::get().take(in->device, true, copied, &stage));
     for (const Part& p : parts)
       if (p.bytes) std::memcpy((char*)stage + p.off, p.src, p.bytes);
     const hipError_t e = hipMemcpy(base, stage, copied, hipMemcpyHostToDevice);
-    BlockPool::get().put(in->device, true, stage);
+    Pool::get().put(in->device, true, stage);
     HIP_OK(in, e);
   }
   const uint64_t h_levels = aligned(sizeof(DevState)), h_tree = h_levels + aligned(3 * L * 8);
   void* h = nullptr;
-  HIP_OK(in, BlockPool::get().take(in->device, true, h_tree + (1 + 4 * kBatchTreeNodes + kMaxMarks + 1) * 8, &h));
+  HIP_OK(in, Pool::get().take(in->device, true, h_tree + (1 + 4 * kBatchTreeNodes + kMaxMarks + 1) * 8, &h));
   in->h_state = (DevState*)h;
   in->h_levels = (uint64_t*)((char*)h + h_levels);
   in->h_tree = (uint64_t*)((char*)h + h_tree);
@@ -2500,7 +2420,12 @@ rei_status rei_create(const char* alphabet, const char* const* pos, size_t n_pos
   in->cache_bytes = cache_bytes;
   in->row_cap = cache_bytes / (8ull * in->st.W + 8);
   in->inl = in->st.W == 1 && in->st.n <= 63;
-  if ((st = create_device(in)) != REI_OK) {
+  try {
+    st = create_device(in);
+  } catch (const std::bad_alloc&) {
+    st = REI_ERR_HOST_ALLOC;
+  }
+  if (st != REI_OK) {
     g_create_error = in->err;
     free_device(in);
     delete in;
@@ -3101,7 +3026,7 @@ rei_status rei_trim(rei_instance* inst) {
   HIP_OK(inst, hipSetDevice(inst->device));
   HIP_OK(inst, hipDeviceSynchronize());
   free_search_buffers(inst);
-  BlockPool::get().give_back();
+  Pool::get().give_back();
   // no rows left to inspect (the result's counts live in uniq / cand)
   std::fill(inst->lstart.begin(), inst->lstart.end(), 0);
   std::fill(inst->lcount.begin(), inst->lcount.end(), 0);
