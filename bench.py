@@ -50,9 +50,9 @@ PROBE_BYTES = 64
 # profiler invocation.  The profile each figure comes from is named beside it.
 # An entry is removed when its kernel changes.
 TRAFFIC = {
-    ("large", "gen_pieces"): (10707892, "profiles/large_workload_kernels.md (16-word launches of the timed and event steps)"),
-    ("row1", "gen_concat"): (441034010, "profiles/table1_row1_kernels.md (launches of the timed and event steps)"),
-    ("single", "solve_batch"): (43782586, "profiles/single_workload_kernels.md (both word widths' launches of the timed and event steps)"),
+    ("large", "gen_pieces"): (8824428, "profiles/large_workload_kernels.md (16-word launches of the timed and event steps)"),
+    ("row1", "gen_concat"): (441027290, "profiles/table1_row1_kernels.md (launches of the timed and event steps)"),
+    ("single", "solve_batch"): (50676539, "profiles/single_workload_kernels.md (both word widths' launches of the timed and event steps)"),
 }
 
 

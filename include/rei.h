@@ -125,7 +125,7 @@ rei_status rei_solve(rei_instance *inst, void *hip_stream, rei_result *out);
  * tree is decoded there too).  An instance whose next level has more
  * candidates than the hand-off size (rei_set_batch_level; 2^16 by default, 2^11
  * for languages of 8 words or more when at most 8 such instances are in the
- * call),
+ * call, and in a server),
  * or more than 4096 after its workgroup has run for the hand-off time
  * (rei_set_batch_time; 500 us by default),
  * continues from that level on rei_solve's path with its lower levels kept;
@@ -299,9 +299,11 @@ rei_status rei_tune_load(const char *path);
  * its own stream (0 = defaults: 64 per batch, 4 streams, 4 workers).  Each
  * result equals rei_solve's for that instance.  The budget counts the device bytes
  * of requests in flight (an estimate made at submit: the batched arena, or
- * the cache budget plus its table for the per-chunk path); a finished
- * instance keeps its buffers until rei_destroy, so that nothing on the
- * serving path frees device memory (a free waits for the whole device).
+ * the cache budget plus its table for the per-chunk path; the chunk buffers of
+ * a request on the per-chunk path, which take what each chunk needs and
+ * nothing ahead, come on top); a finished instance keeps its buffers until
+ * rei_destroy, so that only buffers that grow are freed on the serving path (a
+ * free waits for the whole device).
  * A submitted instance must not be used by the caller until its ticket
  * reports done.  Calls may come from any host thread. */
 typedef struct rei_server rei_server;
@@ -331,8 +333,9 @@ rei_status rei_trim(rei_instance *inst);
 /* Route the device memory of instances created from now on through the
  * caller's allocator, for a framework that owns the device memory (a caching
  * allocator, say) and hands it out.  alloc(bytes,
- * ctx) returns device memory of the current device or NULL on failure (the
- * call then fails with REI_ERR_DEVICE); free_(ptr, ctx) takes back a pointer
+ * ctx) returns device memory of the current device or NULL on failure (a
+ * search is then run again in less memory; the call fails with REI_ERR_DEVICE
+ * where there is not enough for that); free_(ptr, ctx) takes back a pointer
  * alloc returned.  An instance keeps the pair it was created with for all its
  * allocations and frees, so the pair and ctx must stay valid until every such
  * instance is destroyed.  The library drains the device after each alloc and
@@ -368,8 +371,9 @@ rei_status rei_row_regex(rei_instance *inst, uint32_t cost, uint64_t i, char *bu
 
 /* ---- tuning and measurement ------------------------------------------------ */
 
-/* Largest number of candidates processed per chunk (0 = default).  Results
- * do not depend on it; tests vary it to check that. */
+/* Largest number of candidates processed per chunk (0 = default).  With a size
+ * set, rei_solve takes every level on the per-chunk path, also the first ones.
+ * Results do not depend on it; tests vary it to check that. */
 rei_status rei_set_chunk(rei_instance *inst, uint64_t max_candidates);
 /* Largest level, in candidates, that rei_solve_batch searches inside its
  * one-workgroup solver (0 = the process default for the instance's word
@@ -434,7 +438,11 @@ typedef enum {
  * pair at the kernel's own start and end (for rei_solve_batch: each batched
  * launch, counted on insts[0]); enable = 2: every class (the others with
  * events on the stream around the launch); 0: off.  Turning profiling on
- * clears the statistics; turning it off keeps them. */
+ * clears the statistics; turning it off keeps them.  While it is on,
+ * rei_solve takes every level on the per-chunk path, also the first ones,
+ * which it otherwise runs in one launch of the one-workgroup solver: the
+ * statistics describe those levels' launches, which an unprofiled solve does
+ * not have.  The result is the same. */
 rei_status rei_set_profiling(rei_instance *inst, int enable);
 /* As rei_set_profiling, for the launches of one kernel class only: a caller
  * that needs one class's average launch time leaves every other launch
@@ -446,7 +454,8 @@ rei_status rei_set_profiling_class(rei_instance *inst, rei_kernel_class k);
  * accumulated over the solves since profiling was enabled.  Candidates that
  * need no generation, because an algebraic identity makes them equal to an
  * earlier one, are counted under REI_K_GEN_CHAR, which launches nothing for
- * them. */
+ * them: the generator classes' units add up to all candidates, and that
+ * class's are no measure of its rate. */
 rei_status rei_kernel_stats(const rei_instance *inst, rei_kernel_class k, uint64_t *launches,
                             double *ms, uint64_t *units);
 /* Testing: keep only the low `bits` bits of every language hash (0 = all 64)

@@ -219,8 +219,9 @@ hipError_t launch_account(const ChunkArgs& a, hipStream_t s);
 hipError_t launch_noop_timed(hipStream_t s);
 
 // The answer's expression tree of a per-chunk search, decoded on the device
-// (one thread) from the stored back-pointers, so that the host reads a few
-// hundred bytes instead of the back-pointer array.
+// from the stored back-pointers (one wave: its lanes load the level sizes,
+// lane 0 walks the tree), so that the host reads a few hundred bytes instead
+// of the back-pointer array.
 constexpr uint32_t kTreeMaxLevels = 1024;  // max_cost + 2 at most
 constexpr uint32_t kTreeMaxChars = 64;     // alphabet size at most
 struct TreeArgs {
@@ -369,8 +370,14 @@ constexpr uint32_t kBatchTimeUs = 500;         // default workgroup time before 
 constexpr uint64_t kBatchLevelMax = 1ull << 16;  // default: candidates of one level a workgroup takes on
 // ... of eight words or more per language, when no more instances are that wide
 // than the worker threads run at once: a 64-candidate tile of 16 words keeps a
-// wave 20-30 us, and the device beside it is idle (four instances of 8-16
-// words: 1.10 ms at 2^11, 1.45 ms at 2^16)
+// wave 20-30 us, and the device beside it is idle.  Calls of n instances of
+// 8-16 words to their targets' cost, ms at 2^11 / 2^16: n = 1 1.14 / 1.30, 4
+// 1.16 / 1.32, 6 1.19 / 1.48, 8 1.34 / 1.49, 9 1.21 / 1.50, 16 1.35 / 1.45, 24
+// 1.40 / 1.55, 32 2.29 / 2.34 (other seeds: 8 1.58 / 1.57, 9 1.48 / 1.67, 16
+// 1.55 / 1.69, 32 1.74 / 1.79).  To cost 9: 4 0.62 / 0.77, 8 0.72 / 1.03, 9
+// 0.73 / 1.04, 16 0.77 / 1.01, 32 1.03 / 1.07.  The smaller size never loses
+// where each hand-off finds a worker free, the rule's line; beyond it the
+// searches wait for one another there, and what it gains is gone at 32
 constexpr uint64_t kWideLevelMax = 1ull << 11;
 constexpr uint32_t kBatchTreeNodes = 64; // answer-tree nodes written back (cost <= 63 needs <= 63)
 

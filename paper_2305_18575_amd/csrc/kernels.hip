@@ -802,11 +802,13 @@ __device__ __forceinline__ void toggle_bits(uint32_t* bitmap, uint32_t e, bool o
 // its bit on, one that is displaced has its bit toggled off by the displacing
 // survivor.  Toggles commute, so each winner's bit ends up set and every
 // other clear, whatever the order.  Bound by the table's random atomics
-// (probe and atomicMin reach 14-16 G/s on this card).  One-word languages,
-// 58 infixes, per chunk of up to 16.7 M candidates: 121 us with a marking
-// pass of 75 us that read each slot again, and 48 us for the ordered append,
-// which reset the reference beside each key; now 122 us, none, and 20 us.
-// (One toggle per lane instead of one per run of lanes: 166 us.)
+// (probe and atomicMin reach 14-16 G/s on this card): 169 us a launch, mean of
+// the 89 of a one-word search, 58 infixes, that stores 130 M languages, i.e.
+// 116 ps each for the two atomics on a slot's line; the ordered append 25 us.
+// (Marking the winners in a pass of its own, over the survivors of every
+// candidate, took 75 us per chunk beside an insertion of 121 us and an append
+// of 48 us that reset each reference: 122, none and 20 us on the same chunks
+// with toggles, 166 us with one toggle per lane instead of one per run.)
 template <int W, bool kInl>
 __global__ __launch_bounds__(256) void insert_survivors(ChunkArgs a) {
   if (a.st->stop) return;
@@ -1065,9 +1067,9 @@ __device__ void account_scanned(const ChunkArgs& a, uint32_t winners, Before bef
 
 // Chunks whose bitmap has at most kScanSingleWords words (2^18 candidates,
 // eight words per thread): the whole exclusive scan of the winner bitmap in
-// one workgroup (each thread a contiguous run of words), and the accounting.
-// Replaces the two launches below for the mid-sized chunks a level starts
-// with; larger bitmaps scan faster spread out.
+// one workgroup (each thread a contiguous run of words), and the accounting,
+// one launch of 7 us where scan_reduce and scan_down, which account too, take
+// 5 + 7 us and a gap; larger bitmaps scan faster spread out.
 constexpr uint32_t kScanSingleWords = 8192;
 __global__ __launch_bounds__(1024) void scan_single(ChunkArgs a) {
   __shared__ uint32_t part[1024];
