@@ -157,3 +157,32 @@ def test_graph_replay_after_a_failed_one(rei, calls):
         for h in hs:
             h.close()
         assert not m.live
+
+
+@pytest.mark.parametrize("calls", [0, 2, 7, 20, 60])
+def test_batch_while_allocations_are_refused(rei, calls):
+    """A batch whose searches leave their workgroups early, with so many
+    allocations granted: it ends in an error or in the oracle's results, and
+    the same instances give those once there is memory."""
+    specs = instances.batched_instances(9, 12) + [capped(instances.large_instance(0), 8)]
+    cache = 1 << 30
+    want = oracle_of(specs, cache)
+    with memory(rei) as m:
+        hs = handles(rei, specs, cache)
+        for h in hs:
+            h.set_batch_level(300)
+        m.calls = calls
+        print(f"\n{calls} allocations", flush=True)
+        try:
+            got = rei.solve_batch(hs)
+        except rei.ReiError as e:
+            print(e, flush=True)
+        else:
+            assert_equal(got, want, specs)
+        assert m.refused or m.calls > 0
+        m.calls = 1 << 62
+        for _ in range(2):
+            assert_equal(rei.solve_batch(hs), want, specs)
+        for h in hs:
+            h.close()
+        assert not m.live
