@@ -4131,10 +4131,14 @@ rei_status rei_batch_graph_launch(rei_batch_graph* g, void* hip_stream) {
   }
   G_OK(g, hipSetDevice(g->device));
   if (!g->stale.empty()) {  // an earlier replay's results ended in an error
-    const rei_status r = graph_refresh(g, (hipStream_t)hip_stream);
-    if (r != REI_OK) {
-      g->err = g->batched[g->stale.back()]->err;
-      return r;
+    try {
+      const rei_status r = graph_refresh(g, (hipStream_t)hip_stream);
+      if (r != REI_OK) {
+        g->err = g->batched[g->stale.back()]->err;
+        return r;
+      }
+    } catch (const std::bad_alloc&) {
+      return REI_ERR_HOST_ALLOC;
     }
   }
   for (rei_instance* in : g->batched) {
